@@ -31,6 +31,7 @@
 #include "hp.h"
 #include "hp_internal.h"
 
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -98,10 +99,24 @@ struct ConvArgs {
     // non-null (one output tile, two z-slices per wave, bf16 output): the 2x2x2 mean of the
     // stored activation is written here as well ([coarse voxel][16], grid sizes halved)
     bf16_t* pool_out;
+    // backward-data with the ReLU mask of the layer before it (OUT_GRAD, OUT_CONCAT): that layer's
+    // stored activation, and the per-workgroup channel sums of the masked gradient before its
+    // rounding ([block][channels of mask], the bias gradient's partials)
+    const bf16_t* mask = nullptr;
+    float* csum = nullptr;
+    float* skip = nullptr;  // OUT_CONCAT: gradient of the skip channels [voxel][cout - 16 CU], FP32
 };
 
+// What a convolution stores: the (ReLU'd) activation in bfloat16; plain FP32; the gradient at the
+// output of the layer before it, masked by that layer's ReLU, in bfloat16; or, for an input that is
+// [upsampled, skip], the gradient of the upsampled part summed over the 2x2x2 children and masked
+// like that at the coarse voxels, and the skip part in FP32. The masked forms write 2 bytes per
+// value where an FP32 gradient, its split and a masking pass moved 22: at 128^3 these passes took
+// 1.3 ms of a training step, what is left of them beside the convolutions 0.2 ms.
+enum { OUT_ACT = 0, OUT_F32 = 1, OUT_GRAD = 2, OUT_CONCAT = 3 };
+
 // SPW z-slices per wave: the output brick is 16 x 4 x (4 SPW) voxels.
-template <int CT, int G, int SPW, bool OUT_F32>
+template <int CT, int G, int SPW, int OUT>
 __global__ __launch_bounds__(256) void k_conv_fwd(ConvArgs p) {
     constexpr int CC = 8 * G;                  // channels per LDS chunk
     constexpr int FZ = 4 * SPW, FHZ = FZ + 2, FHV = HX * HY * FHZ;
@@ -291,7 +306,58 @@ __global__ __launch_bounds__(256) void k_conv_fwd(ConvArgs p) {
     // included); a brick inside the grid needs no bounds checks
     const bool full = x0 + BX <= p.nx && y0 + BY <= p.ny && z0 + FZ <= p.nz;
     const int gx = x0 + li;
-    constexpr bool POOL = (CT == 1 && SPW == 2 && !OUT_F32);
+    constexpr int CU = OUT == OUT_CONCAT ? 2 * CT / 3 : 0;   // output tiles of the upsampled part
+    constexpr int CM = OUT == OUT_CONCAT ? CU : CT;          // output tiles that are masked
+    f32x4 cs[OUT >= OUT_GRAD ? CM : 1];                      // channel sums of the masked gradient
+#pragma unroll
+    for (int ct = 0; ct < (OUT >= OUT_GRAD ? CM : 1); ++ct) cs[ct] = f32x4{0.f, 0.f, 0.f, 0.f};
+    // v masked by the activation at `at` (4 channels), stored as bfloat16, added to the channel sums
+    auto mask_store = [&](f32x4 v, int64_t at, f32x4& sum) {
+        const uint2 a = *(const uint2*)(p.mask + at);
+        const unsigned on[4] = {a.x << 16, a.x & 0xffff0000u, a.y << 16, a.y & 0xffff0000u};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = __uint_as_float(on[e]) > 0.f ? v[e] : 0.f;
+        sum += v;
+        *(uint2*)((bf16_t*)p.out + at) = uint2{pack_bf2(v[0], v[1]), pack_bf2(v[2], v[3])};
+    };
+    if constexpr (OUT == OUT_CONCAT) {
+        // The children of a coarse voxel sit in two lanes (x), two rows (y) and two waves (z, handed
+        // over through LDS); they are added one after the other, x fastest.
+        __syncthreads();
+        f32x4* odd = (f32x4*)lds + (wave >> 1) * (4 * CU * 64);
+        if (wave & 1) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+#pragma unroll
+                for (int ct = 0; ct < CU; ++ct) odd[(r * CU + ct) * 64 + lane] = acc[r][ct];
+        }
+        __syncthreads();
+        if (!(wave & 1)) {
+            const int gz = z0 + wave;
+#pragma unroll
+            for (int yp = 0; yp < 2; ++yp) {
+                const int gy = y0 + 2 * yp;
+                const bool in = !(li & 1) && gx < p.nx && gy < p.ny && gz < p.nz;
+                const int64_t vox = ((int64_t)(gz >> 1) * (p.ny >> 1) + (gy >> 1)) * (p.nx >> 1) + (gx >> 1);
+#pragma unroll
+                for (int ct = 0; ct < CU; ++ct) {
+                    f32x4 s = acc[2 * yp][ct];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        s[e] += __shfl_xor(acc[2 * yp][ct][e], 1, 64);
+                        s[e] += acc[2 * yp + 1][ct][e];
+                        s[e] += __shfl_xor(acc[2 * yp + 1][ct][e], 1, 64);
+                    }
+#pragma unroll
+                    for (int y = 0; y < 2; ++y)
+#pragma unroll
+                        for (int x = 0; x < 2; ++x) s += odd[((2 * yp + y) * CU + ct) * 64 + (lane ^ x)];
+                    if (in) mask_store(s, vox * (16 * CU) + ct * 16 + 4 * grp, cs[ct]);
+                }
+            }
+        }
+    }
+    constexpr bool POOL = (CT == 1 && SPW == 2 && OUT == OUT_ACT);
     uint2 stored[POOL ? 4 * SPW : 1];  // the bfloat16 pairs written for each row (pooling)
 #pragma unroll
     for (int sr = 0; sr < (POOL ? 4 * SPW : 1); ++sr) stored[sr] = uint2{0u, 0u};
@@ -301,8 +367,16 @@ __global__ __launch_bounds__(256) void k_conv_fwd(ConvArgs p) {
         if (!full && (gx >= p.nx || gy >= p.ny || gz >= p.nz)) continue;
         const int64_t vox = ((int64_t)gz * p.ny + gy) * p.nx + gx;
 #pragma unroll
-        for (int ct = 0; ct < CT; ++ct) {
+        for (int ct = CU; ct < CT; ++ct) {
             const int o = ct * 16 + 4 * grp;
+            if constexpr (OUT == OUT_CONCAT) {
+                *(f32x4*)(p.skip + vox * (16 * (CT - CU)) + (o - 16 * CU)) = acc[sr][ct];
+                continue;
+            }
+            if constexpr (OUT == OUT_GRAD) {
+                mask_store(acc[sr][ct], vox * p.cout + o, cs[ct]);
+                continue;
+            }
             float v[4];
 #pragma unroll
             for (int e = 0; e < 4; ++e) v[e] = p.relu ? fmaxf(acc[sr][ct][e], 0.f) : acc[sr][ct][e];
@@ -317,7 +391,7 @@ __global__ __launch_bounds__(256) void k_conv_fwd(ConvArgs p) {
                 if (grp == 0) ((float*)p.out)[vox] = part + p.head[HEAD];
                 continue;
             }
-            if (OUT_F32) {
+            if (OUT == OUT_F32) {
                 *(float4*)((float*)p.out + vox * p.cout + o) = make_float4(v[0], v[1], v[2], v[3]);
             } else {
                 uint2 pk;
@@ -363,6 +437,26 @@ __global__ __launch_bounds__(256) void k_conv_fwd(ConvArgs p) {
                 }
             }
         }
+    }
+    if constexpr (OUT >= OUT_GRAD) {
+        // channel sums of the workgroup: over the 16 lanes of a row, then over the waves
+        __syncthreads();
+        float* part = (float*)lds;
+#pragma unroll
+        for (int ct = 0; ct < CM; ++ct)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                float v = cs[ct][e];
+                v += __shfl_xor(v, 1, 64);
+                v += __shfl_xor(v, 2, 64);
+                v += __shfl_xor(v, 4, 64);
+                v += __shfl_xor(v, 8, 64);
+                if (li == 0) part[wave * (16 * CM) + ct * 16 + 4 * grp + e] = v;
+            }
+        __syncthreads();
+        if (tid < 16 * CM)
+            p.csum[(int64_t)bid * (16 * CM) + tid] =
+                (part[tid] + part[16 * CM + tid]) + (part[32 * CM + tid] + part[48 * CM + tid]);
     }
 }
 
@@ -633,89 +727,65 @@ __global__ void k_pool(const bf16_t* __restrict__ in, bf16_t* __restrict__ out, 
     *(uint4*)(out + v * c + 8 * g) = r;
 }
 
-// gradient of pool: g_fine[v][c] += g_coarse[v/2][c] / 8   (FP32)
-__global__ void k_pool_bwd_add(const float* __restrict__ gc, float* __restrict__ gf, int fx, int fy,
-                               int fz, int c) {
-    const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t total = (int64_t)fx * fy * fz * c;
-    if (idx >= total) return;
-    const int ch = (int)(idx % c);
-    const int64_t v = idx / c;
-    const int x = (int)(v % fx), y = (int)((v / fx) % fy), z = (int)(v / ((int64_t)fx * fy));
-    const int64_t cv = ((int64_t)(z >> 1) * (fy >> 1) + (y >> 1)) * (fx >> 1) + (x >> 1);
-    gf[idx] += gc[cv * c + ch] * 0.125f;
-}
+// Gradient at a skip connection's activation, g[v][c] + gpool[v/2][c] / 8 (the 2x2x2 pooling's
+// gradient), masked by the activation and rounded to bfloat16 (the operand of the backward
+// convolutions), with the workgroup's channel sums of the masked value in partial[block][c].
+// A thread takes 8 channels of a voxel, kReluVox voxels per workgroup; bound by its memory traffic
+// (57 us at 128^3 x 16, 4.9 TB/s).
+constexpr int kReluVox = 1024;  // voxels per workgroup
 
-// split the backward-data result of a concatenated input: channels [0, ca) go to ga (summed over
-// the 8 children when that input was upsampled: ga has the coarse size), channels [ca, ca+cb)
-// are added to gb.
-__global__ void k_split_grad(const float* __restrict__ gin, int ca, int cb, int a_up,
-                             float* __restrict__ ga, float* __restrict__ gb, int nx, int ny, int nz) {
-    const int cin = ca + cb;
-    if (a_up) {
-        const int cx = nx >> 1, cy = ny >> 1, cz = nz >> 1;
-        const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-        const int64_t total_a = (int64_t)cx * cy * cz * ca;
-        if (idx < total_a) {
-            const int ch = (int)(idx % ca);
-            const int64_t v = idx / ca;
-            const int x = (int)(v % cx), y = (int)((v / cx) % cy), z = (int)(v / ((int64_t)cx * cy));
-            float s = 0.f;
-            for (int q = 0; q < 8; ++q) {
-                const int64_t fv = ((int64_t)(2 * z + (q >> 2)) * ny + (2 * y + ((q >> 1) & 1))) * nx + (2 * x + (q & 1));
-                s += gin[fv * cin + ch];
-            }
-            ga[idx] = s;
+__global__ __launch_bounds__(256) void k_relu_bwd_pool(const float* __restrict__ g, const float* __restrict__ gpool,
+                                                       const bf16_t* __restrict__ act, bf16_t* __restrict__ gp, int nx,
+                                                       int ny, int64_t nv, int c, float* __restrict__ partial) {
+    __shared__ float sums[256][9];
+    const int tid = threadIdx.x, cg = c >> 3;
+    const int ch = (tid % cg) * 8, step = 256 / cg;
+    const int cx = nx >> 1, cy = ny >> 1;
+    float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    const int64_t v0 = (int64_t)blockIdx.x * kReluVox, v1 = min(v0 + kReluVox, nv);
+    for (int64_t v = v0 + tid / cg; v < v1; v += step) {
+        const int x = (int)(v % nx);
+        const int64_t row = v / nx;
+        const int y = (int)(row % ny);
+        const int64_t z = row / ny;
+        const int64_t cv = ((z >> 1) * cy + (y >> 1)) * cx + (x >> 1);
+        const float4* gv = (const float4*)(g + v * c + ch);
+        const float4* pv = (const float4*)(gpool + cv * c + ch);
+        const float4 a = gv[0], b = gv[1], pa = pv[0], pb = pv[1];
+        const uint4 w = *(const uint4*)(act + v * c + ch);
+        const float val[8] = {a.x + pa.x * 0.125f, a.y + pa.y * 0.125f, a.z + pa.z * 0.125f, a.w + pa.w * 0.125f,
+                              b.x + pb.x * 0.125f, b.y + pb.y * 0.125f, b.z + pb.z * 0.125f, b.w + pb.w * 0.125f};
+        const unsigned u[4] = {w.x, w.y, w.z, w.w};
+        unsigned r[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const float lo = __uint_as_float(u[e] << 16) > 0.f ? val[2 * e] : 0.f;
+            const float hi = __uint_as_float(u[e] & 0xffff0000u) > 0.f ? val[2 * e + 1] : 0.f;
+            acc[2 * e] += lo;
+            acc[2 * e + 1] += hi;
+            r[e] = pack_bf2(lo, hi);
         }
+        *(uint4*)(gp + v * c + ch) = uint4{r[0], r[1], r[2], r[3]};
     }
-    const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t nv = (int64_t)nx * ny * nz;
-    if (cb > 0 && idx < nv * cb) {
-        const int ch = (int)(idx % cb);
-        const int64_t v = idx / cb;
-        gb[idx] += gin[v * cin + ca + ch];
-    }
-    if (!a_up && idx < nv * ca) {
-        const int ch = (int)(idx % ca);
-        const int64_t v = idx / ca;
-        ga[idx] = gin[v * cin + ch];
-    }
-}
-
-// ReLU backward: gp = g * (out > 0) as bf16 (MFMA operand); per-workgroup channel sums of gp
-// (bias gradient partials, partial[block][c])
-__global__ void k_relu_bwd(const float* __restrict__ g, const bf16_t* __restrict__ out,
-                           bf16_t* __restrict__ gp, int64_t nv, int c, float* __restrict__ partial) {
-    __shared__ float sums[256];
-    const int tid = threadIdx.x;
-    // each thread handles channel (tid % c) of voxels strided: c divides 256
-    const int ch = tid % c, vstep = 256 / c;
-    float acc = 0.f;
-    const int64_t vpb = 64;  // voxels per workgroup
-    const int64_t v0 = (int64_t)blockIdx.x * vpb;
-    for (int64_t v = v0 + tid / c; v < v0 + vpb && v < nv; v += vstep) {
-        const int64_t i = v * c + ch;
-        const float val = bf2f(out[i]) > 0.f ? g[i] : 0.f;
-        const bf16_t h = f2bf(val);
-        gp[i] = h;
-        acc += val;
-    }
-    sums[tid] = acc;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) sums[tid][e] = acc[e];
     __syncthreads();
     if (tid < c) {
         float s = 0.f;
-        for (int q = tid; q < 256; q += c) s += sums[q];
+        for (int q = tid >> 3; q < 256; q += cg) s += sums[q][tid & 7];
         partial[(int64_t)blockIdx.x * c + tid] = s;
     }
 }
 
-// column sums of partial[nrows][c]: one workgroup per column, fixed-order tree
-__global__ __launch_bounds__(256) void k_reduce_cols(const float* __restrict__ partial, int nrows, int c,
+// column sums of partial[nrows][stride], columns c0 + blockIdx.x: one workgroup per column,
+// fixed-order tree
+__global__ __launch_bounds__(256) void k_reduce_cols(const float* __restrict__ partial, int nrows, int stride, int c0,
                                                      float* __restrict__ out) {
     __shared__ double sm[256];
     const int ch = blockIdx.x, tid = threadIdx.x;
     double s = 0.0;
-    for (int q = tid; q < nrows; q += 256) s += partial[(int64_t)q * c + ch];
+#pragma unroll 8
+    for (int q = tid; q < nrows; q += 256) s += partial[(int64_t)q * stride + c0 + ch];
     sm[tid] = s;
     __syncthreads();
     for (int w = 128; w > 0; w >>= 1) {
@@ -753,34 +823,63 @@ __global__ void k_loss(const float* __restrict__ y, const float* __restrict__ t,
     if (threadIdx.x == 0) partial[blockIdx.x] = ws[0] + ws[1] + ws[2] + ws[3];
 }
 
-// head backward: gd1[v][c] = gy[v] w[c]; partial[block][c] = sum_v gy d1[v][c]; partial[.][16] = sum gy
-__global__ void k_head_bwd(const float* __restrict__ gy, const bf16_t* __restrict__ d1,
-                           const float* __restrict__ wb, float* __restrict__ gd1, int64_t nv,
-                           float* __restrict__ partial) {
-    __shared__ float sums[17][64];
-    const int tid = threadIdx.x;  // 64 threads, one voxel each per step
-    float acc[17];
+// Head backward with the last layer's ReLU: gp[v][c] = bf16(gy[v] w[c] where d1[v][c] > 0, else 0);
+// partial[block][0..15] = sum gy d1, [16] = sum gy, [17..32] = sum of the masked gradient before
+// its rounding (the last layer's bias gradient). A thread takes half a voxel's channels.
+constexpr int kHeadVox = 1024, kHeadCols = 2 * HEAD + 1;
+
+__global__ __launch_bounds__(256) void k_head_bwd(const float* __restrict__ gy, const bf16_t* __restrict__ d1,
+                                                  const float* __restrict__ wb, bf16_t* __restrict__ gp, int64_t nv,
+                                                  float* __restrict__ partial) {
+    __shared__ float sums[4][kHeadCols];
+    const int tid = threadIdx.x, ch = (tid & 1) * 8, lane = tid & 63, wave = tid >> 6;
+    float hs[8], bs[8], w[8], gs = 0.f;
 #pragma unroll
-    for (int c = 0; c < 17; ++c) acc[c] = 0.f;
-    const int64_t vpb = 256;
-    const int64_t v0 = (int64_t)blockIdx.x * vpb;
-    for (int64_t v = v0 + tid; v < v0 + vpb && v < nv; v += 64) {
+    for (int e = 0; e < 8; ++e) {
+        hs[e] = bs[e] = 0.f;
+        w[e] = wb[ch + e];
+    }
+    const int64_t v0 = (int64_t)blockIdx.x * kHeadVox, v1 = min(v0 + kHeadVox, nv);
+    for (int64_t v = v0 + (tid >> 1); v < v1; v += 128) {
         const float g = gy[v];
+        const uint4 a = *(const uint4*)(d1 + v * HEAD + ch);
+        const unsigned u[4] = {a.x, a.y, a.z, a.w};
+        unsigned r[4];
 #pragma unroll
-        for (int c = 0; c < HEAD; ++c) {
-            gd1[v * HEAD + c] = g * wb[c];
-            acc[c] += g * bf2f(d1[v * HEAD + c]);
+        for (int e = 0; e < 4; ++e) {
+            const float d[2] = {__uint_as_float(u[e] << 16), __uint_as_float(u[e] & 0xffff0000u)};
+            float m[2];
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                m[q] = d[q] > 0.f ? g * w[2 * e + q] : 0.f;
+                hs[2 * e + q] += g * d[q];
+                bs[2 * e + q] += m[q];
+            }
+            r[e] = pack_bf2(m[0], m[1]);
         }
-        acc[16] += g;
+        gs += g;
+        *(uint4*)(gp + v * HEAD + ch) = uint4{r[0], r[1], r[2], r[3]};
     }
+    // lanes of the same channel half
+    auto over = [](float v) {
 #pragma unroll
-    for (int c = 0; c < 17; ++c) sums[c][tid] = acc[c];
-    __syncthreads();
-    if (tid < 17) {
-        float s = 0.f;
-        for (int q = 0; q < 64; ++q) s += sums[tid][q];
-        partial[(int64_t)blockIdx.x * 17 + tid] = s;
+        for (int o = 2; o < 64; o <<= 1) v += __shfl_xor(v, o, 64);
+        return v;
+    };
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        const float a = over(hs[e]), b = over(bs[e]);
+        if (lane < 2) {
+            sums[wave][ch + e] = a;
+            sums[wave][HEAD + 1 + ch + e] = b;
+        }
     }
+    gs = over(gs);
+    if (lane == 0) sums[wave][HEAD] = gs;
+    __syncthreads();
+    if (tid < kHeadCols)
+        partial[(int64_t)blockIdx.x * kHeadCols + tid] =
+            (sums[0][tid] + sums[1][tid]) + (sums[2][tid] + sums[3][tid]);
 }
 
 // x_out = scale * y (scale = s * out_scale), FP64 output
@@ -870,10 +969,10 @@ struct hp_net {
     float* y = nullptr;
     // training buffers
     float *t = nullptr, *gy = nullptr;
-    float* gact[NCONV] = {};  // FP32 gradient at each conv output (pre-mask)
-    float *gp1 = nullptr, *gp2 = nullptr;
-    bf16_t* gpre = nullptr;   // masked gradient (bf16), max size
-    float* gin = nullptr;     // backward-data output, max size
+    // masked gradient (bf16) at the output of the layer in turn, and of the layer before it
+    bf16_t *gpre = nullptr, *gnext = nullptr;
+    float *gskip0 = nullptr, *gskip1 = nullptr;  // gradients of e1 and e2 through their skip connections
+    float *gp1 = nullptr, *gp2 = nullptr;        // gradients of the pooled tensors
     float* wpart = nullptr;   // backward-weight partials
     int64_t wpart_cap = 0;
     float* cpart = nullptr;   // column partials (bias / head)
@@ -920,46 +1019,78 @@ int check() {
     return HP_OK;
 }
 
-// returns whether the launch also wrote the 2x2x2 mean into `pool` (one 16-channel output tile
-// with two z-slices per wave and bf16 output; else the caller pools)
-bool conv_launch(hp_net* N, int l, const bf16_t* a, int ca, int a_up, const bf16_t* b, int cb,
-                 const bf16_t* w, const float* bias, void* out, int cout, int relu, bool out_f32,
-                 const float* head = nullptr, bf16_t* pool = nullptr) {
+// Workgroups of layer l's convolution with `cin` input and `cout` output channels. Two z-slices per
+// wave for the 16-channel outputs (more products per staged brick; four were slower: the larger
+// brick leaves room for fewer workgroups per CU).
+int conv_groups(int cin) { return (cin % 32 == 0) ? 4 : ((cin % 16 == 0) ? 2 : 1); }  // 16-byte groups per chunk voxel
+int conv_slices(int cin, int cout) { return (cout == 16 && conv_groups(cin) <= 2) ? 2 : 1; }
+unsigned conv_blocks(const Level& L, int cin, int cout) {
+    const int fz = 4 * conv_slices(cin, cout);
+    return (unsigned)(((L.nx + BX - 1) / BX) * ((L.ny + BY - 1) / BY) * ((L.nz + fz - 1) / fz));
+}
+
+template <int CT, int G, int SPW, int OUT>
+void conv_start(hp_net* N, const ConvArgs& p, unsigned blocks) {
+    hipLaunchKernelGGL((k_conv_fwd<CT, G, SPW, OUT>), dim3(blocks), dim3(256), 0, N->stream, p);
+}
+
+// Forward convolution of layer l; with `pool` (16-channel outputs) the launch also writes the 2x2x2
+// mean there.
+void conv_launch(hp_net* N, int l, const bf16_t* a, int ca, int a_up, const bf16_t* b, int cb,
+                 const bf16_t* w, const float* bias, void* out, int cout, const float* head, bf16_t* pool) {
     const Level& L = N->lv[level_of_conv(l)];
-    ConvArgs p{a, ca, a_up, b, cb, w, bias, out, cout, L.nx, L.ny, L.nz, relu, head, pool};
-    const int ct = cout / 16;
-    const int cin = ca + cb;
-    // two z-slices per wave for the 16-channel outputs (more products per staged brick; four
-    // were slower: the larger brick leaves room for fewer workgroups per CU)
-    const int g = (cin % 32 == 0) ? 4 : ((cin % 16 == 0) ? 2 : 1);  // 16-byte groups per chunk voxel
-    const int spw = (ct == 1 && g <= 2) ? 2 : 1;
-    const unsigned blocks = (unsigned)(((L.nx + BX - 1) / BX) * ((L.ny + BY - 1) / BY) *
-                                       ((L.nz + 4 * spw - 1) / (4 * spw)));
-#define CONV_LAUNCH2(CTV, GV, SV)                                                                    \
-    if (out_f32)                                                                                     \
-        hipLaunchKernelGGL((k_conv_fwd<CTV, GV, SV, true>), dim3(blocks), dim3(256), 0, N->stream, p); \
-    else                                                                                             \
-        hipLaunchKernelGGL((k_conv_fwd<CTV, GV, SV, false>), dim3(blocks), dim3(256), 0, N->stream, p);
-#define CONV_LAUNCH(CTV, GV)                                                                         \
-    if (CTV == 1 && GV <= 2 && spw == 2) { CONV_LAUNCH2(CTV, GV, 2) } else { CONV_LAUNCH2(CTV, GV, 1) }
-#define CONV_CASE(CTV)                                                                           \
-    case CTV:                                                                                    \
-        if (g == 4) { CONV_LAUNCH(CTV, 4) }                                                      \
-        else if (g == 2) { CONV_LAUNCH(CTV, 2) }                                                 \
-        else { CONV_LAUNCH(CTV, 1) }                                                             \
-        break;
-    switch (ct) {
-        CONV_CASE(1)
-        CONV_CASE(2)
-        CONV_CASE(3)
-        CONV_CASE(4)
-        CONV_CASE(6)
-        default: break;
+    ConvArgs p{a, ca, a_up, b, cb, w, bias, out, cout, L.nx, L.ny, L.nz, 1, head, pool};
+    const int cin = ca + cb, g = conv_groups(cin);
+    const unsigned blocks = conv_blocks(L, cin, cout);
+    switch (cout / 16) {
+        case 1:
+            if (g == 2) conv_start<1, 2, 2, OUT_ACT>(N, p, blocks);
+            else conv_start<1, 1, 2, OUT_ACT>(N, p, blocks);
+            break;
+        case 2:
+            if (g == 4) conv_start<2, 4, 1, OUT_ACT>(N, p, blocks);
+            else conv_start<2, 2, 1, OUT_ACT>(N, p, blocks);
+            break;
+        default: conv_start<4, 4, 1, OUT_ACT>(N, p, blocks); break;
     }
-#undef CONV_CASE
-#undef CONV_LAUNCH
-#undef CONV_LAUNCH2
-    return pool && ct == 1 && spw == 2 && !out_f32;
+}
+
+// Backward-data convolution of layer l: the masked gradient gpre with the flipped, transposed
+// weights. The gradient of its input goes, masked by the ReLU of the layer before it, to gnext with
+// the channel sums in cpart (layers 9, 7, 5, 3, 1), for the concatenated inputs of layers 8 and 6
+// only the upsampled part with the skip part in `f32`, and plainly to `f32` for the pooled inputs of
+// layers 4 and 2. Returns the number of channel-sum rows.
+int conv_backward_data(hp_net* N, int l, float* f32) {
+    const Level& L = N->lv[level_of_conv(l)];
+    const unsigned blocks = conv_blocks(L, COUT[l], CIN[l]);
+    ConvArgs p{N->gpre, COUT[l], 0, nullptr, 0, N->wbk[l], nullptr, N->gnext, CIN[l], L.nx, L.ny, L.nz, 0, nullptr,
+               nullptr};
+    p.csum = N->cpart;
+    p.mask = l > 0 ? N->act[l - 1] : nullptr;
+    switch (l) {
+        case 9:
+        case 1: conv_start<1, 2, 2, OUT_GRAD>(N, p, blocks); break;
+        case 7:
+        case 3: conv_start<2, 4, 1, OUT_GRAD>(N, p, blocks); break;
+        case 5: conv_start<4, 4, 1, OUT_GRAD>(N, p, blocks); break;
+        case 8:
+            p.skip = f32;
+            conv_start<3, 2, 1, OUT_CONCAT>(N, p, blocks);
+            break;
+        case 6:
+            p.skip = f32;
+            conv_start<6, 4, 1, OUT_CONCAT>(N, p, blocks);
+            break;
+        case 4:
+            p.out = f32;
+            conv_start<2, 4, 1, OUT_F32>(N, p, blocks);
+            break;
+        default:  // 2
+            p.out = f32;
+            conv_start<1, 4, 1, OUT_F32>(N, p, blocks);
+            break;
+    }
+    return (int)blocks;
 }
 
 // conv input tensors of layer l in the forward pass
@@ -995,13 +1126,7 @@ int pack_weights(hp_net* N) {
 }
 
 int forward_net(hp_net* N) {
-    bool pooled1 = false;  // layer 1 wrote pool(e1) in its epilogue
     for (int l = 0; l < NCONV; ++l) {
-        if (l == 2 && !pooled1) {
-            const Level& L = N->lv[1];
-            hipLaunchKernelGGL(k_pool, dim3(nblk(L.nv * 2)), dim3(256), 0, N->stream, N->act[1], N->p1,
-                               L.nx, L.ny, L.nz, 16);
-        }
         if (l == 4) {
             const Level& L = N->lv[2];
             hipLaunchKernelGGL(k_pool, dim3(nblk(L.nv * 4)), dim3(256), 0, N->stream, N->act[3], N->p2,
@@ -1011,10 +1136,10 @@ int forward_net(hp_net* N) {
         // without training the last layer's activation is only needed by the head, which then
         // runs in that convolution's epilogue
         const bool fuse_head = l == NCONV - 1 && !N->training;
-        const bool done = conv_launch(N, l, in.a, in.ca, in.a_up, in.b, in.cb, N->wf[l], N->theta + N->boff[l],
-                                      fuse_head ? (void*)N->y : (void*)N->act[l], COUT[l], 1, false,
-                                      fuse_head ? N->theta + N->hoff : nullptr, l == 1 ? N->p1 : nullptr);
-        if (l == 1) pooled1 = done;
+        // layer 1 pools in its epilogue
+        conv_launch(N, l, in.a, in.ca, in.a_up, in.b, in.cb, N->wf[l], N->theta + N->boff[l],
+                    fuse_head ? (void*)N->y : (void*)N->act[l], COUT[l], fuse_head ? N->theta + N->hoff : nullptr,
+                    l == 1 ? N->p1 : nullptr);
     }
     if (N->training) {
         const Level& L = N->lv[0];
@@ -1033,32 +1158,46 @@ int rhs_scale(hp_net* N, const double* b) {
     return check();
 }
 
-// backward of one conv layer: gradient at its output gact[l] (FP32, before the ReLU mask) ->
-// parameter gradients, and (if l > 0) the gradient of its input written into gin.
-int backward_conv(hp_net* N, int l) {
+// Weight gradient of layer l from its masked output gradient in gpre.
+void weight_gradient(hp_net* N, int l) {
     const Level& L = N->lv[level_of_conv(l)];
-    const int co = COUT[l], cinp = cin_pad(l);
-    // mask + bias gradient partials
-    const int64_t rows = (L.nv + 63) / 64;
-    hipLaunchKernelGGL(k_relu_bwd, dim3((unsigned)rows), dim3(256), 0, N->stream, N->gact[l], N->act[l],
-                       N->gpre, L.nv, co, N->cpart);
-    hipLaunchKernelGGL(k_reduce_cols, dim3(co), dim3(256), 0, N->stream, N->cpart, (int)rows, co,
-                       N->grad + N->boff[l]);
-    // weight gradient
+    const int co = COUT[l];
     ConvIn in = conv_inputs(N, l);
-    const int chunks = (cinp + 15) / 16;
+    // channel chunks of 16 (the first layer's 8 padded channels read as 8 + 8 zeros)
+    const int chunks = (cin_pad(l) + 15) / 16;
     const int nbr = ((L.nx + BX - 1) / BX) * ((L.ny + BY - 1) / BY) * ((L.nz + WZ - 1) / WZ);
     const int parts = std::min(nbr, std::max(1, kBwdWGroups / (chunks * (co / 16))));
     BwdWArgs bw{N->gpre, co, in.a, in.ca, in.a_up, in.b, in.cb, N->wpart, L.nx, L.ny, L.nz};
-    // channel chunks of 16 (the first layer's 8 padded channels read as 8 + 8 zeros)
     hipLaunchKernelGGL(k_conv_bwd_w, dim3(parts, chunks, co / 16), dim3(256), 0, N->stream, bw);
     const int n = co * 27 * CIN[l];
     hipLaunchKernelGGL(k_reduce_dw, dim3(nblk(n, 16)), dim3(256), 0, N->stream, N->wpart, parts, chunks, co, CIN[l],
                        N->grad + N->woff[l]);
-    if (l == 0) return check();
-    // input gradient: forward conv of the masked gradient with flipped/transposed weights
-    conv_launch(N, l, N->gpre, co, 0, nullptr, 0, N->wbk[l], nullptr, N->gin, CIN[l], 0, true);
-    return check();
+}
+
+// out[0..c) = column sums of cpart[rows][stride] from column c0 on
+void column_sums(hp_net* N, int rows, int stride, int c0, int c, float* out) {
+    hipLaunchKernelGGL(k_reduce_cols, dim3(c), dim3(256), 0, N->stream, N->cpart, rows, stride, c0, out);
+}
+
+// Backward of layer l from its masked output gradient in gpre: its weight gradient, then the
+// gradient of its input (see conv_backward_data). Where that is the masked gradient of layer
+// l - 1's output, it becomes gpre and that layer's bias gradient is formed.
+void backward_conv(hp_net* N, int l, float* f32 = nullptr) {
+    weight_gradient(N, l);
+    if (l == 0) return;
+    const int rows = conv_backward_data(N, l, f32);
+    if (l == 4 || l == 2) return;
+    column_sums(N, rows, COUT[l - 1], 0, COUT[l - 1], N->grad + N->boff[l - 1]);
+    std::swap(N->gpre, N->gnext);
+}
+
+// Masked gradient of the skip activation of layer l (1 or 3) into gpre, and its bias gradient.
+void backward_skip(hp_net* N, int l, const float* g, const float* gpool) {
+    const Level& L = N->lv[level_of_conv(l)];
+    const unsigned rows = nblk(L.nv, kReluVox);
+    hipLaunchKernelGGL(k_relu_bwd_pool, dim3(rows), dim3(256), 0, N->stream, g, gpool, N->act[l], N->gpre, L.nx, L.ny,
+                       L.nv, COUT[l], N->cpart);
+    column_sums(N, (int)rows, COUT[l], 0, COUT[l], N->grad + N->boff[l]);
 }
 
 }  // namespace
@@ -1131,14 +1270,17 @@ int hp_nn_create(int nx, int ny, int nz, int training, hp_net** out) {
         if ((rc = nalloc(N, &N->grad, N->nparam)) || (rc = nalloc(N, &N->m, N->nparam)) ||
             (rc = nalloc(N, &N->v, N->nparam)) || (rc = nalloc(N, &N->t, V)) || (rc = nalloc(N, &N->gy, V)))
             return bail(rc);
-        for (int l = 0; l < NCONV; ++l)
-            if ((rc = nalloc(N, &N->gact[l], N->lv[level_of_conv(l)].nv * COUT[l]))) return bail(rc);
-        if ((rc = nalloc(N, &N->gp1, N->lv[1].nv * 16)) || (rc = nalloc(N, &N->gp2, N->lv[2].nv * 32)) ||
-            (rc = nalloc(N, &N->gpre, V * 16 > N->lv[1].nv * 32 ? V * 16 : N->lv[1].nv * 32)) ||
-            (rc = nalloc(N, &N->gin, std::max(V * 48, N->lv[1].nv * 96))))
+        const int64_t most = std::max(V * 16, N->lv[1].nv * 32);
+        if ((rc = nalloc(N, &N->gpre, most)) || (rc = nalloc(N, &N->gnext, most)) ||
+            (rc = nalloc(N, &N->gskip0, V * 16)) || (rc = nalloc(N, &N->gskip1, N->lv[1].nv * 32)) ||
+            (rc = nalloc(N, &N->gp1, N->lv[1].nv * 16)) || (rc = nalloc(N, &N->gp2, N->lv[2].nv * 32)))
             return bail(rc);
         N->wpart_cap = (int64_t)kBwdWGroups * 16 * 27 * 16;
-        N->cpart_cap = std::max<int64_t>((V + 63) / 64 * 16, (V + 255) / 256 * 17) + 64;
+        // channel-sum rows of the head, of the two skip activations and of the backward convolutions
+        N->cpart_cap = std::max<int64_t>({(int64_t)nblk(V, kHeadVox) * kHeadCols, (int64_t)nblk(V, kReluVox) * COUT[1],
+                                          (int64_t)nblk(N->lv[1].nv, kReluVox) * COUT[3]});
+        for (int l : {9, 8, 7, 6, 5, 3, 1})
+            N->cpart_cap = std::max(N->cpart_cap, (int64_t)conv_blocks(N->lv[level_of_conv(l)], COUT[l], CIN[l]) * COUT[l - 1]);
         if ((rc = nalloc(N, &N->wpart, N->wpart_cap)) || (rc = nalloc(N, &N->cpart, N->cpart_cap)))
             return bail(rc);
         hipLaunchKernelGGL(k_zero_f32, dim3(nblk(N->nparam)), dim3(256), 0, 0, N->m, N->nparam);
@@ -1247,48 +1389,26 @@ int hp_nn_forward_raw(hp_net* N, const unsigned short* in, float* y) {
 
 // backward pass from the output gradient in gy (FP32, network units) to the parameter gradient
 int backward_net(hp_net* N) {
-    const Level& L0 = N->lv[0];
-    const int64_t V = L0.nv;
-    int rc;
-    // head
-    const int64_t hrows = (V + 255) / 256;
-    hipLaunchKernelGGL(k_head_bwd, dim3((unsigned)hrows), dim3(64), 0, N->stream, N->gy, N->act[9],
-                       N->theta + N->hoff, N->gact[9], V, N->cpart);
-    hipLaunchKernelGGL(k_reduce_cols, dim3(17), dim3(256), 0, N->stream, N->cpart, (int)hrows, 17,
-                       N->grad + N->hoff);
+    const int64_t V = N->lv[0].nv;
+    // head, and the masked gradient of the last layer's output
+    const unsigned rows = nblk(V, kHeadVox);
+    hipLaunchKernelGGL(k_head_bwd, dim3(rows), dim3(256), 0, N->stream, N->gy, N->act[9], N->theta + N->hoff, N->gpre,
+                       V, N->cpart);
+    column_sums(N, (int)rows, kHeadCols, 0, HEAD + 1, N->grad + N->hoff);
+    column_sums(N, (int)rows, kHeadCols, HEAD + 1, HEAD, N->grad + N->boff[9]);
     // decoder and encoder in reverse
-    const Level& L1 = N->lv[1];
-    const Level& L2 = N->lv[2];
-    if ((rc = backward_conv(N, 9))) return rc;                 // gin = d(act8) (16 ch, n)
-    hipLaunchKernelGGL(k_split_grad, dim3(nblk(V * 16)), dim3(256), 0, N->stream, N->gin, 16, 0, 0,
-                       N->gact[8], nullptr, L0.nx, L0.ny, L0.nz);
-    if ((rc = backward_conv(N, 8))) return rc;                 // gin = d[up(act7), act1] (48 ch, n)
-    hipLaunchKernelGGL(k_zero_f32, dim3(nblk(V * 16)), dim3(256), 0, N->stream, N->gact[1], V * 16);
-    hipLaunchKernelGGL(k_split_grad, dim3(nblk(std::max(V * 16, L1.nv * 32))), dim3(256), 0, N->stream,
-                       N->gin, 32, 16, 1, N->gact[7], N->gact[1], L0.nx, L0.ny, L0.nz);
-    if ((rc = backward_conv(N, 7))) return rc;                 // gin = d(act6) (32 ch, n/2)
-    hipLaunchKernelGGL(k_split_grad, dim3(nblk(L1.nv * 32)), dim3(256), 0, N->stream, N->gin, 32, 0, 0,
-                       N->gact[6], nullptr, L1.nx, L1.ny, L1.nz);
-    if ((rc = backward_conv(N, 6))) return rc;                 // gin = d[up(act5), act3] (96 ch, n/2)
-    hipLaunchKernelGGL(k_zero_f32, dim3(nblk(L1.nv * 32)), dim3(256), 0, N->stream, N->gact[3], L1.nv * 32);
-    hipLaunchKernelGGL(k_split_grad, dim3(nblk(std::max(L1.nv * 32, L2.nv * 64))), dim3(256), 0, N->stream,
-                       N->gin, 64, 32, 1, N->gact[5], N->gact[3], L1.nx, L1.ny, L1.nz);
-    if ((rc = backward_conv(N, 5))) return rc;                 // gin = d(act4) (64 ch, n/4)
-    hipLaunchKernelGGL(k_split_grad, dim3(nblk(L2.nv * 64)), dim3(256), 0, N->stream, N->gin, 64, 0, 0,
-                       N->gact[4], nullptr, L2.nx, L2.ny, L2.nz);
-    if ((rc = backward_conv(N, 4))) return rc;                 // gin = d(p2) (32 ch, n/4)
-    hipLaunchKernelGGL(k_pool_bwd_add, dim3(nblk(L1.nv * 32)), dim3(256), 0, N->stream, N->gin, N->gact[3],
-                       L1.nx, L1.ny, L1.nz, 32);
-    if ((rc = backward_conv(N, 3))) return rc;                 // gin = d(act2) (32 ch, n/2)
-    hipLaunchKernelGGL(k_split_grad, dim3(nblk(L1.nv * 32)), dim3(256), 0, N->stream, N->gin, 32, 0, 0,
-                       N->gact[2], nullptr, L1.nx, L1.ny, L1.nz);
-    if ((rc = backward_conv(N, 2))) return rc;                 // gin = d(p1) (16 ch, n/2)
-    hipLaunchKernelGGL(k_pool_bwd_add, dim3(nblk(V * 16)), dim3(256), 0, N->stream, N->gin, N->gact[1],
-                       L0.nx, L0.ny, L0.nz, 16);
-    if ((rc = backward_conv(N, 1))) return rc;                 // gin = d(act0) (16 ch, n)
-    hipLaunchKernelGGL(k_split_grad, dim3(nblk(V * 16)), dim3(256), 0, N->stream, N->gin, 16, 0, 0,
-                       N->gact[0], nullptr, L0.nx, L0.ny, L0.nz);
-    if ((rc = backward_conv(N, 0))) return rc;
+    backward_conv(N, 9);
+    backward_conv(N, 8, N->gskip0);  // [up(act7), act1]
+    backward_conv(N, 7);
+    backward_conv(N, 6, N->gskip1);  // [up(act5), act3]
+    backward_conv(N, 5);
+    backward_conv(N, 4, N->gp2);
+    backward_skip(N, 3, N->gskip1, N->gp2);
+    backward_conv(N, 3);
+    backward_conv(N, 2, N->gp1);
+    backward_skip(N, 1, N->gskip0, N->gp1);
+    backward_conv(N, 1);
+    backward_conv(N, 0);
     return check();
 }
 
