@@ -20,7 +20,7 @@
 // gradient or divergence. The interface value of rho kappa_c is the mean of its two cells.
 //
 // Both passes walk z columns over natural-order FP64 arrays (HBM-bound, about 1 flop per byte):
-// workgroups of 64 x 4 columns in x and y so that x neighbours come from the same cache lines and
+// workgroups of 64 columns in x and a few rows in y so that x neighbours come from the same cache lines and
 // y neighbours from rows the workgroup itself loads; the z neighbours stay in registers.
 #include "hp.h"
 #include "hp_internal.h"
@@ -51,11 +51,6 @@ __device__ __forceinline__ int64_t cell(const HGeo& g, int i, int j, int k) {
     return i + (int64_t)g.n[0] * (j + (int64_t)g.n[1] * k);
 }
 
-// flat index of the neighbour of (i, j, k) along d at coordinate t
-__device__ __forceinline__ int64_t along(const HGeo& g, int i, int j, int k, int d, int t) {
-    return d == 0 ? cell(g, t, j, k) : d == 1 ? cell(g, i, t, k) : cell(g, i, j, t);
-}
-
 // eq. pbnd: the pressure at the interface between cells a and b
 __device__ __forceinline__ double pbnd(double pa, double ra, double pb, double rb) {
     return (pb * ra + pa * rb) / (ra + rb);
@@ -68,15 +63,25 @@ struct RhsArgs {
     double* b;
 };
 
-// z planes per thread column in the two passes around the solve
-constexpr int kHZ = 16;
+// z planes per chunk of a column pass with `tiles` column tiles per plane and `threads` threads per
+// workgroup: up to 32, fewer (not under 2) where the launch would leave the 256 CUs short of 2048
+// threads each. A chunk loads its first planes' z neighbours again, so longer ones read less; at
+// 48 x 32 x 44 chunks of 2 against 4 planes took the update from 10.1 to 7.0 us, at 96 x 80 x 72
+// (16 before) from 39.6 to 19.8, and single planes made the advection there slower (25 for 22).
+static int hydro_chunk(int nz, int64_t tiles, int threads) {
+    const int64_t want = (int64_t)256 * 2048 / threads;   // workgroups that fill the GPU once
+    const int64_t kz = nz * tiles / want;
+    return (int)(kz < 2 ? 2 : kz > 32 ? 32 : kz);
+}
 
-// Column tile (64 x 4 columns, one chunk of kHZ planes) of this workgroup of a 1-D grid. The
+constexpr int kHRows = 4;  // rows of a column tile
+
+// Column tile (64 x kHRows columns, one chunk of kz planes) of this workgroup of a 1-D grid. The
 // hardware hands workgroup L to XCD L % 8; numbering the tiles so that each XCD takes one
 // contiguous range of them (whole x-y planes of chunks) keeps the y neighbour rows of a tile in
 // the L2 of the XCD that reads them.
 struct HTiles {
-    int tx, ty, tz;
+    int tx, ty, tz, kz;
 };
 
 __device__ __forceinline__ void htile(const HTiles& t, int& i, int& j, int& k0) {
@@ -84,12 +89,14 @@ __device__ __forceinline__ void htile(const HTiles& t, int& i, int& j, int& k0) 
     unsigned L = blockIdx.x;
     if ((total & 7u) == 0) L = (L & 7u) * (total >> 3) + (L >> 3);
     i = (int)(L % (unsigned)t.tx) * 64 + (threadIdx.x & 63);
-    j = (int)((L / (unsigned)t.tx) % (unsigned)t.ty) * 4 + (threadIdx.x >> 6);
-    k0 = (int)(L / ((unsigned)t.tx * t.ty)) * kHZ;
+    j = (int)((L / (unsigned)t.tx) % (unsigned)t.ty) * kHRows + (threadIdx.x >> 6);
+    k0 = (int)(L / ((unsigned)t.tx * t.ty)) * t.kz;
 }
 
 static HTiles htiles(const int n[3]) {
-    return HTiles{(n[0] + 63) / 64, (n[1] + 3) / 4, (n[2] + kHZ - 1) / kHZ};
+    const int tx = (n[0] + 63) / 64, ty = (n[1] + kHRows - 1) / kHRows;
+    const int kz = hydro_chunk(n[2], (int64_t)tx * ty, 64 * kHRows);
+    return HTiles{tx, ty, (n[2] + kz - 1) / kz, kz};
 }
 
 // Neighbours of the cells of one axis, as the three values (low neighbour, cell, high neighbour)
@@ -143,7 +150,7 @@ __device__ __forceinline__ void load_line(const HGeo& g, const RhsArgs& A, const
     }
 }
 
-// One thread per (x, y) column walking kHZ planes: the x and y neighbours come from memory (the
+// One thread per (x, y) column walking kz planes: the x and y neighbours come from memory (the
 // x ones from the same cache lines), the z neighbours of the six stencil arrays from a ring of
 // registers (each plane is loaded once per column). Every load of a plane is issued whatever the
 // geometry (a missing neighbour, or an axis of one cell, reads the cell itself and contributes
@@ -151,12 +158,12 @@ __device__ __forceinline__ void load_line(const HGeo& g, const RhsArgs& A, const
 // for the next plane's z loads before using this plane's values.
 // TC: the two-component terms (temp_n, conc_n, rkc_n given); VISC: the viscous term (visc given).
 template <bool TC, bool VISC>
-__global__ __launch_bounds__(256) void k_pressure_rhs(HGeo g, HTiles t, RhsArgs A) {
+__global__ __launch_bounds__(64 * kHRows) void k_pressure_rhs(HGeo g, HTiles t, RhsArgs A) {
     int i, j, k0;
     htile(t, i, j, k0);
     if (i >= g.n[0] || j >= g.n[1]) return;
     const int nz = g.n[2];
-    const int k1 = min(k0 + kHZ, nz);
+    const int k1 = min(k0 + t.kz, nz);
     const int64_t sxy = (int64_t)g.n[0] * g.n[1];
     constexpr bool tc = TC;
     const double ih[3] = {1.0 / g.h[0], 1.0 / g.h[1], 1.0 / g.h[2]};
@@ -227,12 +234,12 @@ __device__ __forceinline__ double upd_axis(bool lo, bool hi, const double* p, co
     return (phi - plo) * ih;
 }
 
-__global__ __launch_bounds__(256) void k_pressure_update(HGeo g, HTiles t, UpdArgs A) {
+__global__ __launch_bounds__(64 * kHRows) void k_pressure_update(HGeo g, HTiles t, UpdArgs A) {
     int i, j, k0;
     htile(t, i, j, k0);
     if (i >= g.n[0] || j >= g.n[1]) return;
     const int nz = g.n[2];
-    const int k1 = min(k0 + kHZ, nz);
+    const int k1 = min(k0 + t.kz, nz);
     const int64_t sxy = (int64_t)g.n[0] * g.n[1];
     const double ih[3] = {1.0 / g.h[0], 1.0 / g.h[1], 1.0 / g.h[2]};
     const double* msz = A.mom_star + 2 * A.N;
@@ -292,10 +299,10 @@ __global__ __launch_bounds__(256) void k_pressure_update(HGeo g, HTiles t, UpdAr
 
 // ---- the explicit advective part (steps (i)-(iii)) and the equation of state ----
 
-// q at distance s (+-1, +-2) along axis d from coordinate c: wrapped on a periodic axis, the edge
-// cell repeated beyond a closed boundary (a zero-gradient mirror for the reconstruction)
-__device__ __forceinline__ int reach(const HGeo& g, int d, int c, int s) {
-    int q = c + s;
+// the cell that stands at coordinate q along axis d, up to a few past either end: wrapped on a
+// periodic axis, the edge cell repeated beyond a closed boundary (a zero-gradient mirror for the
+// reconstruction)
+__device__ __forceinline__ int reach(const HGeo& g, int d, int q) {
     const int n = g.n[d];
     if (g.per[d]) return ((q % n) + n) % n;
     return q < 0 ? 0 : (q >= n ? n - 1 : q);
@@ -304,50 +311,151 @@ __device__ __forceinline__ int reach(const HGeo& g, int d, int c, int s) {
 // second-order ENO: the smaller in magnitude of the two one-sided differences (ties: the second)
 __device__ __forceinline__ double eno_slope(double dm, double dp) { return fabs(dm) < fabs(dp) ? dm : dp; }
 
-// the value at the interface between cells q1 (low) and q2 (high), reconstructed on the upwind
-// side of the interface velocity u from the cells q0 .. q3 around it
-__device__ __forceinline__ double eno_face(double u, double q0, double q1, double q2, double q3) {
-    return u >= 0.0 ? q1 + 0.5 * eno_slope(q1 - q0, q2 - q1) : q2 - 0.5 * eno_slope(q2 - q1, q3 - q2);
+// the flux through the interface between cells of values ql (low) and qh (high) and slopes sl, sh,
+// the value reconstructed on the upwind side of the interface velocity u (selected, then added: a
+// choice between two sums compiles to divergent branches)
+__device__ __forceinline__ double eno_flux(double u, double ql, double sl, double qh, double sh) {
+    const bool up = u >= 0.0;
+    const double q = up ? ql : qh, s = up ? sl : -sh;
+    return u * (q + 0.5 * s);
+}
+
+// flux through the high interface of a cell minus that through its low one, from the cells at
+// -2 .. +2 along the axis
+__device__ __forceinline__ double axis_div(double ul, double uh, double v0, double v1, double v2, double v3, double v4) {
+    const double d0 = v1 - v0, d1 = v2 - v1, d2 = v3 - v2, d3 = v4 - v3;
+    const double s = eno_slope(d1, d2);
+    return eno_flux(uh, v2, s, v3, eno_slope(d2, d3)) - eno_flux(ul, v1, eno_slope(d0, d1), v2, s);
+}
+
+// eq. step1: the interface velocity from the momenta and densities of its two cells; zero at a
+// closed boundary
+__device__ __forceinline__ double step1(bool face, double ma, double mb, double ra, double rb) {
+    return face ? (ma + mb) / (ra + rb) : 0.0;
 }
 
 struct AdvArgs {
-    const double *rho, *mom, *e;
-    double *rho_out, *mom_out, *e_out;
-    int64_t N;
+    const double* q[5];  // rho, the three momenta, e
+    double* out[5];
 };
 
-// One thread per cell: for every axis the fluxes through the cell's low and high interfaces of the
-// five conserved fields (rho, three momenta, e), each interface velocity from eq. step1 and each
-// field value reconstructed on its upwind side; q* = q - dt div(flux).
-__global__ __launch_bounds__(256) void k_advect(HGeo g, AdvArgs A) {
-    const int i = blockIdx.x * 64 + (threadIdx.x & 63);
-    const int j = blockIdx.y * 4 + (threadIdx.x >> 6);
-    const int k = blockIdx.z;
-    if (i >= g.n[0] || j >= g.n[1]) return;
-    const int c[3] = {i, j, k};
-    const int64_t a = cell(g, i, j, k);
-    const double* q[5] = {A.rho, A.mom, A.mom + A.N, A.mom + 2 * A.N, A.e};
-    double div[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
-    for (int d = 0; d < 3; ++d) {
-        if (g.n[d] == 1) continue;
-        int64_t b[5];  // cells at -2 .. +2 along d
-        for (int s = -2; s <= 2; ++s) b[s + 2] = along(g, i, j, k, d, reach(g, d, c[d], s));
-        const double* md = A.mom + (int64_t)d * A.N;
-        // interface velocities of eq. step1; zero at a closed boundary
-        const bool hi = g.per[d] || c[d] < g.n[d] - 1, lo = g.per[d] || c[d] > 0;
-        const double uh = hi ? (md[a] + md[b[3]]) / (A.rho[a] + A.rho[b[3]]) : 0.0;
-        const double ul = lo ? (md[b[1]] + md[a]) / (A.rho[b[1]] + A.rho[a]) : 0.0;
+// Column tiles of the advection: 32 x 8 columns (whole 256-byte lines in x, and the fewest halo cells
+// that leaves), chunks of kz planes.
+constexpr int kAdvX = 32, kAdvY = 8, kAdvThreads = kAdvX * kAdvY;
+static_assert(4 * kAdvX + 4 * kAdvY <= kAdvThreads, "one halo cell per thread");
+
+// q* = q - dt div(flux) for the five conserved fields (rho, three momenta, e), the fluxes through
+// the interfaces of every cell from eq. step1 and the upwind reconstruction.
+//
+// A workgroup walks a tile of columns through kz planes. Each plane of the tile goes through LDS
+// with two cells of halo on every side (own cells from registers, one halo cell per thread from
+// memory), so the eight x and y neighbours of a field cost one load; the z neighbours stay in a
+// ring of four planes, and the flux through a cell's low z interface is the one its lower
+// neighbour computed. The next plane's loads are in flight while a plane is computed. Bound by
+// memory: 380 us at 256^3 for 1.4 GB read (the halo rows come from beyond the L2 as often as not)
+// and 0.67 GB written; one thread per cell, with every neighbour from memory and every flux
+// twice, took 1041 us. Tiles of 512 threads left one workgroup per CU (510 us) or spilled.
+__global__ __launch_bounds__(kAdvThreads, 3) void k_advect(HGeo g, HTiles t, AdvArgs A) {
+    constexpr int TX = kAdvX, TY = kAdvY, PX = TX + 4, PY = TY + 4;
+    __shared__ double tile[2][5][PY * PX];
+    // each XCD takes one contiguous range of tiles (see htile)
+    const unsigned total = (unsigned)t.tx * t.ty * t.tz;
+    unsigned L = blockIdx.x;
+    if ((total & 7u) == 0) L = (L & 7u) * (total >> 3) + (L >> 3);
+    const int x0 = (int)(L % (unsigned)t.tx) * TX, y0 = (int)((L / (unsigned)t.tx) % (unsigned)t.ty) * TY;
+    const int k0 = (int)(L / ((unsigned)t.tx * t.ty)) * t.kz, k1 = min(k0 + t.kz, g.n[2]);
+    const int tid = threadIdx.x, lx = tid % TX, ly = tid / TX;
+    const int nx = g.n[0], ny = g.n[1], nz = g.n[2];
+    const int i = x0 + lx, j = y0 + ly;
+    // Positions past the end of an axis hold what its last cells see there (their halo); nothing
+    // past the second is read by a cell of the grid.
+    auto colx = [&](int q) { return reach(g, 0, min(q, nx + 1)); };
+    auto coly = [&](int q) { return reach(g, 1, min(q, ny + 1)); };
+    const int64_t sxy = (int64_t)nx * ny;
+    const int own = colx(i) + nx * coly(j);
+    // the thread's halo cell: two rows below and above the tile, two columns left and right
+    int hx = 0, hy = 0;
+    const bool halo = tid < 4 * TX + 4 * TY;
+    if (tid < 4 * TX) {
+        const int r = tid / TX;
+        hx = lx;
+        hy = r < 2 ? r - 2 : TY + r - 2;
+    } else if (halo) {
+        const int c = (tid - 4 * TX) & 3;
+        hx = c < 2 ? c - 2 : TX + c - 2;
+        hy = (tid - 4 * TX) >> 2;
+    }
+    const int hcell = colx(x0 + hx) + nx * coly(y0 + hy);
+    const int hat = (hy + 2) * PX + hx + 2, at = (ly + 2) * PX + lx + 2;
+    const double ih[3] = {1.0 / g.h[0], 1.0 / g.h[1], 1.0 / g.h[2]};
+    const bool xl = g.per[0] || i > 0, xh = g.per[0] || i < nx - 1;
+    const bool yl = g.per[1] || j > 0, yh = g.per[1] || j < ny - 1;
+    const bool inside = i < nx && j < ny;
+
+    double q0[5], q1[5], q2[5], q3[5], fz[5], hv[5];
+    auto load = [&](double* v, int cell_, int k) {
+        const int64_t a = cell_ + (int64_t)reach(g, 2, k) * sxy;
+#pragma unroll
+        for (int f = 0; f < 5; ++f) v[f] = A.q[f][a];
+    };
+    load(q0, own, k0 - 2);
+    load(q1, own, k0 - 1);
+    load(q2, own, k0);
+    load(q3, own, k0 + 1);
+    load(hv, hcell, k0);
+    {
+        const double u = step1(g.per[2] || k0 > 0, q1[3], q2[3], q1[0], q2[0]);
+#pragma unroll
         for (int f = 0; f < 5; ++f) {
-            const double* qf = q[f];
-            const double v0 = qf[b[0]], v1 = qf[b[1]], v2 = qf[a], v3 = qf[b[3]], v4 = qf[b[4]];
-            const double fh = uh * eno_face(uh, v1, v2, v3, v4);
-            const double fl = ul * eno_face(ul, v0, v1, v2, v3);
-            div[f] += (fh - fl) / g.h[d];
+            const double d1 = q2[f] - q1[f];
+            fz[f] = eno_flux(u, q1[f], eno_slope(q1[f] - q0[f], d1), q2[f], eno_slope(d1, q3[f] - q2[f]));
+            q0[f] = q1[f];
+            q1[f] = q2[f];
+            q2[f] = q3[f];
         }
     }
-    A.rho_out[a] = A.rho[a] - g.dt * div[0];
-    for (int d = 0; d < 3; ++d) A.mom_out[(int64_t)d * A.N + a] = q[1 + d][a] - g.dt * div[1 + d];
-    A.e_out[a] = A.e[a] - g.dt * div[4];
+    load(q3, own, k0 + 2);
+    // one plane from v0 .. v3, planes k-1 .. k+2 of the own column; v0 then takes plane k+3, so that
+    // the ring turns by the names below and nothing is copied
+    auto plane = [&](int k, double* v0, double* v1, double* v2, double* v3) {
+        double(*p)[PY * PX] = tile[k & 1];
+#pragma unroll
+        for (int f = 0; f < 5; ++f) {
+            p[f][at] = v1[f];
+            if (halo) p[f][hat] = hv[f];
+        }
+        __syncthreads();  // (the other slot's readers passed the previous plane's barrier)
+        load(hv, hcell, min(k + 1, k1 - 1));
+        // interface velocities; zero on an axis of one cell, whose fluxes then cancel to zero
+        const double uxl = step1(xl, p[1][at - 1], v1[1], p[0][at - 1], v1[0]);
+        const double uxh = step1(xh, v1[1], p[1][at + 1], v1[0], p[0][at + 1]);
+        const double uyl = step1(yl, p[2][at - PX], v1[2], p[0][at - PX], v1[0]);
+        const double uyh = step1(yh, v1[2], p[2][at + PX], v1[0], p[0][at + PX]);
+        const double uzh = step1(g.per[2] || k < nz - 1, v1[3], v2[3], v1[0], v2[0]);
+        const int64_t a = own + (int64_t)k * sxy, an = own + (int64_t)reach(g, 2, k + 3) * sxy;
+#pragma unroll
+        for (int f = 0; f < 5; ++f) {
+            const double* c = p[f] + at;
+            double div = axis_div(uxl, uxh, c[-2], c[-1], v1[f], c[1], c[2]) * ih[0];
+            div += axis_div(uyl, uyh, c[-2 * PX], c[-PX], v1[f], c[PX], c[2 * PX]) * ih[1];
+            const double d1 = v2[f] - v1[f];
+            const double fh = eno_flux(uzh, v1[f], eno_slope(v1[f] - v0[f], d1), v2[f], eno_slope(d1, v3[f] - v2[f]));
+            v0[f] = A.q[f][an];
+            div += (fh - fz[f]) * ih[2];
+            fz[f] = fh;
+            if (inside) A.out[f][a] = v1[f] - g.dt * div;
+        }
+    };
+    for (int k = k0; k < k1;) {
+        plane(k, q0, q1, q2, q3);
+        if (++k == k1) break;
+        plane(k, q1, q2, q3, q0);
+        if (++k == k1) break;
+        plane(k, q2, q3, q0, q1);
+        if (++k == k1) break;
+        plane(k, q3, q0, q1, q2);
+        ++k;
+    }
 }
 
 // ideal gas: P = (gamma - 1)(e - |rho u|^2 / (2 rho)), c_s^2 = gamma P / rho
@@ -376,9 +484,12 @@ int hydro_launch_advect(const int n[3], const int bc[3], const double h[3], doub
         g.h[d] = h[d];
     }
     g.dt = dt;
-    AdvArgs A{rho, mom, e, rho_out, mom_out, e_out, (int64_t)n[0] * n[1] * n[2]};
-    dim3 grid((unsigned)((n[0] + 63) / 64), (unsigned)((n[1] + 3) / 4), (unsigned)n[2]);
-    hipLaunchKernelGGL(k_advect, grid, dim3(256), 0, s, g, A);
+    const int64_t N = (int64_t)n[0] * n[1] * n[2];
+    AdvArgs A{{rho, mom, mom + N, mom + 2 * N, e}, {rho_out, mom_out, mom_out + N, mom_out + 2 * N, e_out}};
+    HTiles t{(n[0] + kAdvX - 1) / kAdvX, (n[1] + kAdvY - 1) / kAdvY, 1, 1};
+    t.kz = hydro_chunk(n[2], (int64_t)t.tx * t.ty, kAdvThreads);
+    t.tz = (n[2] + t.kz - 1) / t.kz;
+    hipLaunchKernelGGL(k_advect, dim3((unsigned)((int64_t)t.tx * t.ty * t.tz)), dim3(kAdvThreads), 0, s, g, t, A);
     return hipGetLastError() == hipSuccess ? HP_OK : HP_EHIP;
 }
 
@@ -402,13 +513,13 @@ int hydro_launch_rhs(const int n[3], const int bc[3], const double h[3], double 
     const HTiles t = htiles(n);
     const dim3 grid((unsigned)t.tx * t.ty * t.tz);
     if (f->temp_n && f->visc)
-        hipLaunchKernelGGL((k_pressure_rhs<true, true>), grid, dim3(256), 0, s, g, t, A);
+        hipLaunchKernelGGL((k_pressure_rhs<true, true>), grid, dim3(64 * kHRows), 0, s, g, t, A);
     else if (f->temp_n)
-        hipLaunchKernelGGL((k_pressure_rhs<true, false>), grid, dim3(256), 0, s, g, t, A);
+        hipLaunchKernelGGL((k_pressure_rhs<true, false>), grid, dim3(64 * kHRows), 0, s, g, t, A);
     else if (f->visc)
-        hipLaunchKernelGGL((k_pressure_rhs<false, true>), grid, dim3(256), 0, s, g, t, A);
+        hipLaunchKernelGGL((k_pressure_rhs<false, true>), grid, dim3(64 * kHRows), 0, s, g, t, A);
     else
-        hipLaunchKernelGGL((k_pressure_rhs<false, false>), grid, dim3(256), 0, s, g, t, A);
+        hipLaunchKernelGGL((k_pressure_rhs<false, false>), grid, dim3(64 * kHRows), 0, s, g, t, A);
     return hipGetLastError() == hipSuccess ? HP_OK : HP_EHIP;
 }
 
@@ -424,7 +535,7 @@ int hydro_launch_update(const int n[3], const int bc[3], const double h[3], doub
     UpdArgs A{f->p, f->rho_np1, f->mom_star, f->e_star, f->mom_out, f->uface_out, f->e_out,
               (int64_t)n[0] * n[1] * n[2]};
     const HTiles t = htiles(n);
-    hipLaunchKernelGGL(k_pressure_update, dim3((unsigned)t.tx * t.ty * t.tz), dim3(256), 0, s, g, t, A);
+    hipLaunchKernelGGL(k_pressure_update, dim3((unsigned)t.tx * t.ty * t.tz), dim3(64 * kHRows), 0, s, g, t, A);
     return hipGetLastError() == hipSuccess ? HP_OK : HP_EHIP;
 }
 
