@@ -18,6 +18,7 @@
 #include <initializer_list>
 #include <type_traits>
 
+#include "hp_device.h"
 #include "hp_internal.h"
 
 #include <hip/hip_ext.h>
@@ -37,43 +38,6 @@ __device__ __forceinline__ int flat_bid() {
     return blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z);
 }
 __device__ __forceinline__ int num_blocks() { return gridDim.x * gridDim.y * gridDim.z; }
-
-// Reciprocal: hardware estimate refined by two Newton steps (error within a couple of ulp).
-__device__ __forceinline__ double fast_rcp(double x) {
-    double r = __builtin_amdgcn_rcp(x);
-    double e = __builtin_fma(-x, r, 1.0);
-    r = __builtin_fma(r, e, r);
-    e = __builtin_fma(-x, r, 1.0);
-    return __builtin_fma(r, e, r);
-}
-__device__ __forceinline__ float fast_rcp(float x) { return __builtin_amdgcn_rcpf(x); }
-
-// kappa = 1/rho at the face between cells of face densities ra and rb. FR = 0 (the default): the
-// factor 2 / (ra + rb) of the face-velocity update (step (viii)); FR = 1: the mean of the two
-// cells' kappa, (1/ra + 1/rb) / 2.
-template <int FR, typename T>
-__device__ __forceinline__ T face_kappa(T ra, T rb) {
-    if constexpr (FR == 1) return T(0.5) * (fast_rcp(ra) + fast_rcp(rb));
-    return T(2) * fast_rcp(ra + rb);
-}
-
-// the face rule of a launch as the compile-time constant FRV of the statement it runs
-#define WITH_FACE_RULE(rule, ...)      \
-    do {                               \
-        if (rule) {                    \
-            constexpr int FRV = 1;     \
-            __VA_ARGS__;               \
-        } else {                       \
-            constexpr int FRV = 0;     \
-            __VA_ARGS__;               \
-        }                              \
-    } while (0)
-
-__device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
-}
 
 // Sum over the workgroup in a fixed order; result valid in thread 0. Every thread must call.
 __device__ double block_sum(double v) {
@@ -2050,42 +2014,6 @@ void launch_rbgs_zero(const Geo<T>& g, const T* rho, const T* m, const T* r, T* 
 // ------------------------------------------------------------------------------------------
 // transfers
 
-// Fine taps of coarse index I along one axis for R = P^T / 2 (P: weights 3/4 parent, 1/4 the
-// second-nearest coarse cell; mirrored at a Neumann end, wrapped on a periodic axis).
-// Fine taps of coarse index I along one axis for R = P^T / 2: always four (index, weight)
-// pairs; missing taps (Neumann ends, an uncoarsened axis) get weight 0 and an in-range index, so
-// the restriction is straight-line code with all its loads independent.
-__device__ __forceinline__ void restrict_taps(int I, int nf, int coarsened, int periodic, int* idx,
-                                              float* w) {
-    if (!coarsened) {
-#pragma unroll
-        for (int s = 0; s < 4; ++s) {
-            idx[s] = I;
-            w[s] = s == 0 ? 1.0f : 0.0f;
-        }
-        return;
-    }
-    const int nc = nf >> 1;
-#pragma unroll
-    for (int s = 0; s < 4; ++s) {
-        int i = 2 * I - 1 + s;
-        if (i < 0 || i >= nf) {
-            if (!periodic) {
-                idx[s] = 2 * I;
-                w[s] = 0.0f;
-                continue;
-            }
-            i = (i + nf) % nf;
-        }
-        int parent = i >> 1;
-        int other = (i & 1) ? parent + 1 : parent - 1;
-        if (other < 0 || other >= nc) other = periodic ? (other + nc) % nc : parent;
-        float p = (parent == I ? 0.75f : 0.0f) + (other == I ? 0.25f : 0.0f);
-        idx[s] = i;
-        w[s] = 0.5f * p;
-    }
-}
-
 template <typename T>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(1, 2))) void k_restrict(Transfer t, const T* __restrict__ fine,
                                                      T* __restrict__ coarse) {
@@ -2355,26 +2283,6 @@ void launch_restrict(const Transfer& t, const T* fine, T* coarse, hipStream_t s,
     }
     Shape3 sh = cells_shape(t.ncx, t.ncy, t.ncz);
     hipLaunchKernelGGL((k_restrict<T>), sh.grid, sh.block, 0, s, t, fine, coarse);
-}
-
-// Coarse taps of fine index i along one axis for P.
-// Always two (index, weight) pairs: on an axis that is not coarsened the second has weight 0 and
-// the first index again, so the prolongation is straight-line code with independent loads.
-__device__ __forceinline__ void prolong_taps(int i, int nc, int coarsened, int periodic, int* idx,
-                                             float* w) {
-    if (!coarsened) {
-        idx[0] = idx[1] = i;
-        w[0] = 1.0f;
-        w[1] = 0.0f;
-        return;
-    }
-    int parent = i >> 1;
-    int other = (i & 1) ? parent + 1 : parent - 1;
-    if (other < 0 || other >= nc) other = periodic ? (other + nc) % nc : parent;
-    idx[0] = parent;
-    w[0] = 0.75f;
-    idx[1] = other;
-    w[1] = 0.25f;
 }
 
 template <typename T>

@@ -7,6 +7,7 @@
 // squared residual norm per iteration to decide convergence.
 #include "hp.h"
 #include "hp_internal.h"
+#include "hp_small.h"
 
 #include <cmath>
 #include <cstdarg>
@@ -54,6 +55,7 @@ struct LevelData {
     float *rho32 = nullptr, *m32 = nullptr, *dinv32 = nullptr;
     double *r = nullptr, *z = nullptr, *t = nullptr;
     float *r32 = nullptr, *z32 = nullptr, *t32 = nullptr;
+    double* w = nullptr;  // weights of the high faces (levels that one launch takes, hp_small.hip)
     int split = 0;  // arrays of this level are in the red-black split layout
 };
 
@@ -106,6 +108,15 @@ struct hp_handle {
     hipStream_t side = nullptr;
     hipEvent_t ev_fork = nullptr, ev_join = nullptr;
     unsigned dir = 0;              // traversal direction of the last finest-level pass
+    // One-launch V-cycles and solves (hp_small.hip): the level from which a V-cycle runs in one launch
+    // (the number of levels if none), the launch's shape, its level tables, counters, exchange and
+    // the result of a solve (mapped host memory)
+    int small_from = 0;
+    SmallShape small{};
+    SmallTable* small_tab = nullptr;
+    SmallState* small_state = nullptr;
+    double* small_exchange = nullptr;
+    SmallResult *host_small = nullptr, *dev_small = nullptr;
     std::vector<void*> allocs;
     // options
     int mode = HP_MODE_FP64_MGPCG;
@@ -394,6 +405,8 @@ void relayout0(hp_handle* H, const T* src, T* dst, int to_split) {
 
 // ---- coefficients of every level ----
 
+void setup_small_levels(hp_handle* H);
+
 // rho_mass: the density of the mass term m = 1/(rho c2) (time level n); rho_face: the density of
 // the face coefficients (time level n+1); the one-density form passes the same array for both
 int load_coefficients(hp_handle* H, const double* rho_mass, const double* rho_face, const double* c2,
@@ -429,13 +442,14 @@ int load_coefficients(hp_handle* H, const double* rho_mass, const double* rho_fa
     // the coarsest inverse (it needs only the coarsest rho and m) overlaps the Jacobi diagonals
     // and the relayout to the split storage order
     CHK(start_coarse_inverse(H));
-    for (size_t l = 0; l < H->lv.size(); ++l) {
+    for (size_t l = 0; l < H->lv.size() && (int)l < H->small_from; ++l) {
         LevelData& L = H->lv[l];
         launch_jacobi_diag(geo<double>(H, L), geo<float>(H, L), l == 0 ? rho0 : L.rho, l == 0 ? m0 : L.m,
                            L.rho32, L.m32, L.dinv, L.dinv32, H->want_split && split_target(H, l), H->stream);
     }
     CHK(check_launch());
     const int rc = H->want_split ? set_layout(H, 1, true) : HP_OK;
+    setup_small_levels(H);
     CHK(join_coarse_inverse(H));
     HIPCHK(hipStreamSynchronize(H->stream));
     if (H->host_flag[0]) return fail(HP_EDOMAIN, "rho and c2 must be positive and finite in every cell");
@@ -464,6 +478,64 @@ template <typename T> const T* lvl_dinv(const LevelData& L);
 template <> const double* lvl_dinv<double>(const LevelData& L) { return L.dinv; }
 template <> const float* lvl_dinv<float>(const LevelData& L) { return L.dinv32; }
 
+SmallTable small_table(hp_handle* H) {
+    SmallTable A{};
+    const int last = (int)H->lv.size() - 1, base = H->small_from;
+    const int per[3] = {H->bc.x == HP_BC_PERIODIC, H->bc.y == HP_BC_PERIODIC, H->bc.z == HP_BC_PERIODIC};
+    int lds = 0;
+    for (int l = base; l <= last; ++l) {
+        LevelData& L = H->lv[l];
+        SmallLevel& D = A.lv[l - base];
+        D.g = geo<double>(H, L);
+        for (int d = 0; d < 3; ++d) {
+            D.coarsened[d] = l < last ? H->lv[l + 1].coarsened[d] : 0;
+            D.periodic[d] = per[d];
+        }
+        D.n = (int)L.N;
+        D.hx = (L.n[0] + 1) / 2;
+        D.items = D.hx * L.n[1] * L.n[2];
+        D.lds = lds;
+        if (l > base) lds += 3 * D.n;
+        D.inv_nx = 1.0f / (float)L.n[0];
+        D.inv_hx = 1.0f / (float)D.hx;
+        D.inv_ny = 1.0f / (float)L.n[1];
+        D.rho = L.rho;
+        D.m = L.m;
+        D.dinv = L.dinv;
+        D.dinv32 = L.dinv32;
+        const Geo<float> g32 = geo<float>(H, L);
+        D.c32[0] = g32.cx;
+        D.c32[1] = g32.cy;
+        D.c32[2] = g32.cz;
+        D.w = L.w;
+    }
+    A.levels = last - base + 1;
+    A.nc = H->nc;
+    A.ainv = H->ainv;
+    return A;
+}
+
+// The arguments of a one-launch V-cycle, r and z the vectors of level small_from.
+SmallArgs small_args(hp_handle* H, const double* r, double* z) {
+    SmallArgs A{};
+    A.table = H->small_tab;
+    A.nu_pre = H->nu_pre;
+    A.nu_post = H->nu_post;
+    A.r = r;
+    A.z = z;
+    A.exchange = H->small_exchange;
+    A.state = H->small_state;
+    A.scal = H->scal;
+    return A;
+}
+
+// Diagonals, face weights and table of the levels that one launch takes, as they stand now (arrays,
+// orders, face rule).
+void setup_small_levels(hp_handle* H) {
+    if (H->small_from + 1 >= (int)H->lv.size()) return;
+    launch_small_setup(small_table(H), H->face_rule, H->small_tab, H->stream);
+}
+
 // V-cycle z = M r on level l. With dot != nullptr (level 0 only) the final red half sweep also
 // reduces <r, z> under *dot; returns true if it did (else the caller reduces separately).
 template <typename T>
@@ -475,6 +547,12 @@ bool vcycle(hp_handle* H, int l, const T* r, T* z, const RedCtl* dot = nullptr, 
     if (l == (int)H->lv.size() - 1) {
         launch_coarse_solve<T>(H->ainv, H->nc, r, z, s);
         return false;
+    }
+    if constexpr (sizeof(T) == 8) {
+        if (l == H->small_from && !pre_done) {
+            launch_small(small_args(H, r, z), false, H->small, s);
+            return false;
+        }
     }
     Geo<T> g = geo<T>(H, L);
     const T* rho = lvl_rho<T>(L);
@@ -614,6 +692,35 @@ void next_direction64(hp_handle* H, double* x, bool pre_done = false) {
     time_end(H);
 }
 
+// Whether a CG solve of this handle runs as one launch.
+bool small_solve(const hp_handle* H) { return H->small.lds_cg > 0 && !H->timing; }
+
+// The FP64 MG-PCG solve of a grid small enough for one launch (caller's arrays, natural order).
+int solve_small(hp_handle* H, const double* b, double* x, double tol) {
+    hp_stats& st = H->stats;
+    SmallArgs A = small_args(H, nullptr, nullptr);
+    A.cg = {x, b, H->dev_small, tol, H->max_iter};
+    SmallResult& t = *H->host_small;
+    t.code = SMALL_LOST;  // unless the launch says otherwise
+    t.iterations = t.rounds = 0;
+    launch_small(A, true, H->small, H->stream);
+    CHK(check_launch());
+    HIPCHK(hipStreamSynchronize(H->stream));
+    st.iterations = t.iterations;
+    st.restarts = t.rounds;
+    st.rel_residual = t.bb > 0.0 ? std::sqrt(t.rr / t.bb) : 0.0;
+    switch (t.code) {
+        case SMALL_CONVERGED: st.converged = 1; return HP_OK;
+        case SMALL_INPUT: return fail(HP_ENAN, "rhs or initial guess contains non-finite values");
+        case SMALL_BREAKDOWN: return fail(HP_EBREAKDOWN, "CG breakdown: p^T A p <= 0");
+        case SMALL_NAN: return fail(HP_ENAN, "non-finite residual in iteration %d", t.iterations);
+        case SMALL_BUDGET:
+            return fail(HP_ENOCONV, "no convergence in %d iterations (relative residual %.3e)", t.iterations,
+                        st.rel_residual);
+        default: return fail(HP_EHIP, "a CG launch did not finish");
+    }
+}
+
 // FP64 PCG (Jacobi or MG preconditioner) from the current x; r holds b - A x and
 // host_scal[S_RR] its squared norm on entry.
 int pcg64(hp_handle* H, const double* b, double* x, double tol, double bnorm) {
@@ -699,6 +806,55 @@ void next_direction32(hp_handle* H, bool pre_done = false) {
     H->x32_unset = false;
     launch_apply<float>(geo_pass(H, geo<float>(H, F), 0), F.rho32, F.m32, H->p32, nullptr, H->q32, 1,
                         red(H, OP_ALPHA), s);
+}
+
+// Which levels and solves run as one launch (hp_small.hip), and their buffers. The levels that one
+// workgroup's LDS and registers hold do: an FP64 solve of 64 x 64 cells takes 320 us instead of 866 (29 us
+// an iteration, where its 25 launches took 79), of 16 x 16 x 16 cells 272 instead of 686; and one of 64^3, whose
+// V-cycles run in one launch from 16^3 cells down, 1357 instead of 1482. FP64 only: the mixed form keeps its
+// launches, and with them the rounding of its FP32 cycles. Above 512 coarsest cells (odd sizes stop the
+// coarsening early) the helpers' registers don't hold the inverse, and under larger levels the coarsest
+// solve's own launch is the faster (224 x 80 x 44 cells with 1540: 2290 us against 2220); a whole solve
+// still gains (63 x 1 x 62 with 1953: 384 us against 640).
+int setup_small(hp_handle* H) {
+    const int levels = (int)H->lv.size();
+    H->small_from = levels;
+    int64_t below = 0;  // LDS values of the levels under the first
+    for (int l = levels - 2; l >= 0 && levels - l <= kSmallLevels; --l) {
+        const LevelData& L = H->lv[l];
+        below += (l + 1 == levels - 1 ? 2 : 3) * H->lv[l + 1].N;
+        const int64_t items = (int64_t)((L.n[0] + 1) / 2) * L.n[1] * L.n[2];
+        if (items > kSmallItems || (2 * L.N + below) * (int64_t)sizeof(double) > kSmallLds) break;
+        const bool whole = l == 0 && (4 * L.N + below) * (int64_t)sizeof(double) <= kSmallLds;
+        if (H->nc > 512 && !whole) continue;
+        H->small_from = l;
+        H->small.per_thread = (int)((items + kSmallThreads - 1) / kSmallThreads);
+        H->small.lds_cycle = (int)(2 * L.N + below);
+        H->small.lds_cg = whole ? (int)(4 * L.N + below) : 0;
+    }
+    if (H->small_from == levels) return HP_OK;
+    // Helpers for the coarsest solve, two of its rows per wave. A solve of 12 iterations takes 158 us with
+    // them and 182 without at 96 coarsest cells, 180 and 268 at 192, 272 and 810 at 512; at 64 the inverse is
+    // 32 KB, which the owner alone streams in the time that passing the vectors on takes.
+    const int rows = 2 * kSmallThreads / 64;
+    H->small.groups = H->nc <= 64 ? 1 : 1 + std::min((H->nc + rows - 1) / rows, 64);
+    HIPCHK(prepare_small(H->small));
+    // the counters, the table, the exchange and the face weights, in one allocation
+    int64_t weights = 0;
+    for (int l = H->small_from; l < levels - 1; ++l) weights += 3 * H->lv[l].N;
+    const int64_t head = (sizeof(SmallState) + sizeof(SmallTable)) / sizeof(double);
+    double* at;
+    CHK(dalloc(H, &at, head + 2 * H->nc + weights));
+    H->small_state = (SmallState*)at;
+    H->small_tab = (SmallTable*)(H->small_state + 1);
+    H->small_exchange = at + head;
+    at += head + 2 * H->nc;
+    for (int l = H->small_from; l < levels - 1; ++l) {
+        H->lv[l].w = at;
+        at += 3 * H->lv[l].N;
+    }
+    HIPCHK(hipMemsetAsync(H->small_state, 0, sizeof(SmallState), H->stream));
+    return HP_OK;
 }
 
 // FP32 MG-PCG on A32 d = r32 (unit-norm r32), d = x32 starts at 0 (unset: its first update writes
@@ -1151,12 +1307,14 @@ int hp_setup_two_density(const hp_grid* grid, const double* rho_n, const double*
         (rc = dalloc(H, &H->flag, 2)))
         return bail(rc);
     if (hipHostMalloc((void**)&H->host_scal, S_COUNT * sizeof(double), hipHostMallocDefault) != hipSuccess ||
-        hipHostMalloc((void**)&H->host_part, (cap + 1) * sizeof(double),
+        hipHostMalloc((void**)&H->host_part, (cap + 1) * sizeof(double) + sizeof(SmallResult),
                       hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess ||
         hipHostMalloc((void**)&H->host_flag, 2 * sizeof(int), hipHostMallocDefault) != hipSuccess)
         return bail(fail(HP_ENOMEM, "pinned host allocation failed"));
     if (hipHostGetDevicePointer((void**)&H->dev_part, H->host_part, 0) != hipSuccess)
         return bail(fail(HP_EHIP, "hipHostGetDevicePointer failed"));
+    H->host_small = (SmallResult*)(H->host_part + cap + 1);
+    H->dev_small = (SmallResult*)(H->dev_part + cap + 1);
     if (hipEventCreate(&H->ev0) != hipSuccess || hipEventCreate(&H->ev1) != hipSuccess ||
         hipEventCreateWithFlags(&H->ev_scal, hipEventDisableTiming) != hipSuccess ||
         hipEventCreateWithFlags(&H->ev_fork, hipEventDisableTiming) != hipSuccess ||
@@ -1166,6 +1324,7 @@ int hp_setup_two_density(const hp_grid* grid, const double* rho_n, const double*
         return bail(fail(HP_EHIP, "hipStreamCreateWithFlags failed"));
     if (hipMemsetAsync(H->scal, 0, S_COUNT * sizeof(double), H->stream) != hipSuccess)
         return bail(fail(HP_EHIP, "hipMemsetAsync failed"));
+    if ((rc = setup_small(H))) return bail(rc);
     H->want_split = split_allowed(H) ? 1 : 0;
     if ((rc = load_coefficients(H, rho_n, rho_np1, c2, dt))) return bail(rc);
     H->stats.levels = (int)H->lv.size();
@@ -1244,13 +1403,19 @@ int hp_set_option(hp_handle* H, int key, double v) {
                                    L.dinv32, false, H->stream);
             CHK(check_launch());
             CHK(build_coarse_inverse(H));
-            return was_split ? set_layout(H, 1) : HP_OK;
+            if (was_split) CHK(set_layout(H, 1));
+            setup_small_levels(H);
+            return check_launch();
         }
         case HP_OPT_LAYOUT: {
             if (v != 0.0 && v != 1.0) return fail(HP_EINVAL, "layout must be 0 (natural) or 1 (split)");
             if (v == 1.0 && !split_allowed(H)) return fail(HP_EINVAL, "the grid does not allow the split layout");
             int rc = set_layout(H, (int)v);
-            if (rc == HP_OK) H->want_split = (int)v;
+            if (rc == HP_OK) {
+                H->want_split = (int)v;
+                setup_small_levels(H);  // in the new order
+                rc = check_launch();
+            }
             return rc;
         }
         default:
@@ -1320,6 +1485,16 @@ int hp_solve(hp_handle* H, const double* b, double* x, double tol) {
     H->spans.clear();
     H->tev_used = 0;
     HIPCHK(hipEventRecord(H->ev0, s));
+    if (H->mode == HP_MODE_FP64_MGPCG && small_solve(H)) {
+        const int rc = solve_small(H, b, x, tol);
+        HIPCHK(hipEventRecord(H->ev1, s));
+        HIPCHK(hipEventSynchronize(H->ev1));
+        float ms = 0.0f;
+        (void)hipEventElapsedTime(&ms, H->ev0, H->ev1);
+        st.time_ms = ms;
+        st.status = rc;
+        return rc;
+    }
     HIPCHK(hipMemsetAsync(H->flag, 0, sizeof(int), s));
     HIPCHK(hipMemsetAsync(H->scal, 0, S_COUNT * sizeof(double), s));
     // in the split layout the solve runs on split copies of b and x (made in the pass that checks
