@@ -100,19 +100,17 @@ struct ConvArgs {
     // stored activation is written here as well ([coarse voxel][16], grid sizes halved)
     bf16_t* pool_out;
     // backward-data with the ReLU mask of the layer before it (OUT_GRAD, OUT_CONCAT): that layer's
-    // stored activation, and the per-workgroup channel sums of the masked gradient before its
-    // rounding ([block][channels of mask], the bias gradient's partials)
+    // stored activation, and the masked gradient before its rounding (for the bias gradient's sums)
     const bf16_t* mask = nullptr;
-    float* csum = nullptr;
+    float* full = nullptr;
     float* skip = nullptr;  // OUT_CONCAT: gradient of the skip channels [voxel][cout - 16 CU], FP32
 };
 
 // What a convolution stores: the (ReLU'd) activation in bfloat16; plain FP32; the gradient at the
 // output of the layer before it, masked by that layer's ReLU, in bfloat16; or, for an input that is
 // [upsampled, skip], the gradient of the upsampled part summed over the 2x2x2 children and masked
-// like that at the coarse voxels, and the skip part in FP32. The masked forms write 2 bytes per
-// value where an FP32 gradient, its split and a masking pass moved 22: at 128^3 these passes took
-// 1.3 ms of a training step, what is left of them beside the convolutions 0.2 ms.
+// like that at the coarse voxels, and the skip part in FP32. The masked forms write 6 bytes per
+// value (2, and 4 for the bias sums) where an FP32 gradient, its split and a masking pass moved 22.
 enum { OUT_ACT = 0, OUT_F32 = 1, OUT_GRAD = 2, OUT_CONCAT = 3 };
 
 // SPW z-slices per wave: the output brick is 16 x 4 x (4 SPW) voxels.
@@ -307,17 +305,13 @@ __global__ __launch_bounds__(256) void k_conv_fwd(ConvArgs p) {
     const bool full = x0 + BX <= p.nx && y0 + BY <= p.ny && z0 + FZ <= p.nz;
     const int gx = x0 + li;
     constexpr int CU = OUT == OUT_CONCAT ? 2 * CT / 3 : 0;   // output tiles of the upsampled part
-    constexpr int CM = OUT == OUT_CONCAT ? CU : CT;          // output tiles that are masked
-    f32x4 cs[OUT >= OUT_GRAD ? CM : 1];                      // channel sums of the masked gradient
-#pragma unroll
-    for (int ct = 0; ct < (OUT >= OUT_GRAD ? CM : 1); ++ct) cs[ct] = f32x4{0.f, 0.f, 0.f, 0.f};
-    // v masked by the activation at `at` (4 channels), stored as bfloat16, added to the channel sums
-    auto mask_store = [&](f32x4 v, int64_t at, f32x4& sum) {
+    // v masked by the activation at `at` (4 channels), stored as bfloat16 and in full
+    auto mask_store = [&](f32x4 v, int64_t at) {
         const uint2 a = *(const uint2*)(p.mask + at);
         const unsigned on[4] = {a.x << 16, a.x & 0xffff0000u, a.y << 16, a.y & 0xffff0000u};
 #pragma unroll
         for (int e = 0; e < 4; ++e) v[e] = __uint_as_float(on[e]) > 0.f ? v[e] : 0.f;
-        sum += v;
+        *(f32x4*)(p.full + at) = v;
         *(uint2*)((bf16_t*)p.out + at) = uint2{pack_bf2(v[0], v[1]), pack_bf2(v[2], v[3])};
     };
     if constexpr (OUT == OUT_CONCAT) {
@@ -352,7 +346,7 @@ __global__ __launch_bounds__(256) void k_conv_fwd(ConvArgs p) {
                     for (int y = 0; y < 2; ++y)
 #pragma unroll
                         for (int x = 0; x < 2; ++x) s += odd[((2 * yp + y) * CU + ct) * 64 + (lane ^ x)];
-                    if (in) mask_store(s, vox * (16 * CU) + ct * 16 + 4 * grp, cs[ct]);
+                    if (in) mask_store(s, vox * (16 * CU) + ct * 16 + 4 * grp);
                 }
             }
         }
@@ -374,7 +368,7 @@ __global__ __launch_bounds__(256) void k_conv_fwd(ConvArgs p) {
                 continue;
             }
             if constexpr (OUT == OUT_GRAD) {
-                mask_store(acc[sr][ct], vox * p.cout + o, cs[ct]);
+                mask_store(acc[sr][ct], vox * p.cout + o);
                 continue;
             }
             float v[4];
@@ -438,38 +432,26 @@ __global__ __launch_bounds__(256) void k_conv_fwd(ConvArgs p) {
             }
         }
     }
-    if constexpr (OUT >= OUT_GRAD) {
-        // channel sums of the workgroup: over the 16 lanes of a row, then over the waves
-        __syncthreads();
-        float* part = (float*)lds;
-#pragma unroll
-        for (int ct = 0; ct < CM; ++ct)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                float v = cs[ct][e];
-                v += __shfl_xor(v, 1, 64);
-                v += __shfl_xor(v, 2, 64);
-                v += __shfl_xor(v, 4, 64);
-                v += __shfl_xor(v, 8, 64);
-                if (li == 0) part[wave * (16 * CM) + ct * 16 + 4 * grp + e] = v;
-            }
-        __syncthreads();
-        if (tid < 16 * CM)
-            p.csum[(int64_t)bid * (16 * CM) + tid] =
-                (part[tid] + part[16 * CM + tid]) + (part[32 * CM + tid] + part[48 * CM + tid]);
-    }
 }
 
 // ------------------------------------------------------------------------------------------
-// backward weights: dW[o][t][c] = sum_v g[v][o] x[v + d_t][c], a contraction over voxels. A
-// workgroup owns 16 output and 16 input channels and a range of 16 x 4 x 8 bricks, all 27 taps.
-// Both operands go to LDS as they lie in memory ([voxel][16 channels], 16-byte stores), and the
-// LDS transposed read (ds_read_b64_tr_b16) hands each lane four voxels of one channel: a K step
-// of 32 pairs the 16 x positions of two rows neighbouring in z. Wave w owns the z pair 2w, 2w + 1
-// of the brick; it walks its input rows, and each B fragment read feeds every output row it
-// reaches (up to three in y), so 54 fragment reads serve 108 products. Bound by LDS reads and
-// by staging the halo brick (2.1 voxels per output voxel). Measured at 128^3: 44 us for a 16 -> 16
-// layer, 115 us for 48 -> 16; with 2-byte transposes written to LDS by 96 workgroups it was 870 us.
+// backward weights: dW[o][t][c] = sum_v g[v][o] x[v + d_t][c], a contraction over voxels, in kBwdWParts
+// partial sums over every kBwdWParts-th brick of 16 x 4 x 4 voxels. The order of every sum is fixed: brick by
+// brick, its rows in y pairs, one matrix product of 32 voxels for each (lane group g of the product: voxels
+// 8 g .. 8 g + 7 of the pair). Training keeps its weights for long, and they must not move with the launch
+// shape: a gradient that differs in its last bit flips a bfloat16 rounding now and then, and a step
+// later the gradients are 1e-4 apart.
+//
+// A workgroup owns 16 output and 16 input channels of one partial sum. Its first three waves multiply: wave w the nine
+// taps of x offset w, walking the input's row pairs, each B fragment read once for every product it has a
+// part in (30 fragments for 72 products). The other kLoaders threads bring the bricks: loads two bricks
+// ahead in registers, into one of two LDS bricks as they lie in memory ([voxel][16 channels], 16-byte
+// stores) while the other is multiplied, one barrier per brick; the LDS transposed read
+// (ds_read_b64_tr_b16) hands each lane four voxels of one channel. A workgroup has up to 1 / 96 of the bricks one
+// after the other, so a brick's time counts: 1.4 us at 128^3, bound by the loaders (120 us for a 16 -> 16 layer,
+// 176 for 48 -> 16); 1.7 with the same waves loading and multiplying in turn, and 10 (870 us for the layer)
+// with 2-byte transposes written to LDS. More partial sums would give shorter chains (512 of them: 44 us), but
+// other sums.
 
 struct BwdWArgs {
     const bf16_t* g;  // [voxel][cout] gradient at the convolution output (after the ReLU mask)
@@ -482,129 +464,195 @@ struct BwdWArgs {
     int nx, ny, nz;
 };
 
-constexpr int WZ = 8, WHZ = WZ + 2;      // z extent of a brick, with halo
-constexpr int WHV = HX * HY * WHZ;       // 1080 halo voxels
-constexpr int WV = BX * BY * WZ;         // 512 voxels
-constexpr int kBwdWGroups = 512;         // workgroups of one launch: two per CU (registers)
+constexpr int kBwdWParts = 96;
+constexpr int kMultipliers = 192, kLoaders = 320;  // threads
 
 typedef short i16x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) i16x4 lds_i16x4;
 
-// MFMA fragment (lane li: channel li; K = the lane group's four x positions of the row at p, then
-// of the row `next` 8-byte words further) from [voxel][16 channels] in LDS
-__device__ __forceinline__ bf16x8 frag_tr(const uint2* p, int next) {
+// MFMA fragment (lane li: channel li; K = eight x positions from the lane's word p on) from
+// [voxel][16 channels] in LDS
+__device__ __forceinline__ bf16x8 frag_tr(const uint2* p) {
     const i16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)p);
-    const i16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(p + next));
+    const i16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(p + 16));
     typedef short i16x8 __attribute__((ext_vector_type(8)));
     return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
 }
 
-// (two waves per SIMD: with three, the 108 accumulators and the staged loads spill, 127 us for 52)
-__global__ __launch_bounds__(256, 2) void k_conv_bwd_w(BwdWArgs p) {
-    __shared__ uint4 lds[2 * WHV + 2 * WV];  // halo brick, then the gradient brick
-    uint4* const xs = lds;
-    uint4* const gs = lds + 2 * WHV;
+__global__ __launch_bounds__(kMultipliers + kLoaders, 1) void k_conv_bwd_w(BwdWArgs p) {
+    constexpr int XW = 2 * HV, GW = 2 * BX * BY * BZ;  // 16-byte words of the halo brick and of g's
+    constexpr int NX = (XW + kLoaders - 1) / kLoaders, NG = (GW + kLoaders - 1) / kLoaders;
+    // (every loader stores all its words: what is past the brick goes to the padding)
+    constexpr int XP = NX * kLoaders, GP = NG * kLoaders;
+    __shared__ uint4 lds[2][XP + GP];
     const int cin = p.ca + p.cb;
     const int c0 = blockIdx.y * 16, o0 = blockIdx.z * 16;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = (int)threadIdx.x - kMultipliers, lane = threadIdx.x & 63, dx = threadIdx.x >> 6;
     const int li = lane & 15, grp = lane >> 4;
-    const int bxn = (p.nx + BX - 1) / BX, byn = (p.ny + BY - 1) / BY, bzn = (p.nz + WZ - 1) / WZ;
+    const int bxn = (p.nx + BX - 1) / BX, byn = (p.ny + BY - 1) / BY, bzn = (p.nz + BZ - 1) / BZ;
     const int nbricks = bxn * byn * bzn;
-    const int anx = p.a_up ? p.nx >> 1 : p.nx, any = p.a_up ? p.ny >> 1 : p.ny;
     const bool from_a = c0 < p.ca;
-    f32x4 acc[27];
+    // Byte offsets of this thread's words from the first voxel of a brick's halo (of an
+    // inner brick; an upsampled input's voxels have half the coordinates) and of the brick.
+    const int xc = from_a ? p.ca : p.cb, xs = from_a && p.a_up ? 1 : 0, xnx = p.nx >> xs, xny = p.ny >> xs;
+    const char* const xbase = (const char*)(from_a ? p.a + c0 : p.b + (c0 - p.ca));
+    const char* const gbase = (const char*)(p.g + o0);
+    // which half of its voxel's channels a thread takes is fixed; the first layer has no second half
+    const int half = (tid & 1) * 8;
+    const bool there = c0 + half < cin;
+    int64_t xoff[NX], goff[NG];
+    unsigned hpos[NX], gpos[NG];  // and the coordinates, 8 bits each
 #pragma unroll
-    for (int q = 0; q < 27; ++q) acc[q] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int i = 0; i < NX; ++i) {
+        const int hv = min(tid + kLoaders * i, XW - 1) >> 1, hx = hv % HX, hy = (hv / HX) % HY, hz = hv / (HX * HY);
+        // (an inner brick starts at even coordinates: its halo's first voxel is at -1, of which the half is -1)
+        const int x = xs ? (hx + 1) >> 1 : hx, y = xs ? (hy + 1) >> 1 : hy, z = xs ? (hz + 1) >> 1 : hz;
+        xoff[i] = (int64_t)((z * xny + y) * xnx + x) * (xc * 2) + (there ? half * 2 : 0);
+        hpos[i] = hx | hy << 8 | hz << 16;
+    }
+#pragma unroll
+    for (int i = 0; i < NG; ++i) {
+        const int v = min(tid + kLoaders * i, GW - 1) >> 1, vx = v % BX, vy = (v / BX) % BY, vz = v / (BX * BY);
+        goff[i] = (int64_t)((vz * p.ny + vy) * p.nx + vx) * (p.cout * 2) + half * 2;
+        gpos[i] = vx | vy << 8 | vz << 16;
+    }
 
-    // consecutive workgroups take consecutive bricks in turn, so that those running together
-    // share halo lines in the caches
-    for (int br = blockIdx.x; br < nbricks; br += gridDim.x) {
-        const int x0 = (br % bxn) * BX, y0 = ((br / bxn) % byn) * BY, z0 = (br / (bxn * byn)) * WZ;
-        constexpr int NX = (2 * WHV + 255) / 256, NG = 2 * WV / 256;
-        uint4 xv[NX], gv[NG];
+    struct Stage {
+        uint4 x[NX], g[NG];
+        unsigned in;  // which of them lie inside, one bit each
+    };
+    constexpr unsigned kAll = (1u << (NX + NG)) - 1;
+    // Where this workgroup's next 64 bricks lie, one to a lane (the divisions and products of one brick alone
+    // would take longer than its matrix products): its coordinates, the voxels that the offsets count
+    // from (-1 where the brick isn't an inner one).
+    const int step = gridDim.x;
+    int bx, by, bz, xat, gat;
+    auto plan = [&](int k) {
+        const int b = min((int)blockIdx.x + (k + lane) * step, nbricks - 1), row = b / bxn;
+        bx = (b - row * bxn) * BX;
+        bz = row / byn * BZ;
+        by = (row - row / byn * byn) * BY;
+        const bool inner = bx > 0 && bx + BX < p.nx && by > 0 && by + BY < p.ny && bz > 0 && bz + BZ < p.nz;
+        xat = inner ? (((bz - 1) >> xs) * xny + ((by - 1) >> xs)) * xnx + ((bx - 1) >> xs) : -1;
+        gat = (bz * p.ny + by) * p.nx + bx;
+    };
+    // (the loads are the same instructions for every brick, and for none past the last: only then can the
+    // wait for one stage's leave the next one's in flight)
+    auto fetch = [&](int k, Stage& st) {
+        if ((k & 63) == 0) plan(k);
+        int xv = __builtin_amdgcn_readlane(xat, k & 63), gv = __builtin_amdgcn_readlane(gat, k & 63);
+        int64_t xo[NX], go[NG];
+        unsigned in = kAll;
+        if (xv >= 0) {
 #pragma unroll
-        for (int i = 0; i < NX; ++i) {
-            const int u = tid + 256 * i;
-            const int hv = u >> 1, ch = c0 + (u & 1) * 8;
-            const int hx = hv % HX, hy = (hv / HX) % HY, hz = hv / (HX * HY);
-            int gx = x0 + hx - 1, gy = y0 + hy - 1;
-            const int gz = z0 + hz - 1;
-            gx = gx < 0 ? gx + p.nx : (gx >= p.nx ? gx - p.nx : gx);
-            gy = gy < 0 ? gy + p.ny : (gy >= p.ny ? gy - p.ny : gy);
-            // past the periodic image (a brick wider than the grid): zero, as its gradient is
-            const bool in = u < 2 * WHV && gz >= 0 && gz < p.nz && gx >= 0 && gx < p.nx && gy >= 0 && gy < p.ny &&
-                            ch < cin;
-            const bf16_t* src = p.a;
-            if (in) {
-                if (!from_a)
-                    src = p.b + (((int64_t)gz * p.ny + gy) * p.nx + gx) * p.cb + (ch - p.ca);
-                else if (p.a_up)
-                    src = p.a + (((int64_t)(gz >> 1) * any + (gy >> 1)) * anx + (gx >> 1)) * p.ca + ch;
-                else
-                    src = p.a + (((int64_t)gz * p.ny + gy) * p.nx + gx) * p.ca + ch;
+            for (int i = 0; i < NX; ++i) xo[i] = xoff[i];
+#pragma unroll
+            for (int i = 0; i < NG; ++i) go[i] = goff[i];
+        } else {
+            const int x0 = __builtin_amdgcn_readlane(bx, k & 63), y0 = __builtin_amdgcn_readlane(by, k & 63),
+                      z0 = __builtin_amdgcn_readlane(bz, k & 63);
+            xv = gv = 0;
+            in = 0u;
+#pragma unroll
+            for (int i = 0; i < NX; ++i) {
+                int gx = x0 + (int)(hpos[i] & 255u) - 1, gy = y0 + (int)(hpos[i] >> 8 & 255u) - 1;
+                const int gz = z0 + (int)(hpos[i] >> 16) - 1;
+                gx = gx < 0 ? gx + p.nx : (gx >= p.nx ? gx - p.nx : gx);
+                gy = gy < 0 ? gy + p.ny : (gy >= p.ny ? gy - p.ny : gy);
+                // past the periodic image (a brick wider than the grid): zero, as its gradient is
+                const bool ok = (gz >= 0) & (gz < p.nz) & (gx >= 0) & (gx < p.nx) & (gy >= 0) & (gy < p.ny);
+                in |= ok ? 1u << i : 0u;
+                const int v = ok ? ((gz >> xs) * xny + (gy >> xs)) * xnx + (gx >> xs) : 0;
+                xo[i] = (int64_t)v * (xc * 2) + (there ? half * 2 : 0);
             }
-            const uint4 t = *(const uint4*)src;  // outside: a harmless load of voxel 0
-            xv[i] = in ? t : uint4{0u, 0u, 0u, 0u};
+#pragma unroll
+            for (int i = 0; i < NG; ++i) {
+                const int gx = x0 + (int)(gpos[i] & 255u), gy = y0 + (int)(gpos[i] >> 8 & 255u), gz = z0 + (int)(gpos[i] >> 16);
+                const bool ok = (gx < p.nx) & (gy < p.ny) & (gz < p.nz);
+                in |= ok ? 1u << (NX + i) : 0u;
+                go[i] = (int64_t)(ok ? (gz * p.ny + gy) * p.nx + gx : 0) * (p.cout * 2) + half * 2;
+            }
         }
+        if (!there) in &= ~((1u << NX) - 1);
+        st.in = (int)blockIdx.x + k * step < nbricks ? in : 0u;
+        const char* const xfrom = xbase + (int64_t)xv * (xc * 2);
+        const char* const gfrom = gbase + (int64_t)gv * (p.cout * 2);
 #pragma unroll
-        for (int i = 0; i < NG; ++i) {
-            const int u = tid + 256 * i;
-            const int v = u >> 1;
-            const int gx = x0 + (v % BX), gy = y0 + (v / BX) % BY, gz = z0 + v / (BX * BY);
-            const bool in = gx < p.nx && gy < p.ny && gz < p.nz;
-            const int64_t vox = in ? ((int64_t)gz * p.ny + gy) * p.nx + gx : 0;
-            const uint4 t = *(const uint4*)(p.g + vox * p.cout + o0 + (u & 1) * 8);
-            gv[i] = in ? t : uint4{0u, 0u, 0u, 0u};
-        }
-        __syncthreads();  // the previous brick's reads of lds are done
+        for (int i = 0; i < NX; ++i) st.x[i] = *(const uint4*)(xfrom + xo[i]);
 #pragma unroll
-        for (int i = 0; i < NX; ++i)
-            if ((i + 1) * 256 <= 2 * WHV || tid + 256 * i < 2 * WHV) xs[tid + 256 * i] = xv[i];
+        for (int i = 0; i < NG; ++i) st.g[i] = *(const uint4*)(gfrom + go[i]);
+    };
+    auto store = [&](const Stage& st, uint4* to) {
+        auto put = [&](int at, const uint4& v, int bit) {
+            const unsigned m = 0u - (st.in >> bit & 1u);
+            to[at] = uint4{v.x & m, v.y & m, v.z & m, v.w & m};
+        };
 #pragma unroll
-        for (int i = 0; i < NG; ++i) gs[tid + 256 * i] = gv[i];
+        for (int i = 0; i < NX; ++i) put(tid + kLoaders * i, st.x[i], i);
+#pragma unroll
+        for (int i = 0; i < NG; ++i) put(XP + tid + kLoaders * i, st.g[i], NX + i);
+    };
+    // consecutive workgroups take consecutive bricks in turn, so that those running together
+    // share halo lines in the caches; two a turn, a brick of zeros past an odd last one
+    const int mine = (nbricks - (int)blockIdx.x + step - 1) / step;
+    if (tid >= 0) {
+        Stage st[2];
+        fetch(0, st[0]);
+        fetch(1, st[1]);
+        store(st[0], lds[0]);
+        fetch(2, st[0]);
         __syncthreads();
-        // this lane's word of the transposed reads: voxel 4 grp + li / 4 of a row, channels 4 (li % 4) ...
-        const int at = (4 * grp + (li >> 2)) * 4 + (li & 3);
-        const uint2* gw = (const uint2*)gs + (2 * wave) * (BY * BX * 4) + at;
-        const uint2* xw = (const uint2*)xs + (2 * wave) * (HY * HX * 4) + at;
-        bf16x8 af[BY];
+        for (int k = 0; k < mine; k += 2)
 #pragma unroll
-        for (int r = 0; r < BY; ++r) af[r] = frag_tr(gw + r * BX * 4, BY * BX * 4);
+            for (int q = 0; q < 2; ++q) {
+                store(st[1 - q], lds[1 - q]);
+                fetch(k + q + 3, st[1 - q]);
+                __syncthreads();
+            }
+        return;
+    }
+
+    f32x4 acc[9];
 #pragma unroll
-        for (int dz = 0; dz < 3; ++dz)
+    for (int q = 0; q < 9; ++q) acc[q] = f32x4{0.f, 0.f, 0.f, 0.f};
+    // this lane's word of the transposed reads: of the row pair's row grp / 2, the voxel 8 (grp % 2) + li / 4,
+    // channels 4 (li % 4) ...
+    const int at = (8 * (grp & 1) + (li >> 2)) * 4 + (li & 3);
+    auto multiply = [&](const uint4* from) {
+        const uint2* gw = (const uint2*)(from + XP) + (grp >> 1) * (BX * 4) + at;
+        const uint2* xw = (const uint2*)from + (grp >> 1) * (HX * 4) + dx * 4 + at;
+        bf16x8 af[2 * BZ];
 #pragma unroll
-            for (int iy = 0; iy < HY; ++iy)
+        for (int q = 0; q < 2 * BZ; ++q) af[q] = frag_tr(gw + q * 2 * BX * 4);
 #pragma unroll
-                for (int dx = 0; dx < 3; ++dx) {
-                    const bf16x8 bf = frag_tr(xw + ((dz * HY + iy) * HX + dx) * 4, HY * HX * 4);
+        for (int iz = 0; iz < HZ; ++iz)
+#pragma unroll
+            for (int iy = 0; iy < HY - 1; ++iy) {
+                const bf16x8 bf = frag_tr(xw + (iz * HY + iy) * HX * 4);
+#pragma unroll
+                for (int dz = 0; dz < 3; ++dz)
 #pragma unroll
                     for (int dy = 0; dy < 3; ++dy) {
-                        const int r = iy - dy;
-                        if (r < 0 || r >= BY) continue;
-                        const int t = (dz * 3 + dy) * 3 + dx;
-                        acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[r], bf, acc[t], 0, 0, 0);
+                        const int z = iz - dz, y = iy - dy;
+                        if (z < 0 || z >= BZ || (y != 0 && y != 2)) continue;
+                        acc[dz * 3 + dy] =
+                            __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[2 * z + y / 2], bf, acc[dz * 3 + dy], 0, 0, 0);
                     }
-                }
+            }
+    };
+    __syncthreads();
+    for (int k = 0; k < mine; k += 2) {
+        multiply(lds[0]);
+        __syncthreads();
+        multiply(lds[1]);
+        __syncthreads();
     }
-    // The lane holds D[o = 4 grp + e][c = li] of every tap for its wave's rows: the four waves are
-    // summed in order through LDS, nine taps at a time.
+    // the lane holds D[o = 4 grp + e][c = li] of its taps
     float* out = p.partial + (((int64_t)blockIdx.x * gridDim.y + blockIdx.y) * p.cout + o0) * (27 * 16);
-    float* sum = (float*)lds;
 #pragma unroll
-    for (int part = 0; part < 3; ++part) {
-        __syncthreads();
+    for (int q = 0; q < 9; ++q)
 #pragma unroll
-        for (int q = 0; q < 9; ++q)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) sum[(wave * 9 + q) * 256 + (4 * grp + e) * 16 + li] = acc[part * 9 + q][e];
-        __syncthreads();
-#pragma unroll
-        for (int q = 0; q < 9; ++q) {
-            const float* v = sum + q * 256 + tid;
-            out[((int64_t)(tid >> 4) * 27 + part * 9 + q) * 16 + (tid & 15)] =
-                ((v[0] + v[9 * 256]) + v[18 * 256]) + v[27 * 256];
-        }
-    }
+        for (int e = 0; e < 4; ++e) out[((int64_t)(4 * grp + e) * 27 + 3 * q + dx) * 16 + li] = acc[q][e];
 }
 
 // sum the per-workgroup partials in a fixed order into the flat gradient W[o][t][c] (c < creal):
@@ -727,59 +775,96 @@ __global__ void k_pool(const bf16_t* __restrict__ in, bf16_t* __restrict__ out, 
     *(uint4*)(out + v * c + 8 * g) = r;
 }
 
-// Gradient at a skip connection's activation, g[v][c] + gpool[v/2][c] / 8 (the 2x2x2 pooling's
-// gradient), masked by the activation and rounded to bfloat16 (the operand of the backward
-// convolutions), with the workgroup's channel sums of the masked value in partial[block][c].
-// A thread takes 8 channels of a voxel, kReluVox voxels per workgroup; bound by its memory traffic
-// (57 us at 128^3 x 16, 4.9 TB/s).
-constexpr int kReluVox = 1024;  // voxels per workgroup
+// Channel sums (bias and head gradients). Like the weights' sums theirs keep one order whatever the launch: FP32
+// sums over groups of 64 consecutive voxels, voxel j of every 256 / C together first, then j = 0, 1, ..; FP64
+// over the groups. A wave takes a group, lane (j, q) channels 4 q .. 4 q + 3.
+constexpr int kSumVox = 4 * 64;  // voxels per workgroup
 
+// the group's sums of channel `lane` from the lanes' own sums; `ws`: 64 values of LDS for this wave
+template <int C>
+__device__ __forceinline__ float group_sum(float4 own, float4* ws) {
+    const int lane = threadIdx.x & 63;
+    ws[lane] = own;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    float s = 0.f;
+    if (lane < C)
+#pragma unroll
+        for (int j = 0; j < 256 / C; ++j) s += ((const float*)ws)[j * C + lane];
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    return s;
+}
+
+// the workgroup's sums: partial[block][C] from each wave's sum of channel `lane`
+template <int C>
+__device__ __forceinline__ void block_sums(double total, double* __restrict__ partial) {
+    __shared__ double sums[4][64];
+    sums[threadIdx.x >> 6][threadIdx.x & 63] = total;
+    __syncthreads();
+    if (threadIdx.x < C)
+        partial[(int64_t)blockIdx.x * C + threadIdx.x] =
+            (sums[0][threadIdx.x] + sums[1][threadIdx.x]) + (sums[2][threadIdx.x] + sums[3][threadIdx.x]);
+}
+
+// Channel sums of g[v][C].
+template <int C>
+__global__ __launch_bounds__(256) void k_channel_sums(const float* __restrict__ g, int64_t nv, double* __restrict__ partial) {
+    __shared__ float4 ws[4][64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int64_t v0 = (int64_t)blockIdx.x * kSumVox + wave * 64 + lane / (C / 4);
+    float4 own = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int i = 0; i < C / 4; ++i) {
+        const int64_t v = v0 + i * (256 / C);
+        if (v < nv) {
+            const float4 t = *(const float4*)(g + v * C + 4 * (lane % (C / 4)));
+            own.x += t.x;
+            own.y += t.y;
+            own.z += t.z;
+            own.w += t.w;
+        }
+    }
+    block_sums<C>(group_sum<C>(own, ws[wave]), partial);
+}
+
+// Gradient at a skip connection's activation, g[v][C] + gpool[v/2][C] / 8 (the 2x2x2 pooling's
+// gradient), masked by the activation and rounded to bfloat16 (the operand of the backward
+// convolutions), with the channel sums of the masked value. Bound by its memory traffic (53 us at
+// 128^3 x 16, 5.3 TB/s).
+template <int C>
 __global__ __launch_bounds__(256) void k_relu_bwd_pool(const float* __restrict__ g, const float* __restrict__ gpool,
                                                        const bf16_t* __restrict__ act, bf16_t* __restrict__ gp, int nx,
-                                                       int ny, int64_t nv, int c, float* __restrict__ partial) {
-    __shared__ float sums[256][9];
-    const int tid = threadIdx.x, cg = c >> 3;
-    const int ch = (tid % cg) * 8, step = 256 / cg;
+                                                       int ny, int64_t nv, double* __restrict__ partial) {
+    __shared__ float4 ws[4][64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, ch = 4 * (lane % (C / 4));
     const int cx = nx >> 1, cy = ny >> 1;
-    float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    const int64_t v0 = (int64_t)blockIdx.x * kReluVox, v1 = min(v0 + kReluVox, nv);
-    for (int64_t v = v0 + tid / cg; v < v1; v += step) {
-        const int x = (int)(v % nx);
-        const int64_t row = v / nx;
-        const int y = (int)(row % ny);
-        const int64_t z = row / ny;
-        const int64_t cv = ((z >> 1) * cy + (y >> 1)) * cx + (x >> 1);
-        const float4* gv = (const float4*)(g + v * c + ch);
-        const float4* pv = (const float4*)(gpool + cv * c + ch);
-        const float4 a = gv[0], b = gv[1], pa = pv[0], pb = pv[1];
-        const uint4 w = *(const uint4*)(act + v * c + ch);
-        const float val[8] = {a.x + pa.x * 0.125f, a.y + pa.y * 0.125f, a.z + pa.z * 0.125f, a.w + pa.w * 0.125f,
-                              b.x + pb.x * 0.125f, b.y + pb.y * 0.125f, b.z + pb.z * 0.125f, b.w + pb.w * 0.125f};
-        const unsigned u[4] = {w.x, w.y, w.z, w.w};
-        unsigned r[4];
+    const int64_t v0 = (int64_t)blockIdx.x * kSumVox + wave * 64 + lane / (C / 4);
+    float4 own = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const float lo = __uint_as_float(u[e] << 16) > 0.f ? val[2 * e] : 0.f;
-            const float hi = __uint_as_float(u[e] & 0xffff0000u) > 0.f ? val[2 * e + 1] : 0.f;
-            acc[2 * e] += lo;
-            acc[2 * e + 1] += hi;
-            r[e] = pack_bf2(lo, hi);
+    for (int i = 0; i < C / 4; ++i) {
+        const int64_t v = v0 + i * (256 / C);
+        if (v < nv) {
+            // (fewer than 2^31 voxels)
+            const int x = (int)v % nx, row = (int)v / nx, y = row % ny, z = row / ny;
+            const int64_t cv = ((int64_t)(z >> 1) * cy + (y >> 1)) * cx + (x >> 1);
+            const float4 a = *(const float4*)(g + v * C + ch), b = *(const float4*)(gpool + cv * C + ch);
+            const uint2 w = *(const uint2*)(act + v * C + ch);
+            const float4 t = {__uint_as_float(w.x << 16) > 0.f ? a.x + b.x * 0.125f : 0.f,
+                              __uint_as_float(w.x & 0xffff0000u) > 0.f ? a.y + b.y * 0.125f : 0.f,
+                              __uint_as_float(w.y << 16) > 0.f ? a.z + b.z * 0.125f : 0.f,
+                              __uint_as_float(w.y & 0xffff0000u) > 0.f ? a.w + b.w * 0.125f : 0.f};
+            own.x += t.x;
+            own.y += t.y;
+            own.z += t.z;
+            own.w += t.w;
+            *(uint2*)(gp + v * C + ch) = uint2{pack_bf2(t.x, t.y), pack_bf2(t.z, t.w)};
         }
-        *(uint4*)(gp + v * c + ch) = uint4{r[0], r[1], r[2], r[3]};
     }
-#pragma unroll
-    for (int e = 0; e < 8; ++e) sums[tid][e] = acc[e];
-    __syncthreads();
-    if (tid < c) {
-        float s = 0.f;
-        for (int q = tid >> 3; q < 256; q += cg) s += sums[q][tid & 7];
-        partial[(int64_t)blockIdx.x * c + tid] = s;
-    }
+    block_sums<C>(group_sum<C>(own, ws[wave]), partial);
 }
 
 // column sums of partial[nrows][stride], columns c0 + blockIdx.x: one workgroup per column,
 // fixed-order tree
-__global__ __launch_bounds__(256) void k_reduce_cols(const float* __restrict__ partial, int nrows, int stride, int c0,
+__global__ __launch_bounds__(256) void k_reduce_cols(const double* __restrict__ partial, int nrows, int stride, int c0,
                                                      float* __restrict__ out) {
     __shared__ double sm[256];
     const int ch = blockIdx.x, tid = threadIdx.x;
@@ -824,62 +909,70 @@ __global__ void k_loss(const float* __restrict__ y, const float* __restrict__ t,
 }
 
 // Head backward with the last layer's ReLU: gp[v][c] = bf16(gy[v] w[c] where d1[v][c] > 0, else 0);
-// partial[block][0..15] = sum gy d1, [16] = sum gy, [17..32] = sum of the masked gradient before
-// its rounding (the last layer's bias gradient). A thread takes half a voxel's channels.
+// partial[block][0..15] = sum gy d1, [16] = sum gy, [17..32] = sum of the masked gradient before its rounding (the last
+// layer's bias gradient). The head's sums keep an order too: FP32 over 256 consecutive voxels, voxels t, t + 64,
+// .. together first, then t = 0, 1, ..; so thread (t, q) takes those voxels, channels 4 q .. 4 q + 3, and the bias
+// sums' groups of 64 (see group_sum) go through LDS. kHeadVox voxels per workgroup.
 constexpr int kHeadVox = 1024, kHeadCols = 2 * HEAD + 1;
 
 __global__ __launch_bounds__(256) void k_head_bwd(const float* __restrict__ gy, const bf16_t* __restrict__ d1,
                                                   const float* __restrict__ wb, bf16_t* __restrict__ gp, int64_t nv,
-                                                  float* __restrict__ partial) {
-    __shared__ float sums[4][kHeadCols];
-    const int tid = threadIdx.x, ch = (tid & 1) * 8, lane = tid & 63, wave = tid >> 6;
-    float hs[8], bs[8], w[8], gs = 0.f;
+                                                  double* __restrict__ partial) {
+    __shared__ float4 masked[256][4];   // [voxel][q]
+    __shared__ float4 heads[64][4];     // [t][q]: sum of gy d1
+    __shared__ float ones[64];          // [t]: sum of gy
+    const int tid = threadIdx.x, t = tid >> 2, q = tid & 3, lane = tid & 63, wave = tid >> 6;
+    const float w[4] = {wb[4 * q], wb[4 * q + 1], wb[4 * q + 2], wb[4 * q + 3]};
+    double total = 0.0, bias = 0.0;  // of column tid, and of the wave's bias sum of channel `lane`
+    for (int64_t v0 = (int64_t)blockIdx.x * kHeadVox; v0 < min(nv, ((int64_t)blockIdx.x + 1) * kHeadVox); v0 += 256) {
+        float hs[4] = {0.f, 0.f, 0.f, 0.f}, gs = 0.f;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        hs[e] = bs[e] = 0.f;
-        w[e] = wb[ch + e];
-    }
-    const int64_t v0 = (int64_t)blockIdx.x * kHeadVox, v1 = min(v0 + kHeadVox, nv);
-    for (int64_t v = v0 + (tid >> 1); v < v1; v += 128) {
-        const float g = gy[v];
-        const uint4 a = *(const uint4*)(d1 + v * HEAD + ch);
-        const unsigned u[4] = {a.x, a.y, a.z, a.w};
-        unsigned r[4];
+        for (int k = 0; k < 4; ++k) {
+            const int64_t v = v0 + 64 * k + t;
+            float m[4] = {0.f, 0.f, 0.f, 0.f};
+            if (v < nv) {
+                const float g = gy[v];
+                const uint2 a = *(const uint2*)(d1 + v * HEAD + 4 * q);
+                const float d[4] = {__uint_as_float(a.x << 16), __uint_as_float(a.x & 0xffff0000u),
+                                    __uint_as_float(a.y << 16), __uint_as_float(a.y & 0xffff0000u)};
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const float d[2] = {__uint_as_float(u[e] << 16), __uint_as_float(u[e] & 0xffff0000u)};
-            float m[2];
-#pragma unroll
-            for (int q = 0; q < 2; ++q) {
-                m[q] = d[q] > 0.f ? g * w[2 * e + q] : 0.f;
-                hs[2 * e + q] += g * d[q];
-                bs[2 * e + q] += m[q];
+                for (int e = 0; e < 4; ++e) {
+                    m[e] = d[e] > 0.f ? g * w[e] : 0.f;
+                    hs[e] = __builtin_fmaf(g, d[e], hs[e]);
+                }
+                gs += g;
+                *(uint2*)(gp + v * HEAD + 4 * q) = uint2{pack_bf2(m[0], m[1]), pack_bf2(m[2], m[3])};
             }
-            r[e] = pack_bf2(m[0], m[1]);
+            masked[64 * k + t][q] = make_float4(m[0], m[1], m[2], m[3]);
         }
-        gs += g;
-        *(uint4*)(gp + v * HEAD + ch) = uint4{r[0], r[1], r[2], r[3]};
-    }
-    // lanes of the same channel half
-    auto over = [](float v) {
+        heads[t][q] = make_float4(hs[0], hs[1], hs[2], hs[3]);
+        if (q == 0) ones[t] = gs;
+        __syncthreads();
+        // the wave's group of 64 voxels: lane (j, q) takes j, j + 16, ..
+        float4 own = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int o = 2; o < 64; o <<= 1) v += __shfl_xor(v, o, 64);
-        return v;
-    };
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        const float a = over(hs[e]), b = over(bs[e]);
-        if (lane < 2) {
-            sums[wave][ch + e] = a;
-            sums[wave][HEAD + 1 + ch + e] = b;
+        for (int i = 0; i < 4; ++i) {
+            const float4 m = masked[64 * wave + 16 * i + (lane >> 2)][lane & 3];
+            own.x += m.x;
+            own.y += m.y;
+            own.z += m.z;
+            own.w += m.w;
         }
+        bias += group_sum<HEAD>(own, &masked[64 * wave][0]);
+        if (tid <= HEAD) {
+            float s = 0.f;
+#pragma unroll 16
+            for (int i = 0; i < 64; ++i) s += tid < HEAD ? ((const float*)&heads[i][0])[tid] : ones[i];
+            total += s;
+        }
+        __syncthreads();
     }
-    gs = over(gs);
-    if (lane == 0) sums[wave][HEAD] = gs;
+    __shared__ double sums[4][HEAD];
+    if (lane < HEAD) sums[wave][lane] = bias;
     __syncthreads();
-    if (tid < kHeadCols)
-        partial[(int64_t)blockIdx.x * kHeadCols + tid] =
-            (sums[0][tid] + sums[1][tid]) + (sums[2][tid] + sums[3][tid]);
+    double* const row = partial + (int64_t)blockIdx.x * kHeadCols;
+    if (tid <= HEAD) row[tid] = total;
+    if (tid < HEAD) row[HEAD + 1 + tid] = (sums[0][tid] + sums[1][tid]) + (sums[2][tid] + sums[3][tid]);
 }
 
 // x_out = scale * y (scale = s * out_scale), FP64 output
@@ -975,7 +1068,8 @@ struct hp_net {
     float *gp1 = nullptr, *gp2 = nullptr;        // gradients of the pooled tensors
     float* wpart = nullptr;   // backward-weight partials
     int64_t wpart_cap = 0;
-    float* cpart = nullptr;   // column partials (bias / head)
+    double* cpart = nullptr;  // column partials (bias / head)
+    float* gfull = nullptr;   // a masked gradient before its rounding (see ConvArgs::full)
     int64_t cpart_cap = 0;
     double* ss = nullptr;     // [sum b^2, s, loss]
     double* dpart = nullptr;
@@ -1056,16 +1150,15 @@ void conv_launch(hp_net* N, int l, const bf16_t* a, int ca, int a_up, const bf16
 }
 
 // Backward-data convolution of layer l: the masked gradient gpre with the flipped, transposed
-// weights. The gradient of its input goes, masked by the ReLU of the layer before it, to gnext with
-// the channel sums in cpart (layers 9, 7, 5, 3, 1), for the concatenated inputs of layers 8 and 6
-// only the upsampled part with the skip part in `f32`, and plainly to `f32` for the pooled inputs of
-// layers 4 and 2. Returns the number of channel-sum rows.
-int conv_backward_data(hp_net* N, int l, float* f32) {
+// weights. The gradient of its input goes, masked by the ReLU of the layer before it, to gnext and
+// gfull (layers 9, 7, 5, 3, 1), for the concatenated inputs of layers 8 and 6 only the upsampled
+// part with the skip part in `f32`, and plainly to `f32` for the pooled inputs of layers 4 and 2.
+void conv_backward_data(hp_net* N, int l, float* f32) {
     const Level& L = N->lv[level_of_conv(l)];
     const unsigned blocks = conv_blocks(L, COUT[l], CIN[l]);
     ConvArgs p{N->gpre, COUT[l], 0, nullptr, 0, N->wbk[l], nullptr, N->gnext, CIN[l], L.nx, L.ny, L.nz, 0, nullptr,
                nullptr};
-    p.csum = N->cpart;
+    p.full = N->gfull;
     p.mask = l > 0 ? N->act[l - 1] : nullptr;
     switch (l) {
         case 9:
@@ -1090,7 +1183,6 @@ int conv_backward_data(hp_net* N, int l, float* f32) {
             conv_start<1, 4, 1, OUT_F32>(N, p, blocks);
             break;
     }
-    return (int)blocks;
 }
 
 // conv input tensors of layer l in the forward pass
@@ -1165,10 +1257,10 @@ void weight_gradient(hp_net* N, int l) {
     ConvIn in = conv_inputs(N, l);
     // channel chunks of 16 (the first layer's 8 padded channels read as 8 + 8 zeros)
     const int chunks = (cin_pad(l) + 15) / 16;
-    const int nbr = ((L.nx + BX - 1) / BX) * ((L.ny + BY - 1) / BY) * ((L.nz + WZ - 1) / WZ);
-    const int parts = std::min(nbr, std::max(1, kBwdWGroups / (chunks * (co / 16))));
+    const int nbr = ((L.nx + BX - 1) / BX) * ((L.ny + BY - 1) / BY) * ((L.nz + BZ - 1) / BZ);
+    const int parts = std::min(nbr, kBwdWParts);
     BwdWArgs bw{N->gpre, co, in.a, in.ca, in.a_up, in.b, in.cb, N->wpart, L.nx, L.ny, L.nz};
-    hipLaunchKernelGGL(k_conv_bwd_w, dim3(parts, chunks, co / 16), dim3(256), 0, N->stream, bw);
+    hipLaunchKernelGGL(k_conv_bwd_w, dim3(parts, chunks, co / 16), dim3(kMultipliers + kLoaders), 0, N->stream, bw);
     const int n = co * 27 * CIN[l];
     hipLaunchKernelGGL(k_reduce_dw, dim3(nblk(n, 16)), dim3(256), 0, N->stream, N->wpart, parts, chunks, co, CIN[l],
                        N->grad + N->woff[l]);
@@ -1185,18 +1277,27 @@ void column_sums(hp_net* N, int rows, int stride, int c0, int c, float* out) {
 void backward_conv(hp_net* N, int l, float* f32 = nullptr) {
     weight_gradient(N, l);
     if (l == 0) return;
-    const int rows = conv_backward_data(N, l, f32);
+    conv_backward_data(N, l, f32);
     if (l == 4 || l == 2) return;
-    column_sums(N, rows, COUT[l - 1], 0, COUT[l - 1], N->grad + N->boff[l - 1]);
+    const int64_t nv = N->lv[level_of_conv(l - 1)].nv;
+    const unsigned rows = nblk(nv, kSumVox);
+    const int c = COUT[l - 1];
+    switch (c) {
+        case 16: hipLaunchKernelGGL(k_channel_sums<16>, dim3(rows), dim3(256), 0, N->stream, N->gfull, nv, N->cpart); break;
+        case 32: hipLaunchKernelGGL(k_channel_sums<32>, dim3(rows), dim3(256), 0, N->stream, N->gfull, nv, N->cpart); break;
+        default: hipLaunchKernelGGL(k_channel_sums<64>, dim3(rows), dim3(256), 0, N->stream, N->gfull, nv, N->cpart); break;
+    }
+    column_sums(N, (int)rows, c, 0, c, N->grad + N->boff[l - 1]);
     std::swap(N->gpre, N->gnext);
 }
 
 // Masked gradient of the skip activation of layer l (1 or 3) into gpre, and its bias gradient.
 void backward_skip(hp_net* N, int l, const float* g, const float* gpool) {
     const Level& L = N->lv[level_of_conv(l)];
-    const unsigned rows = nblk(L.nv, kReluVox);
-    hipLaunchKernelGGL(k_relu_bwd_pool, dim3(rows), dim3(256), 0, N->stream, g, gpool, N->act[l], N->gpre, L.nx, L.ny,
-                       L.nv, COUT[l], N->cpart);
+    const unsigned rows = nblk(L.nv, kSumVox);
+    auto kernel = l == 1 ? k_relu_bwd_pool<16> : k_relu_bwd_pool<32>;
+    hipLaunchKernelGGL(kernel, dim3(rows), dim3(256), 0, N->stream, g, gpool, N->act[l], N->gpre, L.nx, L.ny, L.nv,
+                       N->cpart);
     column_sums(N, (int)rows, COUT[l], 0, COUT[l], N->grad + N->boff[l]);
 }
 
@@ -1271,16 +1372,16 @@ int hp_nn_create(int nx, int ny, int nz, int training, hp_net** out) {
             (rc = nalloc(N, &N->v, N->nparam)) || (rc = nalloc(N, &N->t, V)) || (rc = nalloc(N, &N->gy, V)))
             return bail(rc);
         const int64_t most = std::max(V * 16, N->lv[1].nv * 32);
-        if ((rc = nalloc(N, &N->gpre, most)) || (rc = nalloc(N, &N->gnext, most)) ||
+        if ((rc = nalloc(N, &N->gpre, most)) || (rc = nalloc(N, &N->gnext, most)) || (rc = nalloc(N, &N->gfull, most)) ||
             (rc = nalloc(N, &N->gskip0, V * 16)) || (rc = nalloc(N, &N->gskip1, N->lv[1].nv * 32)) ||
             (rc = nalloc(N, &N->gp1, N->lv[1].nv * 16)) || (rc = nalloc(N, &N->gp2, N->lv[2].nv * 32)))
             return bail(rc);
-        N->wpart_cap = (int64_t)kBwdWGroups * 16 * 27 * 16;
-        // channel-sum rows of the head, of the two skip activations and of the backward convolutions
-        N->cpart_cap = std::max<int64_t>({(int64_t)nblk(V, kHeadVox) * kHeadCols, (int64_t)nblk(V, kReluVox) * COUT[1],
-                                          (int64_t)nblk(N->lv[1].nv, kReluVox) * COUT[3]});
-        for (int l : {9, 8, 7, 6, 5, 3, 1})
-            N->cpart_cap = std::max(N->cpart_cap, (int64_t)conv_blocks(N->lv[level_of_conv(l)], COUT[l], CIN[l]) * COUT[l - 1]);
+        for (int l = 0; l < NCONV; ++l)
+            N->wpart_cap = std::max(N->wpart_cap, (int64_t)kBwdWParts * ((cin_pad(l) + 15) / 16) * COUT[l] * 27 * 16);
+        // channel-sum rows of the head and of the layers
+        N->cpart_cap = (int64_t)nblk(V, kHeadVox) * kHeadCols;
+        for (int l = 0; l < NCONV; ++l)
+            N->cpart_cap = std::max(N->cpart_cap, (int64_t)nblk(N->lv[level_of_conv(l)].nv, kSumVox) * COUT[l]);
         if ((rc = nalloc(N, &N->wpart, N->wpart_cap)) || (rc = nalloc(N, &N->cpart, N->cpart_cap)))
             return bail(rc);
         hipLaunchKernelGGL(k_zero_f32, dim3(nblk(N->nparam)), dim3(256), 0, 0, N->m, N->nparam);
