@@ -1,5 +1,5 @@
 // hp_coarse.hip -- the coarsest multigrid level: its dense operator, assembled on the device, and
-// the operator's inverse by blocked Gauss-Jordan elimination.
+// the operator's inverse by blocked symmetric elimination.
 //
 // The coarsest level holds at most a few thousand cells, so the V-cycle solves it exactly with
 // one dense matrix-vector product by the stored inverse. The operator is the same seven-point
@@ -7,82 +7,146 @@
 // coefficients of eqs. cpoiss/kappapoiss and the face factor of step (viii)); it is symmetric
 // positive definite when m > 0 and rho > 0, so elimination needs no pivoting and every pivot
 // (a diagonal entry of a Schur complement) is positive.
+//
+// The unknowns are cut into blocks of at most kB, each within a layer of the grid along one axis (or a few thin
+// layers). A step eliminates a set of blocks a that don't couple with each other, by the symmetric sweep: with D_a
+// the inverse of the diagonal block that the steps before left, P_aJ = D_a A_aJ,
+//     A_IJ <- A_IJ - sum_a A_Ia P_aJ,   A_aJ <- P_aJ,   A_Ia <- A_Ia D_a,   A_aa <- -D_a,
+// and after the last step the array holds minus the inverse. A layer couples with its neighbours alone, so
+// every other layer goes at once, then every other one of those left (of 8 layers 4, 2, 1, 1): 8 x 8 x 8 cells
+// take 8 steps where one block after the other takes 16, 16 x 16 cells 4 instead of 8.
+//
+// The steps are a chain of launches, bound by latency: pivots one after the other, and what a launch costs. So
+// a step is one launch, a workgroup per tile (I, J), I <= J: it updates its tile, and where that is the diagonal
+// block of a pivot of the next step, inverts it at once (k_inverse_step). The products are matrix
+// instructions, whose operand layout is that of the rows as they lie in memory, and by symmetry
+// also that of the columns. A step takes 9 to 11 us, 6 of them the 32 pivots of the next. New coefficients
+// take 225 us on 96 x 56 x 192 cells (504 coarsest ones) and 141 on 64 x 64 (256); with two launches per 32
+// pivots, swept one at a time through LDS (15 us), and every block on its own it was 475 and 265.
 #include "hp_internal.h"
 
+#include <algorithm>
 #include <cmath>
 
 namespace hp {
 
-// ------------------------------------------------------------------------------------------
-// assembly: one thread per matrix entry (row a, column b), row-major, n = nx ny nz
+typedef double f64x4 __attribute__((ext_vector_type(4)));
 
-__global__ __launch_bounds__(kBlock) void k_coarse_assemble(const double* __restrict__ rho,
-                                                            const double* __restrict__ m, int nx, int ny,
-                                                            int nz, int px, int py, int pz, double cx,
-                                                            double cy, double cz, int face_rule,
-                                                            double* __restrict__ A) {
-    const int n = nx * ny * nz;
-    const int64_t e = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (e >= (int64_t)n * n) return;
-    const int a = (int)(e / n), b = (int)(e - (int64_t)a * n);
-    const int c[3] = {a % nx, (a / nx) % ny, a / (nx * ny)};
-    const int dims[3] = {nx, ny, nz}, per[3] = {px, py, pz};
-    const int stride[3] = {1, nx, nx * ny};
-    const double cd[3] = {cx, cy, cz};
-    double v = 0.0;
-    if (a == b) v += m[a];
-    const double ra = rho[a];
-    // faces in the order x-, x+, y-, y+, z-, z+ (a diagonal entry accumulates them in that order)
-    for (int d = 0; d < 3; ++d)
-        for (int s = -1; s <= 1; s += 2) {
-            int t = c[d] + s;
-            if (t < 0 || t >= dims[d]) {
-                if (!per[d] || dims[d] < 2) continue;  // Neumann wall: no face
-                t = (t + dims[d]) % dims[d];
-            }
-            const int nb = a + (t - c[d]) * stride[d];
-            if (a != b && nb != b) continue;
-            const double rb = rho[nb];
-            const double kappa = face_rule == 1 ? 0.5 * (1.0 / ra + 1.0 / rb) : 2.0 / (ra + rb);
-            const double w = cd[d] * kappa;
-            v = (a == b) ? v + w : v - w;
+constexpr int kB = 32;    // widest block (a tile: kB x kB, padded with the identity)
+constexpr int kTile = kB * kB;
+constexpr int kSet = 8;   // most blocks eliminated in one step
+
+// ---- plan (host) ----
+
+// Layers of the grid along an axis, thin ones taken together to at most kB unknowns; the sets in which they
+// are eliminated.
+namespace {
+struct Layers {
+    std::vector<int> first, size;       // of each: first layer, unknowns
+    std::vector<std::vector<int>> sets;
+    int steps = 0;
+};
+
+Layers layers_along(const int n[3], const int per[3], int axis) {
+    Layers L;
+    const int cells = n[0] * n[1] * n[2] / n[axis], group = std::max(1, kB / cells);
+    for (int f = 0; f < n[axis]; f += group) {
+        L.first.push_back(f);
+        L.size.push_back(std::min(group, n[axis] - f) * cells);
+    }
+    std::vector<int> left(L.first.size());
+    for (size_t q = 0; q < left.size(); ++q) left[q] = (int)q;
+    while (!left.empty()) {
+        std::vector<int> set, rest;
+        for (size_t q = 0; q < left.size(); ++q) {
+            // every other one; on a ring the last one is the first one's neighbour
+            const bool next_to_first = per[axis] && q > 0 && q + 1 == left.size();
+            if (q % 2 == 0 && !next_to_first && (int)set.size() < kSet) set.push_back(left[q]);
+            else rest.push_back(left[q]);
         }
-    A[e] = v;
+        int chunks = 0;
+        for (int l : set) chunks = std::max(chunks, (L.size[l] + kB - 1) / kB);
+        L.steps += chunks;
+        L.sets.push_back(set);
+        left = rest;
+    }
+    return L;
+}
+}  // namespace
+
+InversePlan plan_inverse(const int n[3], const int per[3]) {
+    InversePlan P;
+    P.n = n[0] * n[1] * n[2];
+    int axis = 2;
+    Layers L = layers_along(n, per, 2);
+    for (int d = 1; d >= 0; --d) {
+        Layers o = layers_along(n, per, d);
+        if (o.steps < L.steps) {
+            L = o;
+            axis = d;
+        }
+    }
+    P.steps = L.steps;
+    // blocks (size, step, slot) in the order of the layers, and their unknowns
+    std::vector<int> blocks, perm, set_of(L.first.size()), slot_of(L.first.size()), step_of(L.sets.size());
+    for (size_t s = 0, at = 0; s < L.sets.size(); ++s) {
+        int chunks = 0;
+        for (size_t q = 0; q < L.sets[s].size(); ++q) {
+            set_of[L.sets[s][q]] = (int)s;
+            slot_of[L.sets[s][q]] = (int)q;
+            chunks = std::max(chunks, (L.size[L.sets[s][q]] + kB - 1) / kB);
+        }
+        step_of[s] = (int)at;
+        at += chunks;
+    }
+    std::vector<int> sets((size_t)L.steps * kSet, -1);
+    const int u = axis == 0 ? 1 : 0, v = axis == 2 ? 1 : 2;
+    const int stride[3] = {1, n[0], n[0] * n[1]};
+    for (size_t l = 0; l < L.first.size(); ++l) {
+        const int chunks = (L.size[l] + kB - 1) / kB, width = (L.size[l] + chunks - 1) / chunks;
+        const int layers = L.size[l] / (n[u] * n[v]);
+        std::vector<int> cells;
+        for (int k = L.first[l]; k < L.first[l] + layers; ++k)
+            for (int j = 0; j < n[v]; ++j)
+                for (int i = 0; i < n[u]; ++i) cells.push_back(k * stride[axis] + j * stride[v] + i * stride[u]);
+        for (int c = 0; c < chunks; ++c) {
+            const int step = step_of[set_of[l]] + c, id = (int)blocks.size() / 2;
+            sets[(size_t)step * kSet + slot_of[l]] = id;
+            blocks.push_back(step);
+            blocks.push_back(slot_of[l]);
+            for (int q = 0; q < kB; ++q)
+                perm.push_back(q < width && c * width + q < L.size[l] ? cells[c * width + q] : -1);
+        }
+    }
+    P.blocks = (int)blocks.size() / 2;
+    P.tables = blocks;
+    P.tables.insert(P.tables.end(), sets.begin(), sets.end());
+    P.tables.insert(P.tables.end(), perm.begin(), perm.end());
+    P.doubles = (int64_t)P.blocks * (P.blocks + 1) / 2 * kTile + 2 * kSet * (int64_t)(P.blocks + 1) * kTile;
+    P.ints = (int64_t)P.tables.size() + 2 * kSet * (int64_t)P.blocks;
+    return P;
 }
 
-void launch_coarse_assemble(const double* rho, const double* m, const int n[3], const int per[3],
-                            const double cd[3], int face_rule, double* A, hipStream_t s) {
-    const int64_t N = (int64_t)n[0] * n[1] * n[2];
-    const unsigned blocks = (unsigned)((N * N + kBlock - 1) / kBlock);
-    hipLaunchKernelGGL(k_coarse_assemble, dim3(blocks), dim3(kBlock), 0, s, rho, m, n[0], n[1], n[2],
-                       per[0], per[1], per[2], cd[0], cd[1], cd[2], face_rule, A);
-}
+// ---- device ----
 
-// ------------------------------------------------------------------------------------------
-// inverse by blocked Gauss-Jordan elimination, in place
-//
-// The matrix is cut into kGJ-wide block rows and columns. Step K eliminates block column K:
-// with D the inverse of the diagonal block A_KK (the Schur complement block left by steps
-// 0 .. K-1), the block row becomes A_Kj <- D A_Kj, every other block row loses its multiple
-// A_ij <- A_ij - A_iK A_Kj (old A_iK, new A_Kj), block column K takes A_iK <- -A_iK D, and the
-// diagonal block becomes D. After the last step the array holds the inverse. This is the
-// unblocked Gauss-Jordan sweep grouped by kGJ pivots: the same pivots, with the products summed in
-// another order (and each pivot applied through its reciprocal).
-//
-// Two launches per step: k_gj_panel (one workgroup per block column) inverts A_KK in LDS by the
-// unblocked sweep, updates its tile of block row K and saves its rows of the old block column K
-// to the workspace; k_gj_update (one workgroup per tile) applies the rank-kGJ update. Neither
-// launch writes what another workgroup of it reads:
-//   k_gj_panel writes block row K outside block column K; it reads block column K and its own tile.
-//   k_gj_update writes tiles outside block row K (and A_KK); it reads block row K outside block
-//   column K and the workspace.
-// Workspace layout (doubles): old block column K, n x kGJ row-major, then D, kGJ x kGJ.
+namespace {
 
-constexpr int kGJ = 32;
-constexpr int kGJThreads = 256;
-constexpr int kGJPer = kGJ * kGJ / kGJThreads;  // entries of a kGJ x kGJ tile per thread
-
-int64_t spd_inverse_work(int n) { return (int64_t)n * kGJ + kGJ * kGJ; }
+struct InverseArgs {
+    const int* blocks;  // per block: its step, its slot in the step's set
+    const int* sets;    // per step: kSet blocks (-1: none)
+    const int* perm;    // per block: its kB unknowns (-1: padding)
+    int* nonzero;       // [step parity][slot][block]: whether the panel's tile holds anything
+    double* tiles;      // upper tiles (I, J), row-major: tile J (J + 1) / 2 + I
+    double* panels;     // [step parity][slot][block]: row tiles of the step's pivots
+    double* diag;       // [step parity][slot]: inverses of their diagonal blocks
+    int nb, n, step;
+    const double *rho, *m;
+    int nx, ny, nz, px, py, pz;
+    double cx, cy, cz;
+    int face_rule;
+    double* out;
+    int* flag;
+};
 
 // 1/x from the hardware estimate and two Newton steps (within an ulp or so). A zero, infinite or
 // NaN pivot gives a result that is not finite; the pivot flag is taken from the pivot itself.
@@ -94,163 +158,275 @@ __device__ __forceinline__ double rcp_nr(double x) {
     return __builtin_fma(r, e, r);
 }
 
-__global__ __launch_bounds__(kGJThreads) void k_gj_panel(double* __restrict__ a, double* __restrict__ work,
-                                                         int n, int k0, int* __restrict__ flag) {
-    __shared__ double Db[2][kGJ][kGJ + 1];  // the diagonal block, ping-ponged between pivots
-    __shared__ double T[kGJ][kGJ + 1];
-    const int t = threadIdx.x;
-    const int bk = min(kGJ, n - k0);
-    const int j0 = blockIdx.x * kGJ;
-    const int nc = min(kGJ, n - j0);  // columns of this block column, rows of this row tile
-    // every global read of the kernel up front, from clamped (in-range) indices, so that they are
-    // in flight together: the diagonal block, this tile of block row K, and this tile's rows of
-    // block column K; the padding is selected afterwards
-    double dv[kGJPer], tv[kGJPer], cv[kGJPer];
-#pragma unroll
-    for (int u = 0; u < kGJPer; ++u) {
-        const int e = t + kGJThreads * u, r = e / kGJ, c = e % kGJ;
-        const int64_t rk = (int64_t)(k0 + min(r, bk - 1)) * n;
-        dv[u] = a[rk + k0 + min(c, bk - 1)];
-        tv[u] = a[rk + j0 + min(c, nc - 1)];
-        cv[u] = a[(int64_t)(j0 + min(r, nc - 1)) * n + k0 + min(c, bk - 1)];
-    }
-    // the diagonal block, padded to kGJ x kGJ with the identity (which the sweep leaves alone);
-    // the row-panel tile, padded with zeros
-#pragma unroll
-    for (int u = 0; u < kGJPer; ++u) {
-        const int e = t + kGJThreads * u, r = e / kGJ, c = e % kGJ;
-        Db[0][r][c] = (r < bk && c < bk) ? dv[u] : (r == c ? 1.0 : 0.0);
-        T[r][c] = (r < bk && c < nc) ? tv[u] : 0.0;
-    }
-    // unblocked Gauss-Jordan: pivot p scales row p by its reciprocal, the other rows lose their
-    // multiple of it, column p takes the negated multipliers and 1/pivot on the diagonal. Every
-    // entry of a step is read before the reciprocal is formed and the result is selected, not
-    // branched to, so each step costs one LDS round trip, the reciprocal and one barrier.
-    bool bad = false;
-    for (int p = 0; p < kGJ; ++p) {
-        __syncthreads();
-        const double(*S)[kGJ + 1] = Db[p & 1];
-        double(*W)[kGJ + 1] = Db[(p + 1) & 1];
-        const double piv = S[p][p];
-        double dpc[kGJPer], drp[kGJPer], drc[kGJPer];
-#pragma unroll
-        for (int u = 0; u < kGJPer; ++u) {
-            const int e = t + kGJThreads * u, r = e / kGJ, c = e % kGJ;
-            dpc[u] = S[p][c];
-            drp[u] = S[r][p];
-            drc[u] = S[r][c];
-        }
-        const double rp = rcp_nr(piv);
-#pragma unroll
-        for (int u = 0; u < kGJPer; ++u) {
-            // keeps the read of drc[u] up front (otherwise it can sink under the c != p branch)
-            asm volatile("" : "+v"(drc[u]));
-            const int e = t + kGJThreads * u, r = e / kGJ, c = e % kGJ;
-            const double f = drp[u] * rp;
-            const double other = (c == p) ? -f : drc[u] - f * dpc[u];
-            const double prow = (c == p) ? rp : dpc[u] * rp;
-            W[r][c] = (r == p) ? prow : other;
-        }
-        bad = bad || (p < bk && !(piv > 0.0 && piv < INFINITY));
-    }
-    if (bad && blockIdx.x == 0 && t == 0) *flag = 1;
-    double(*D)[kGJ + 1] = Db[kGJ & 1];
-    __syncthreads();
-    if (j0 == k0) {
-        for (int e = t; e < kGJ * kGJ; e += kGJThreads) work[(int64_t)n * kGJ + e] = D[e / kGJ][e % kGJ];
-    } else {
-        // the padding of D (identity) and T (zero rows) adds exact zeros to the sums
-        for (int e = t; e < kGJ * kGJ; e += kGJThreads) {
-            const int r = e / kGJ, c = e % kGJ;
-            double s = 0.0;
-#pragma unroll
-            for (int q = 0; q < kGJ; ++q) s += D[r][q] * T[q][c];
-            if (r < bk && c < nc) a[(int64_t)(k0 + r) * n + j0 + c] = s;
-        }
-    }
-    // this tile's rows of block column K as they were before this step (the update reads them)
-#pragma unroll
-    for (int u = 0; u < kGJPer; ++u) {
-        const int e = t + kGJThreads * u, r = e / kGJ, q = e % kGJ;
-        if (r < nc && q < bk) work[(int64_t)(j0 + r) * kGJ + q] = cv[u];
-    }
+__device__ __forceinline__ double lane_value(double v, int lane) {
+    const uint64_t u = __builtin_bit_cast(uint64_t, v);
+    const unsigned lo = __builtin_amdgcn_readlane((unsigned)u, lane), hi = __builtin_amdgcn_readlane((unsigned)(u >> 32), lane);
+    return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
 }
 
-__global__ __launch_bounds__(kGJThreads) void k_gj_update(double* __restrict__ a,
-                                                          const double* __restrict__ work, int n, int k0) {
-    __shared__ double C[kGJ][kGJ + 1];  // old block column K, this tile's rows
-    __shared__ double P[kGJ][kGJ + 1];  // new block row K, this tile's columns (D for column K)
-    const int t = threadIdx.x;
-    const int bk = min(kGJ, n - k0);
-    const int i0 = blockIdx.y * kGJ, j0 = blockIdx.x * kGJ;
-    const double* Dw = work + (int64_t)n * kGJ;
-    if (i0 == k0) {
-        if (j0 == k0)
-            for (int e = t; e < kGJ * kGJ; e += kGJThreads) {
-                const int r = e / kGJ, c = e % kGJ;
-                if (r < bk && c < bk) a[(int64_t)(k0 + r) * n + k0 + c] = Dw[e];
+__device__ __forceinline__ f64x4 mfma(double a, double b, f64x4 c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0); }
+
+// The operator's entries (a[e], b), natural indices (-1: none): a lane's part of a tile's quadrant. On a diagonal
+// tile one of them may be a diagonal entry. Every load is issued before the first is waited for.
+__device__ __forceinline__ f64x4 operator_entries(const InverseArgs& p, const int (&a)[4], int b, bool diagonal) {
+    const int at = max(b, 0), row = at / p.nx, i = at - row * p.nx, k = row / p.ny, j = row - k * p.ny;
+    const int sy = p.nx, sz = p.nx * p.ny;
+    // the neighbours in the order x-, x+, y-, y+, z-, z+ (a diagonal entry sums their faces in that order)
+    const int nb[6] = {i > 0 ? at - 1 : p.px ? at + (p.nx - 1) : -1,  i < p.nx - 1 ? at + 1 : p.px ? at - (p.nx - 1) : -1,
+                       j > 0 ? at - sy : p.py ? at + (p.ny - 1) * sy : -1, j < p.ny - 1 ? at + sy : p.py ? at - (p.ny - 1) * sy : -1,
+                       k > 0 ? at - sz : p.pz ? at + (p.nz - 1) * sz : -1, k < p.nz - 1 ? at + sz : p.pz ? at - (p.nz - 1) * sz : -1};
+    const double cd[3] = {p.cx, p.cy, p.cz};
+    const double rb = p.rho[at], mb = p.m[at];
+    double ra[4], rn[6];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) ra[e] = p.rho[max(a[e], 0)];
+    if (diagonal)
+#pragma unroll
+        for (int f = 0; f < 6; ++f) rn[f] = p.rho[nb[f] >= 0 ? nb[f] : at];
+    auto kappa = [&](double x, double y) { return p.face_rule == 1 ? 0.5 * (1.0 / x + 1.0 / y) : 2.0 / (x + y); };
+    double own = mb;
+    if (diagonal)
+#pragma unroll
+        for (int f = 0; f < 6; ++f)
+            if (nb[f] >= 0) own += cd[f >> 1] * kappa(rb, rn[f]);
+    f64x4 v;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        double w = 0.0;
+#pragma unroll
+        for (int f = 0; f < 6; ++f)
+            if (a[e] == nb[f]) w -= cd[f >> 1];
+        if (w != 0.0) w *= kappa(ra[e], rb);
+        v[e] = a[e] < 0 || b < 0 ? 0.0 : a[e] == b ? own : w;
+    }
+    return v;
+}
+
+// Minus the inverse of a 32 x 32 matrix held by a wave as four 16 x 16 results of the matrix instruction (lane l, value
+// i: row l / 16 + 4 i, column l % 16), by symmetric sweeps of four pivots. Rows 4 q .. 4 q + 3 of a tile are then value q
+// of every lane, in the layout of the instruction's right operand, and by symmetry columns 4 q .. in that of its
+// left operand: nothing moves between lanes but the 4 x 4 pivot block. Returns whether every pivot is positive
+// and finite.
+__device__ __forceinline__ bool sweep_32(f64x4 (&v)[2][2]) {
+    const int lane = threadIdx.x & 63, k = lane >> 4, j = lane & 3;
+    const f64x4 zero = {0.0, 0.0, 0.0, 0.0};
+    bool good = true;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+        const int tq = q >> 2, rq = q & 3;
+        const double row[2] = {v[tq][0][rq], v[tq][1][rq]}, src = row[tq];
+        auto at = [&](int r, int c) { return lane_value(src, 4 * rq + c + 16 * r); };
+        const double a00 = at(0, 0), a01 = at(0, 1), a02 = at(0, 2), a03 = at(0, 3), a11 = at(1, 1), a12 = at(1, 2),
+                     a13 = at(1, 3), a22 = at(2, 2), a23 = at(2, 3), a33 = at(3, 3);
+        // the inverse of [X Y; Y^T Z], 2 x 2 each, by X's inverse and that of S = Z - Y^T X^-1 Y
+        const double det = a00 * a11 - a01 * a01, rd = rcp_nr(det);
+        const double x00 = a11 * rd, x01 = -a01 * rd, x11 = a00 * rd;
+        const double w00 = x00 * a02 + x01 * a12, w01 = x00 * a03 + x01 * a13;  // W = X^-1 Y
+        const double w10 = x01 * a02 + x11 * a12, w11 = x01 * a03 + x11 * a13;
+        const double s00 = a22 - (a02 * w00 + a12 * w10), s01 = a23 - (a02 * w01 + a12 * w11),
+                     s11 = a33 - (a03 * w01 + a13 * w11);
+        const double dets = s00 * s11 - s01 * s01, rs = rcp_nr(dets);
+        const double d22 = s11 * rs, d23 = -s01 * rs, d33 = s00 * rs;
+        const double d02 = -(w00 * d22 + w01 * d23), d03 = -(w00 * d23 + w01 * d33);
+        const double d12 = -(w10 * d22 + w11 * d23), d13 = -(w10 * d23 + w11 * d33);
+        const double d00 = x00 - (d02 * w00 + d03 * w01), d01 = x01 - (d02 * w10 + d03 * w11),
+                     d11 = x11 - (d12 * w10 + d13 * w11);
+        good = good && a00 > 0.0 && a00 < INFINITY && det > 0.0 && det < INFINITY && s00 > 0.0 && s00 < INFINITY &&
+               dets > 0.0 && dets < INFINITY;
+        // entry (lane % 4, lane / 16) of the inverse
+        auto pick = [](int e, double a, double b, double c, double d) { return e & 2 ? (e & 1 ? d : c) : (e & 1 ? b : a); };
+        const double inv = pick(j, pick(k, d00, d01, d02, d03), pick(k, d01, d11, d12, d13), pick(k, d02, d12, d22, d23),
+                                pick(k, d03, d13, d23, d33));
+        const double prow[2] = {mfma(inv, row[0], zero)[0], mfma(inv, row[1], zero)[0]};
+        // the lanes that hold the pivots' own columns (of tile column tq): these become A_iK D
+        const bool own = ((lane & 15) >> 2) == rq;
+#pragma unroll
+        for (int tj = 0; tj < 2; ++tj) {
+            const bool mine = own && tj == tq;
+            const double b = mine ? inv : -prow[tj];
+#pragma unroll
+            for (int ti = 0; ti < 2; ++ti) {
+                f64x4 c = v[ti][tj];
+                if (tj == tq)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) c[e] = own ? 0.0 : c[e];
+                v[ti][tj] = mfma(row[ti], b, c);
             }
+            v[tq][tj][rq] = mine ? -inv : prow[tj];
+        }
+    }
+    return good;
+}
+
+enum { STEP_FIRST, STEP_INNER, STEP_LAST };
+
+// One step on one tile, a wave per 16 x 16 quadrant; its pivots' row tiles and inverted diagonal blocks are there from the
+// launch before (STEP_FIRST: no pivots, the tile is assembled), and those of the next step are left for the
+// next launch. No workgroup reads what another one writes in the same launch. STEP_LAST writes the inverse.
+template <int MODE>
+__global__ __launch_bounds__(256) void k_inverse_step(InverseArgs p) {
+    __shared__ double lds[2][8][2][64];  // -P of a pivot, by rows of four and column half; at the end the tile
+    const int t = blockIdx.x;
+    int J = (int)((sqrtf(8.0f * (float)t + 1.0f) - 1.0f) * 0.5f);
+    while ((J + 1) * (J + 2) / 2 <= t) ++J;
+    while (J * (J + 1) / 2 > t) --J;
+    const int I = t - J * (J + 1) / 2;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, qi = wave >> 1, qj = wave & 1;
+    const int k = lane >> 4, c = lane & 15;
+    const int here = p.step & 1, then = here ^ 1, next = p.step + 1;
+    const int step_i = p.blocks[2 * I], slot_i = p.blocks[2 * I + 1], step_j = p.blocks[2 * J], slot_j = p.blocks[2 * J + 1];
+    double* const tile = p.tiles + (int64_t)t * kTile + (16 * qi + k) * kB + 16 * qj + c;
+    f64x4 acc;
+    if constexpr (MODE == STEP_FIRST) {
+        const int b = p.perm[J * kB + 16 * qj + c];
+        int a[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) a[e] = p.perm[I * kB + 16 * qi + k + 4 * e];
+        acc = operator_entries(p, a, b, I == J);
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (I == J && a[e] < 0 && 16 * qi + k + 4 * e == 16 * qj + c) acc[e] = 1.0;  // padding
+    } else {
+        int in[kSet], full[kSet];  // the step's pivots, and whether both tiles of the product hold anything
+#pragma unroll
+        for (int a = 0; a < kSet; ++a) {
+            in[a] = p.sets[p.step * kSet + a];
+            const int* const nz = p.nonzero + (here * kSet + a) * p.nb;
+            full[a] = nz[I] & nz[J];
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[e] = tile[4 * e * kB];
+        const f64x4 zero = {0.0, 0.0, 0.0, 0.0};
+        // rows 4 i .. of a tile, columns of this lane's half
+        auto rows = [&](const double* tile, int half, int i) { return tile[(4 * i + k) * kB + 16 * half + c]; };
+        auto panel = [&](int a, int block) { return p.panels + ((int64_t)(here * kSet + a) * p.nb + block) * kTile; };
+        auto diag = [&](int a) { return p.diag + (here * kSet + a) * kTile; };
+        // A^T B (the first by its columns), quadrant (half_a, half_b)
+        auto product = [&](const double* A, int half_a, const double* B, int half_b) {
+            double x[8], y[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                x[i] = rows(A, half_a, i);
+                y[i] = rows(B, half_b, i);
+            }
+            f64x4 s = zero;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) s = mfma(x[i], y[i], s);
+            return s;
+        };
+        const bool pi = step_i == p.step, pj = step_j == p.step;
+        if (pi && pj) {
+            // (two pivots of a step don't couple: that tile stays zero)
+            if (I == J)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) acc[e] = -diag(slot_i)[(16 * qi + k + 4 * e) * kB + 16 * qj + c];
+        } else if (pi) {
+            acc = product(diag(slot_i), qi, panel(slot_i, J), qj);
+        } else if (pj) {
+            acc = product(panel(slot_j, I), qi, diag(slot_j), qj);
+        } else {
+            int turn = 0;
+#pragma unroll
+            for (int a = 0; a < kSet; ++a) {
+                if (in[a] < 0 || !full[a]) continue;
+                // this wave's rows of P, then the product with all of them
+                const f64x4 s = product(diag(a), qi, panel(a, J), qj);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) lds[turn][4 * qi + e][qj][lane] = -s[e];
+                double x[8];
+#pragma unroll
+                for (int i = 0; i < 8; ++i) x[i] = rows(panel(a, I), qi, i);
+                __syncthreads();
+#pragma unroll
+                for (int i = 0; i < 8; ++i) acc = mfma(x[i], lds[turn][i][qj][lane], acc);
+                turn ^= 1;
+            }
+        }
+    }
+    if constexpr (MODE == STEP_LAST) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            // (the lower half of a diagonal tile is left out: the inverse is exactly symmetric)
+            const int row = 16 * qi + k + 4 * e, col = 16 * qj + c, a = p.perm[I * kB + row], b = p.perm[J * kB + col];
+            if (a < 0 || b < 0 || (I == J && row > col)) continue;
+            p.out[(int64_t)a * p.n + b] = -acc[e];
+            p.out[(int64_t)b * p.n + a] = -acc[e];
+        }
         return;
     }
-    const bool colK = (j0 == k0);
-    const int nr = min(kGJ, n - i0), nc = min(kGJ, n - j0);
-    // block row K's tile (D for block column K), row stride ps
-    const double* Ps = colK ? Dw : a + (int64_t)k0 * n + j0;
-    const int64_t ps = colK ? kGJ : n;
-    // thread t updates row t / 8 of the tile, columns t % 8 + 8 u
-    const int r = t / 8;
-    // every global read up front, from clamped indices; the zero padding is selected afterwards
-    double cv[kGJPer], pv[kGJPer], old[kGJPer];
 #pragma unroll
-    for (int u = 0; u < kGJPer; ++u) {
-        const int e = t + kGJThreads * u, er = e / kGJ, ec = e % kGJ;
-        cv[u] = work[(int64_t)(i0 + min(er, nr - 1)) * kGJ + min(ec, bk - 1)];
-        pv[u] = Ps[(int64_t)min(er, bk - 1) * ps + min(ec, nc - 1)];
-        old[u] = a[(int64_t)(i0 + min(r, nr - 1)) * n + j0 + min(t % 8 + 8 * u, nc - 1)];
-    }
+    for (int e = 0; e < 4; ++e) tile[4 * e * kB] = acc[e];
+    const bool ni = step_i == next, nj = step_j == next;
+    if (!ni && !nj) return;
+    const int any = __syncthreads_or(acc[0] != 0.0 || acc[1] != 0.0 || acc[2] != 0.0 || acc[3] != 0.0);
+    auto leave = [&](int slot, int block, bool turned) {
+        double* const to = p.panels + ((int64_t)(then * kSet + slot) * p.nb + block) * kTile;
 #pragma unroll
-    for (int u = 0; u < kGJPer; ++u) {
-        const int e = t + kGJThreads * u, er = e / kGJ, ec = e % kGJ;
-        C[er][ec] = (er < nr && ec < bk) ? cv[u] : 0.0;
-        P[er][ec] = (er < bk && ec < nc) ? pv[u] : 0.0;
+        for (int e = 0; e < 4; ++e) {
+            const int row = 16 * qi + k + 4 * e, col = 16 * qj + c;
+            to[turned ? col * kB + row : row * kB + col] = acc[e];
+        }
+        if (threadIdx.x == 0) p.nonzero[(then * kSet + slot) * p.nb + block] = any;
+    };
+    if (I != J) {
+        if (ni) leave(slot_i, J, false);
+        if (nj) leave(slot_j, I, true);
+        return;
     }
+    // the next step's pivot block: its inverse, by the first wave
+    double* const own = &lds[0][0][0][0];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) own[(wave * 4 + e) * 64 + lane] = acc[e];
     __syncthreads();
-    // the zero padding of C and P adds exact zeros to the sums
-    double s[kGJPer];
+    if (wave) return;
+    f64x4 v[2][2];
 #pragma unroll
-    for (int u = 0; u < kGJPer; ++u) s[u] = 0.0;
+    for (int w = 0; w < 4; ++w)
 #pragma unroll
-    for (int q = 0; q < kGJ; ++q) {
-        const double cq = C[r][q];
+        for (int e = 0; e < 4; ++e) v[w >> 1][w & 1][e] = own[(w * 4 + e) * 64 + lane];
+    if (!sweep_32(v) && lane == 0) *p.flag = 1;
+    double* const to = p.diag + (then * kSet + slot_i) * kTile;
 #pragma unroll
-        for (int u = 0; u < kGJPer; ++u) s[u] += cq * P[q][t % 8 + 8 * u];
-    }
+    for (int w = 0; w < 4; ++w)
 #pragma unroll
-    for (int u = 0; u < kGJPer; ++u) {
-        const int c = t % 8 + 8 * u;
-        if (r < nr && c < nc) a[(int64_t)(i0 + r) * n + j0 + c] = colK ? -s[u] : old[u] - s[u];
-    }
+        for (int e = 0; e < 4; ++e) to[(16 * (w >> 1) + k + 4 * e) * kB + 16 * (w & 1) + c] = -v[w >> 1][w & 1][e];
 }
 
-// x = (x + x^T) / 2 in place (one thread per pair i < j)
-__global__ __launch_bounds__(kBlock) void k_symmetrize(double* __restrict__ x, int n) {
-    const int64_t e = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (e >= (int64_t)n * n) return;
-    const int i = (int)(e / n), j = (int)(e - (int64_t)i * n);
-    if (i >= j) return;
-    const double v = 0.5 * (x[(int64_t)i * n + j] + x[(int64_t)j * n + i]);
-    x[(int64_t)i * n + j] = v;
-    x[(int64_t)j * n + i] = v;
-}
+}  // namespace
 
-void launch_spd_inverse(double* a, double* work, int n, int* flag, hipStream_t s) {
-    const unsigned nt = (unsigned)((n + kGJ - 1) / kGJ);
-    for (int k0 = 0; k0 < n; k0 += kGJ) {
-        hipLaunchKernelGGL(k_gj_panel, dim3(nt), dim3(kGJThreads), 0, s, a, work, n, k0, flag);
-        hipLaunchKernelGGL(k_gj_update, dim3(nt, nt), dim3(kGJThreads), 0, s, a, (const double*)work, n, k0);
-    }
-    const unsigned blocks = (unsigned)(((int64_t)n * n + kBlock - 1) / kBlock);
-    hipLaunchKernelGGL(k_symmetrize, dim3(blocks), dim3(kBlock), 0, s, a, n);
+void launch_coarse_inverse(const InversePlan& P, double* work, int* tables, const double* rho, const double* m,
+                           const int n[3], const int per[3], const double cd[3], int face_rule, double* out, int* flag,
+                           hipStream_t s) {
+    const int64_t tiles = (int64_t)P.blocks * (P.blocks + 1) / 2;
+    InverseArgs a{};
+    a.blocks = tables;
+    a.sets = a.blocks + 2 * P.blocks;
+    a.perm = a.sets + P.steps * kSet;
+    a.nonzero = tables + P.tables.size();
+    a.tiles = work;
+    a.panels = a.tiles + tiles * kTile;
+    a.diag = a.panels + 2 * kSet * (int64_t)P.blocks * kTile;
+    a.nb = P.blocks;
+    a.n = P.n;
+    a.step = -1;
+    a.rho = rho;
+    a.m = m;
+    a.nx = n[0];
+    a.ny = n[1];
+    a.nz = n[2];
+    a.px = per[0] && n[0] > 1;  // one cell has no wrap face
+    a.py = per[1] && n[1] > 1;
+    a.pz = per[2] && n[2] > 1;
+    a.cx = cd[0];
+    a.cy = cd[1];
+    a.cz = cd[2];
+    a.face_rule = face_rule;
+    a.out = out;
+    a.flag = flag;
+    const dim3 grid((unsigned)tiles), block(256);
+    hipLaunchKernelGGL(k_inverse_step<STEP_FIRST>, grid, block, 0, s, a);
+    for (a.step = 0; a.step + 1 < P.steps; ++a.step) hipLaunchKernelGGL(k_inverse_step<STEP_INNER>, grid, block, 0, s, a);
+    hipLaunchKernelGGL(k_inverse_step<STEP_LAST>, grid, block, 0, s, a);
 }
 
 }  // namespace hp

@@ -3,6 +3,7 @@
 
 #include <hip/hip_runtime.h>
 #include <cstdint>
+#include <vector>
 
 #include "hp.h"
 
@@ -154,14 +155,19 @@ void launch_relayout(const T* src, T* dst, int nx, int ny, int nz, int to_split,
 bool split_layout_ok(int nx, int ny, int nz, const Transfer* t);
 template <typename T>
 void launch_coarse_solve(const double* ainv, int nc, const T* b, T* x, hipStream_t s);
-// Dense coarsest operator (N x N row-major, N = n[0] n[1] n[2]) from the level's rho and m: the
-// seven-point flux-form matrix with face weights cd[d] * kappa (per[d]: axis d periodic).
-void launch_coarse_assemble(const double* rho, const double* m, const int n[3], const int per[3],
-                            const double cd[3], int face_rule, double* A, hipStream_t s);
-// In-place inverse of the dense SPD n x n matrix a (row-major) by blocked Gauss-Jordan steps;
-// work holds spd_inverse_work(n) doubles; *flag is set on a pivot that is not positive and finite.
-int64_t spd_inverse_work(int n);
-void launch_spd_inverse(double* a, double* work, int n, int* flag, hipStream_t s);
+// Order of elimination for the coarsest operator's inverse (per[d]: axis d periodic).
+struct InversePlan {
+    int n = 0, blocks = 0, steps = 0;
+    int64_t doubles = 0, ints = 0;  // device memory of work and tables
+    std::vector<int> tables;        // what stands at the start of tables
+};
+InversePlan plan_inverse(const int n[3], const int per[3]);
+// Inverse (N x N row-major, N = n[0] n[1] n[2]) of the dense coarsest operator, the seven-point flux-form
+// matrix with face weights cd[d] * kappa, from the level's rho and m; *flag is set on a pivot that
+// is not positive and finite.
+void launch_coarse_inverse(const InversePlan& plan, double* work, int* tables, const double* rho, const double* m,
+                           const int n[3], const int per[3], const double cd[3], int face_rule, double* out, int* flag,
+                           hipStream_t s);
 
 // Deterministic dot <x, y> accumulated in FP64.
 template <typename T>

@@ -76,7 +76,9 @@ struct hp_handle {
     std::vector<LevelData> lv;
     int nc = 0;
     double* ainv = nullptr;       // inverse of the coarsest operator (nc x nc)
-    double* ainv_work = nullptr;  // workspace of the blocked Gauss-Jordan inverse
+    InversePlan ainv_plan;        // its order of elimination, and the workspace
+    double* ainv_work = nullptr;
+    int* ainv_tables = nullptr;
     double *r = nullptr, *z = nullptr, *p = nullptr, *q = nullptr;
     double* r2 = nullptr;  // second residual array: the fused residual update writes r' there
     // the split iterate of the running solve is zero and has not been written yet (a zero initial
@@ -251,7 +253,6 @@ void time_end(hp_handle* H) {
 // has waited for the side stream (join_coarse_inverse) and been synchronised.
 int start_coarse_inverse(hp_handle* H) {
     LevelData& C = H->lv.back();
-    const int n = (int)C.N;
     const int per[3] = {H->bc.x == HP_BC_PERIODIC, H->bc.y == HP_BC_PERIODIC,
                         H->bc.z == HP_BC_PERIODIC};
     const double dt2 = H->dt * H->dt;
@@ -261,8 +262,8 @@ int start_coarse_inverse(hp_handle* H) {
     HIPCHK(hipEventRecord(H->ev_fork, H->stream));
     HIPCHK(hipStreamWaitEvent(H->side, H->ev_fork, 0));
     HIPCHK(hipMemsetAsync(H->flag + 1, 0, sizeof(int), H->side));
-    launch_coarse_assemble(C.rho, C.m, C.n, per, cd, H->face_rule, H->ainv, H->side);
-    launch_spd_inverse(H->ainv, H->ainv_work, n, H->flag + 1, H->side);
+    launch_coarse_inverse(H->ainv_plan, H->ainv_work, H->ainv_tables, C.rho, C.m, C.n, per, cd, H->face_rule, H->ainv,
+                          H->flag + 1, H->side);
     CHK(check_launch());
     HIPCHK(hipMemcpyAsync(H->host_flag + 1, H->flag + 1, sizeof(int), hipMemcpyDeviceToHost, H->side));
     HIPCHK(hipEventRecord(H->ev_join, H->side));
@@ -1288,9 +1289,14 @@ int hp_setup_two_density(const hp_grid* grid, const double* rho_n, const double*
             if ((rc = dalloc(H, &L.t, L.N)) || (rc = dalloc(H, &L.t32, L.N))) return bail(rc);
         }
     }
-    if ((rc = dalloc(H, &H->ainv, (int64_t)H->nc * H->nc)) ||
-        (rc = dalloc(H, &H->ainv_work, spd_inverse_work(H->nc))))
+    const int per[3] = {H->bc.x == HP_BC_PERIODIC, H->bc.y == HP_BC_PERIODIC, H->bc.z == HP_BC_PERIODIC};
+    H->ainv_plan = plan_inverse(H->lv.back().n, per);
+    const InversePlan& plan = H->ainv_plan;
+    if ((rc = dalloc(H, &H->ainv, (int64_t)H->nc * H->nc)) || (rc = dalloc(H, &H->ainv_work, plan.doubles)) ||
+        (rc = dalloc(H, &H->ainv_tables, plan.ints)))
         return bail(rc);
+    if (hipMemcpy(H->ainv_tables, plan.tables.data(), plan.tables.size() * sizeof(int), hipMemcpyHostToDevice) != hipSuccess)
+        return bail(fail(HP_EHIP, "hipMemcpy failed"));
     if ((rc = dalloc(H, &H->r, N)) || (rc = dalloc(H, &H->z, N)) || (rc = dalloc(H, &H->p, N)) ||
         (rc = dalloc(H, &H->q, N)) || (rc = dalloc(H, &H->r2, N)))
         return bail(rc);
