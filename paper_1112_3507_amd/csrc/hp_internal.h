@@ -94,6 +94,19 @@ void launch_neumann_rhs(int nx, int ny, int nz, int d, int side, double coef, co
                         hipStream_t s);
 // coarse rho and m as the means over each coarse cell's children (natural order; the FP32 copies
 // in the red-black split order with split32)
+// Where the coefficients of the finest level (rho_split and m_split only in split order, then the FP32 ones are, too)
+// and of the next one go.
+struct SetupOut {
+    double *rho, *m, *rho_split, *m_split;
+    float *rho32, *m32;
+    double *rho_c, *m_c;
+    float *rho32_c, *m32_c;
+    int split32_c;  // the next level's FP32 ones in split order
+};
+// launch_setup_coef and launch_coarsen_coef towards the next level in one pass; false where the grid or the
+// arrays don't allow it
+bool launch_setup_coarsen(const double* rho_mass, const double* rho_face, const double* c2, const SetupOut& o,
+                          const Transfer& t, int* bad, hipStream_t s);
 void launch_coarsen_coef(const Transfer& t, const double* rho_f, const double* m_f,
                          double* rho_c, double* m_c, float* rho32_c, float* m32_c, bool split32,
                          hipStream_t s);

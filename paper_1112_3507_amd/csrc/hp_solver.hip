@@ -427,14 +427,22 @@ int load_coefficients(hp_handle* H, const double* rho_mass, const double* rho_fa
     if (split0) CHK(alloc_split_buffers(H));
     double* rho0 = split0 ? H->rho_nat : F.rho;
     double* m0 = split0 ? H->m_nat : F.m;
-    launch_setup_coef(rho_mass, rho_face, c2, rho0, m0, split0 ? F.rho : nullptr, split0 ? F.m : nullptr,
-                      F.rho32, F.m32, F.n[0], F.n[1], F.n[2], split0, H->flag, H->stream);
+    bool coarsened = false;  // level 1 is done
+    if (H->lv.size() > 1) {
+        LevelData& C = H->lv[1];
+        const SetupOut out{rho0, m0, split0 ? F.rho : nullptr, split0 ? F.m : nullptr, F.rho32, F.m32,
+                           C.rho, C.m, C.rho32, C.m32, H->want_split && split_target(H, 1)};
+        coarsened = launch_setup_coarsen(rho_mass, rho_face, c2, out, transfer(H, 0), H->flag, H->stream);
+    }
+    if (!coarsened)
+        launch_setup_coef(rho_mass, rho_face, c2, rho0, m0, split0 ? F.rho : nullptr, split0 ? F.m : nullptr,
+                          F.rho32, F.m32, F.n[0], F.n[1], F.n[2], split0, H->flag, H->stream);
     CHK(check_launch());
     HIPCHK(hipMemcpyAsync(H->host_flag, H->flag, sizeof(int), hipMemcpyDeviceToHost, H->stream));
     // The input check is read once everything below has run: with an invalid cell the steps
     // below compute non-finite values (no index or trip count depends on a value) and the call
     // fails at the end, leaving the coefficients undefined as before.
-    for (size_t l = 0; l + 1 < H->lv.size(); ++l) {
+    for (size_t l = coarsened ? 1 : 0; l + 1 < H->lv.size(); ++l) {
         LevelData& C = H->lv[l + 1];
         launch_coarsen_coef(transfer(H, (int)l), l == 0 ? rho0 : H->lv[l].rho, l == 0 ? m0 : H->lv[l].m,
                             C.rho, C.m, C.rho32, C.m32, H->want_split && split_target(H, l + 1), H->stream);
