@@ -1047,6 +1047,11 @@ struct Level {
 
 using namespace hpnn;
 
+constexpr int kGradBufs = 4, kSides = 2;
+// Fewest voxels for weight gradients on streams of their own: the events take the host 50 us a step, and below it is the
+// host that a step waits for (32 x 64 x 32: 690 us with them, 655 without; 64^3: 750 and 803).
+constexpr int64_t kBesideVoxels = 1 << 17;
+
 struct hp_net {
     hipStream_t stream = nullptr;
     Level lv[3];
@@ -1062,11 +1067,18 @@ struct hp_net {
     float* y = nullptr;
     // training buffers
     float *t = nullptr, *gy = nullptr;
-    // masked gradient (bf16) at the output of the layer in turn, and of the layer before it
-    bf16_t *gpre = nullptr, *gnext = nullptr;
+    // masked gradients (bf16) at the layers' outputs, taken in turn: the layer's own in gbuf[cur]. The weight
+    // gradients read them on streams of their own, taken in turn, too.
+    bf16_t* gbuf[kGradBufs] = {};
+    int cur = 0;
+    bool beside = false;  // whether they do; two buffers and one wpart otherwise
+    hipStream_t side[kSides] = {};
+    int turn = 0;
+    hipEvent_t ready = nullptr, read[kGradBufs] = {};  // a gradient is written; gbuf[q] has been read
+    bool reading[kGradBufs] = {};                      // read[q] has been recorded in this pass
     float *gskip0 = nullptr, *gskip1 = nullptr;  // gradients of e1 and e2 through their skip connections
     float *gp1 = nullptr, *gp2 = nullptr;        // gradients of the pooled tensors
-    float* wpart = nullptr;   // backward-weight partials
+    float* wpart[kSides] = {};  // backward-weight partials
     int64_t wpart_cap = 0;
     double* cpart = nullptr;  // column partials (bias / head)
     float* gfull = nullptr;   // a masked gradient before its rounding (see ConvArgs::full)
@@ -1149,14 +1161,14 @@ void conv_launch(hp_net* N, int l, const bf16_t* a, int ca, int a_up, const bf16
     }
 }
 
-// Backward-data convolution of layer l: the masked gradient gpre with the flipped, transposed
-// weights. The gradient of its input goes, masked by the ReLU of the layer before it, to gnext and
+// Backward-data convolution of layer l: its masked gradient with the flipped, transposed
+// weights. The gradient of its input goes, masked by the ReLU of the layer before it, to `next` and
 // gfull (layers 9, 7, 5, 3, 1), for the concatenated inputs of layers 8 and 6 only the upsampled
 // part with the skip part in `f32`, and plainly to `f32` for the pooled inputs of layers 4 and 2.
-void conv_backward_data(hp_net* N, int l, float* f32) {
+void conv_backward_data(hp_net* N, int l, bf16_t* next, float* f32) {
     const Level& L = N->lv[level_of_conv(l)];
     const unsigned blocks = conv_blocks(L, COUT[l], CIN[l]);
-    ConvArgs p{N->gpre, COUT[l], 0, nullptr, 0, N->wbk[l], nullptr, N->gnext, CIN[l], L.nx, L.ny, L.nz, 0, nullptr,
+    ConvArgs p{N->gbuf[N->cur], COUT[l], 0, nullptr, 0, N->wbk[l], nullptr, next, CIN[l], L.nx, L.ny, L.nz, 0, nullptr,
                nullptr};
     p.full = N->gfull;
     p.mask = l > 0 ? N->act[l - 1] : nullptr;
@@ -1250,8 +1262,24 @@ int rhs_scale(hp_net* N, const double* b) {
     return check();
 }
 
-// Weight gradient of layer l from its masked output gradient in gpre.
+// The buffer for the next masked gradient, once nothing reads it any more.
+int next_gradient(hp_net* N) {
+    const int q = (N->cur + 1) % (N->beside ? kGradBufs : 2);
+    if (N->reading[q]) (void)hipStreamWaitEvent(N->stream, N->read[q], 0);
+    return q;
+}
+
+// Weight gradient of layer l from its masked output gradient, beside what follows on the network's stream: its
+// workgroups are few (96 at 16 -> 16 channels) and each brick waits for the one before. A step at 128^3
+// takes 1941 us so, 2238 in one stream (2105 with one stream for them and three buffers).
 void weight_gradient(hp_net* N, int l) {
+    hipStream_t side = N->stream;
+    if (N->beside) {
+        N->turn = (N->turn + 1) % kSides;
+        side = N->side[N->turn];
+        (void)hipEventRecord(N->ready, N->stream);
+        (void)hipStreamWaitEvent(side, N->ready, 0);
+    }
     const Level& L = N->lv[level_of_conv(l)];
     const int co = COUT[l];
     ConvIn in = conv_inputs(N, l);
@@ -1259,11 +1287,15 @@ void weight_gradient(hp_net* N, int l) {
     const int chunks = (cin_pad(l) + 15) / 16;
     const int nbr = ((L.nx + BX - 1) / BX) * ((L.ny + BY - 1) / BY) * ((L.nz + BZ - 1) / BZ);
     const int parts = std::min(nbr, kBwdWParts);
-    BwdWArgs bw{N->gpre, co, in.a, in.ca, in.a_up, in.b, in.cb, N->wpart, L.nx, L.ny, L.nz};
-    hipLaunchKernelGGL(k_conv_bwd_w, dim3(parts, chunks, co / 16), dim3(kMultipliers + kLoaders), 0, N->stream, bw);
+    BwdWArgs bw{N->gbuf[N->cur], co, in.a, in.ca, in.a_up, in.b, in.cb, N->wpart[N->turn], L.nx, L.ny, L.nz};
+    hipLaunchKernelGGL(k_conv_bwd_w, dim3(parts, chunks, co / 16), dim3(kMultipliers + kLoaders), 0, side, bw);
     const int n = co * 27 * CIN[l];
-    hipLaunchKernelGGL(k_reduce_dw, dim3(nblk(n, 16)), dim3(256), 0, N->stream, N->wpart, parts, chunks, co, CIN[l],
+    hipLaunchKernelGGL(k_reduce_dw, dim3(nblk(n, 16)), dim3(256), 0, side, N->wpart[N->turn], parts, chunks, co, CIN[l],
                        N->grad + N->woff[l]);
+    if (N->beside) {
+        (void)hipEventRecord(N->read[N->cur], side);
+        N->reading[N->cur] = true;
+    }
 }
 
 // out[0..c) = column sums of cpart[rows][stride] from column c0 on
@@ -1271,14 +1303,16 @@ void column_sums(hp_net* N, int rows, int stride, int c0, int c, float* out) {
     hipLaunchKernelGGL(k_reduce_cols, dim3(c), dim3(256), 0, N->stream, N->cpart, rows, stride, c0, out);
 }
 
-// Backward of layer l from its masked output gradient in gpre: its weight gradient, then the
+// Backward of layer l from its masked output gradient: its weight gradient, and the
 // gradient of its input (see conv_backward_data). Where that is the masked gradient of layer
-// l - 1's output, it becomes gpre and that layer's bias gradient is formed.
+// l - 1's output, it becomes the current one and that layer's bias gradient is formed.
 void backward_conv(hp_net* N, int l, float* f32 = nullptr) {
     weight_gradient(N, l);
     if (l == 0) return;
-    conv_backward_data(N, l, f32);
-    if (l == 4 || l == 2) return;
+    const bool pooled = l == 4 || l == 2;
+    const int q = pooled ? N->cur : next_gradient(N);
+    conv_backward_data(N, l, pooled ? nullptr : N->gbuf[q], f32);
+    if (pooled) return;
     const int64_t nv = N->lv[level_of_conv(l - 1)].nv;
     const unsigned rows = nblk(nv, kSumVox);
     const int c = COUT[l - 1];
@@ -1288,15 +1322,16 @@ void backward_conv(hp_net* N, int l, float* f32 = nullptr) {
         default: hipLaunchKernelGGL(k_channel_sums<64>, dim3(rows), dim3(256), 0, N->stream, N->gfull, nv, N->cpart); break;
     }
     column_sums(N, (int)rows, c, 0, c, N->grad + N->boff[l - 1]);
-    std::swap(N->gpre, N->gnext);
+    N->cur = q;
 }
 
-// Masked gradient of the skip activation of layer l (1 or 3) into gpre, and its bias gradient.
+// Masked gradient of the skip activation of layer l (1 or 3), now the current one, and its bias gradient.
 void backward_skip(hp_net* N, int l, const float* g, const float* gpool) {
     const Level& L = N->lv[level_of_conv(l)];
     const unsigned rows = nblk(L.nv, kSumVox);
     auto kernel = l == 1 ? k_relu_bwd_pool<16> : k_relu_bwd_pool<32>;
-    hipLaunchKernelGGL(kernel, dim3(rows), dim3(256), 0, N->stream, g, gpool, N->act[l], N->gpre, L.nx, L.ny, L.nv,
+    N->cur = next_gradient(N);
+    hipLaunchKernelGGL(kernel, dim3(rows), dim3(256), 0, N->stream, g, gpool, N->act[l], N->gbuf[N->cur], L.nx, L.ny, L.nv,
                        N->cpart);
     column_sums(N, (int)rows, COUT[l], 0, COUT[l], N->grad + N->boff[l]);
 }
@@ -1320,6 +1355,14 @@ void hp_nn_free(hp_net* N) {
     if (!N) return;
     if (N->stream) (void)hipStreamSynchronize(N->stream);
     else (void)hipDeviceSynchronize();
+    for (hipStream_t t : N->side)
+        if (t) {
+            (void)hipStreamSynchronize(t);
+            (void)hipStreamDestroy(t);
+        }
+    if (N->ready) (void)hipEventDestroy(N->ready);
+    for (hipEvent_t e : N->read)
+        if (e) (void)hipEventDestroy(e);
     for (void* p : N->allocs) (void)hipFree(p);
     delete N;
 }
@@ -1372,7 +1415,16 @@ int hp_nn_create(int nx, int ny, int nz, int training, hp_net** out) {
             (rc = nalloc(N, &N->v, N->nparam)) || (rc = nalloc(N, &N->t, V)) || (rc = nalloc(N, &N->gy, V)))
             return bail(rc);
         const int64_t most = std::max(V * 16, N->lv[1].nv * 32);
-        if ((rc = nalloc(N, &N->gpre, most)) || (rc = nalloc(N, &N->gnext, most)) || (rc = nalloc(N, &N->gfull, most)) ||
+        N->beside = V >= kBesideVoxels;
+        for (int q = 0; q < (N->beside ? kGradBufs : 2); ++q)
+            if ((rc = nalloc(N, &N->gbuf[q], most))) return bail(rc);
+        if (N->beside) {
+            bool made = hipEventCreateWithFlags(&N->ready, hipEventDisableTiming) == hipSuccess;
+            for (hipStream_t& t : N->side) made = made && hipStreamCreateWithFlags(&t, hipStreamNonBlocking) == hipSuccess;
+            for (hipEvent_t& e : N->read) made = made && hipEventCreateWithFlags(&e, hipEventDisableTiming) == hipSuccess;
+            if (!made) return bail(nfail(HP_EHIP, "stream or event creation failed"));
+        }
+        if ((rc = nalloc(N, &N->gfull, most)) ||
             (rc = nalloc(N, &N->gskip0, V * 16)) || (rc = nalloc(N, &N->gskip1, N->lv[1].nv * 32)) ||
             (rc = nalloc(N, &N->gp1, N->lv[1].nv * 16)) || (rc = nalloc(N, &N->gp2, N->lv[2].nv * 32)))
             return bail(rc);
@@ -1382,7 +1434,8 @@ int hp_nn_create(int nx, int ny, int nz, int training, hp_net** out) {
         N->cpart_cap = (int64_t)nblk(V, kHeadVox) * kHeadCols;
         for (int l = 0; l < NCONV; ++l)
             N->cpart_cap = std::max(N->cpart_cap, (int64_t)nblk(N->lv[level_of_conv(l)].nv, kSumVox) * COUT[l]);
-        if ((rc = nalloc(N, &N->wpart, N->wpart_cap)) || (rc = nalloc(N, &N->cpart, N->cpart_cap)))
+        if ((rc = nalloc(N, &N->wpart[0], N->wpart_cap)) || (N->beside && (rc = nalloc(N, &N->wpart[1], N->wpart_cap))) ||
+            (rc = nalloc(N, &N->cpart, N->cpart_cap)))
             return bail(rc);
         hipLaunchKernelGGL(k_zero_f32, dim3(nblk(N->nparam)), dim3(256), 0, 0, N->m, N->nparam);
         hipLaunchKernelGGL(k_zero_f32, dim3(nblk(N->nparam)), dim3(256), 0, 0, N->v, N->nparam);
@@ -1490,10 +1543,12 @@ int hp_nn_forward_raw(hp_net* N, const unsigned short* in, float* y) {
 
 // backward pass from the output gradient in gy (FP32, network units) to the parameter gradient
 int backward_net(hp_net* N) {
+    N->cur = 0;
+    for (bool& r : N->reading) r = false;
     const int64_t V = N->lv[0].nv;
     // head, and the masked gradient of the last layer's output
     const unsigned rows = nblk(V, kHeadVox);
-    hipLaunchKernelGGL(k_head_bwd, dim3(rows), dim3(256), 0, N->stream, N->gy, N->act[9], N->theta + N->hoff, N->gpre,
+    hipLaunchKernelGGL(k_head_bwd, dim3(rows), dim3(256), 0, N->stream, N->gy, N->act[9], N->theta + N->hoff, N->gbuf[0],
                        V, N->cpart);
     column_sums(N, (int)rows, kHeadCols, 0, HEAD + 1, N->grad + N->hoff);
     column_sums(N, (int)rows, kHeadCols, HEAD + 1, HEAD, N->grad + N->boff[9]);
@@ -1510,6 +1565,10 @@ int backward_net(hp_net* N) {
     backward_skip(N, 1, N->gskip0, N->gp1);
     backward_conv(N, 1);
     backward_conv(N, 0);
+    // what follows stands behind the weight gradients, too
+    for (hipStream_t t : N->side)
+        if (N->beside && (hipEventRecord(N->ready, t) != hipSuccess || hipStreamWaitEvent(N->stream, N->ready, 0) != hipSuccess))
+            return nfail(HP_EHIP, "event wait failed");
     return check();
 }
 
