@@ -19,9 +19,9 @@
 // velocity is zero and the interface pressure is the cell's own; an axis of one cell has no
 // gradient or divergence. The interface value of rho kappa_c is the mean of its two cells.
 //
-// Both passes walk z columns over natural-order FP64 arrays (HBM-bound, about 1 flop per byte):
-// workgroups of 64 columns in x and a few rows in y so that x neighbours come from the same cache lines and
-// y neighbours from rows the workgroup itself loads; the z neighbours stay in registers.
+// The passes walk z over natural-order FP64 arrays (HBM-bound, about 1 flop per byte) in tiles of 32 x 8
+// columns, one thread each: a plane of the tile and its halo goes through LDS, so that a cell's values and what
+// depends on them alone are loaded and computed once; the z neighbours stay in registers.
 #include "hp.h"
 #include "hp_internal.h"
 
@@ -63,156 +63,217 @@ struct RhsArgs {
     double* b;
 };
 
-// z planes per chunk of a column pass with `tiles` column tiles per plane and `threads` threads per
+// z planes per chunk of a pass with `tiles` column tiles per plane and `threads` threads per
 // workgroup: up to 32, fewer (not under 2) where the launch would leave the 256 CUs short of 2048
 // threads each. A chunk loads its first planes' z neighbours again, so longer ones read less; at
-// 48 x 32 x 44 chunks of 2 against 4 planes took the update from 10.1 to 7.0 us, at 96 x 80 x 72
-// (16 before) from 39.6 to 19.8, and single planes made the advection there slower (25 for 22).
+// 96 x 80 x 72 chunks of 16, 2 (this rule) and 1 planes took 28, 20 and 24 us for the right-hand side with every
+// term, 26, 17 and 18 for the update, and 34, 22 and 26 for the advection.
 static int hydro_chunk(int nz, int64_t tiles, int threads) {
     const int64_t want = (int64_t)256 * 2048 / threads;   // workgroups that fill the GPU once
     const int64_t kz = nz * tiles / want;
     return (int)(kz < 2 ? 2 : kz > 32 ? 32 : kz);
 }
 
-constexpr int kHRows = 4;  // rows of a column tile
+// the cell that stands at coordinate q along axis d, up to a few past either end: wrapped on a
+// periodic axis, the edge cell repeated beyond a closed boundary (a zero-gradient mirror for the
+// reconstruction; behind a face that doesn't exist nothing is used)
+__device__ __forceinline__ int reach(const HGeo& g, int d, int q) {
+    const int n = g.n[d];
+    if (g.per[d]) return ((q % n) + n) % n;
+    return q < 0 ? 0 : (q >= n ? n - 1 : q);
+}
 
-// Column tile (64 x kHRows columns, one chunk of kz planes) of this workgroup of a 1-D grid. The
-// hardware hands workgroup L to XCD L % 8; numbering the tiles so that each XCD takes one
-// contiguous range of them (whole x-y planes of chunks) keeps the y neighbour rows of a tile in
-// the L2 of the XCD that reads them.
+// Column tiles: 32 x 8 columns (whole 256-byte lines in x, and the fewest halo cells that leaves), chunks of kz
+// planes, one thread per column. The hardware hands workgroup L to XCD L % 8; the tiles are numbered so that
+// each XCD takes one contiguous range of them (whole x-y planes of chunks), which keeps the halo rows
+// of a tile in the L2 of the XCD that reads them.
 struct HTiles {
     int tx, ty, tz, kz;
 };
-
-__device__ __forceinline__ void htile(const HTiles& t, int& i, int& j, int& k0) {
-    const unsigned total = (unsigned)t.tx * t.ty * t.tz;
-    unsigned L = blockIdx.x;
-    if ((total & 7u) == 0) L = (L & 7u) * (total >> 3) + (L >> 3);
-    i = (int)(L % (unsigned)t.tx) * 64 + (threadIdx.x & 63);
-    j = (int)((L / (unsigned)t.tx) % (unsigned)t.ty) * kHRows + (threadIdx.x >> 6);
-    k0 = (int)(L / ((unsigned)t.tx * t.ty)) * t.kz;
-}
+constexpr int kTileX = 32, kTileY = 8, kTileThreads = kTileX * kTileY;
 
 static HTiles htiles(const int n[3]) {
-    const int tx = (n[0] + 63) / 64, ty = (n[1] + kHRows - 1) / kHRows;
-    const int kz = hydro_chunk(n[2], (int64_t)tx * ty, 64 * kHRows);
+    const int tx = (n[0] + kTileX - 1) / kTileX, ty = (n[1] + kTileY - 1) / kTileY;
+    const int kz = hydro_chunk(n[2], (int64_t)tx * ty, kTileThreads);
     return HTiles{tx, ty, (n[2] + kz - 1) / kz, kz};
 }
 
-// Neighbours of the cells of one axis, as the three values (low neighbour, cell, high neighbour)
-// of each array, and whether the two faces exist.
-struct Line {
-    bool lo, hi;
-    double p[3], rn[3], r1[3], ms[3], c[3], k[3];
+// A thread's place in its tile with a halo of H cells, and the halo cell that it brings. Positions past the end of
+// an axis hold what its last cells see there (their halo); nothing past those is read by a cell of the grid.
+template <int H>
+struct Place {
+    static constexpr int PX = kTileX + 2 * H, PY = kTileY + 2 * H;
+    static_assert(2 * H * (kTileX + kTileY) <= kTileThreads, "one halo cell per thread");
+    int i, j, k0, k1;
+    int own, hcell;     // columns of the plane: the thread's, its halo cell's
+    int at, hat;        // their places in the tile
+    bool halo, beside;  // it brings a halo cell; one left or right of the tile (else below or above)
+    bool inside, xl, xh, yl, yh;  // the column is one of the grid's; its faces exist
+    __device__ __forceinline__ Place(const HGeo& g, const HTiles& t) {
+        const unsigned total = (unsigned)t.tx * t.ty * t.tz;
+        unsigned L = blockIdx.x;
+        if ((total & 7u) == 0) L = (L & 7u) * (total >> 3) + (L >> 3);
+        const int x0 = (int)(L % (unsigned)t.tx) * kTileX, y0 = (int)((L / (unsigned)t.tx) % (unsigned)t.ty) * kTileY;
+        k0 = (int)(L / ((unsigned)t.tx * t.ty)) * t.kz;
+        k1 = min(k0 + t.kz, g.n[2]);
+        const int tid = threadIdx.x, lx = tid % kTileX, ly = tid / kTileX, nx = g.n[0], ny = g.n[1];
+        i = x0 + lx;
+        j = y0 + ly;
+        auto colx = [&](int q) { return reach(g, 0, min(q, nx + H - 1)); };
+        auto coly = [&](int q) { return reach(g, 1, min(q, ny + H - 1)); };
+        own = colx(i) + nx * coly(j);
+        int hx = 0, hy = 0;
+        beside = tid >= 2 * H * kTileX;
+        halo = tid < 2 * H * (kTileX + kTileY);
+        if (!beside) {
+            const int r = tid / kTileX;
+            hx = lx;
+            hy = r < H ? r - H : kTileY + r - H;
+        } else if (halo) {
+            const int q = tid - 2 * H * kTileX, c = q % (2 * H);
+            hx = c < H ? c - H : kTileX + c - H;
+            hy = q / (2 * H);
+        }
+        hcell = colx(x0 + hx) + nx * coly(y0 + hy);
+        hat = (hy + H) * PX + hx + H;
+        at = (ly + H) * PX + lx + H;
+        inside = i < nx && j < ny;
+        xl = g.per[0] || i > 0;
+        xh = g.per[0] || i < nx - 1;
+        yl = g.per[1] || j > 0;
+        yh = g.per[1] || j < ny - 1;
+    }
 };
 
-// The contributions of one axis to the rhs (steps (iv)-(v)): u_d (grad P^n)_d, (div u*)_d and the
-// d-part of div(rho kappa_c grad c); ih = 1/h_d.
-__device__ __forceinline__ void rhs_axis(const Line& L, double ud, double ih, bool tc, double& adv, double& divu,
-                                         double& dc) {
-    const double phi = L.hi ? pbnd(L.p[1], L.rn[1], L.p[2], L.rn[2]) : L.p[1];
-    const double plo = L.lo ? pbnd(L.p[0], L.rn[0], L.p[1], L.rn[1]) : L.p[1];
-    adv += ud * ((phi - plo) * ih);
-    const double uhi = L.hi ? (L.ms[1] + L.ms[2]) / (L.r1[1] + L.r1[2]) : 0.0;
-    const double ulo = L.lo ? (L.ms[0] + L.ms[1]) / (L.r1[0] + L.r1[1]) : 0.0;
-    divu += (uhi - ulo) * ih;
-    if (tc) {
-        const double fhi = L.hi ? 0.5 * (L.k[1] + L.k[2]) * (L.c[2] - L.c[1]) * ih : 0.0;
-        const double flo = L.lo ? 0.5 * (L.k[0] + L.k[1]) * (L.c[1] - L.c[0]) * ih : 0.0;
-        dc += (fhi - flo) * ih;
-    }
+// What a cell of the rhs reads at its neighbours, one value of it per array; of the momentum mom_star the
+// component of the axis at hand.
+struct RhsCell {
+    double p, rn, r1, ms, c, k;
+};
+
+// A face between cells a and b: the pressure there, the interface velocity and the flux of the two-component term.
+// Where there is none: the cell's own pressure, zero.
+struct RhsFace {
+    double p, u, f;
+};
+template <bool TC>
+__device__ __forceinline__ RhsFace rhs_face(bool face, const RhsCell& a, const RhsCell& b, double own, double ih) {
+    return {face ? pbnd(a.p, a.rn, b.p, b.rn) : own, face ? (a.ms + b.ms) / (a.r1 + b.r1) : 0.0,
+            TC && face ? 0.5 * (a.k + b.k) * (b.c - a.c) * ih : 0.0};
 }
 
-// x or y neighbour line of cell a (coordinate c along axis d, stride st): the neighbours from
-// memory, the cell itself from the z ring Z; ms is the momentum component of axis d
-__device__ __forceinline__ void load_line(const HGeo& g, const RhsArgs& A, const double* ms, int d, int c, int64_t a,
-                                          int64_t st, bool tc, const Line& Z, Line& L) {
-    int tl, th;
-    L.lo = neighbour(g, d, c, -1, &tl);
-    L.hi = neighbour(g, d, c, 1, &th);
-    const int64_t bl = L.lo ? a + (int64_t)(tl - c) * st : a, bh = L.hi ? a + (int64_t)(th - c) * st : a;
-    L.p[1] = Z.p[1];
-    L.rn[1] = Z.rn[1];
-    L.r1[1] = Z.r1[1];
-    L.ms[1] = ms[a];
-    L.c[1] = Z.c[1];
-    L.k[1] = Z.k[1];
-    const int64_t idx[2] = {bl, bh};
-#pragma unroll
-    for (int e = 0; e < 2; ++e) {
-        const int q = 2 * e;
-        L.p[q] = A.p_n[idx[e]];
-        L.rn[q] = A.rho_n[idx[e]];
-        L.r1[q] = A.rho_np1[idx[e]];
-        L.ms[q] = ms[idx[e]];
-        L.c[q] = tc ? A.conc_n[idx[e]] : 0.0;
-        L.k[q] = tc ? A.rkc_n[idx[e]] : 0.0;
-    }
-}
-
-// One thread per (x, y) column walking kz planes: the x and y neighbours come from memory (the
-// x ones from the same cache lines), the z neighbours of the six stencil arrays from a ring of
-// registers (each plane is loaded once per column). Every load of a plane is issued whatever the
-// geometry (a missing neighbour, or an axis of one cell, reads the cell itself and contributes
-// nothing): with loads under branches the compiler cannot count what is in flight and waited
-// for the next plane's z loads before using this plane's values.
+// The right-hand side by tiles (see k_advect): the arrays with neighbours in x and y go through LDS with one cell of
+// halo, the next plane's own values and the halo are loaded a plane ahead, and the low z face of a cell is
+// the high one of the plane before. Bound by memory: 375 us at 256^3 for 80 B read and 8 written per cell;
+// 414 us with every neighbour from memory, the planes of 8 workgroups per CU thrashing the L2.
 // TC: the two-component terms (temp_n, conc_n, rkc_n given); VISC: the viscous term (visc given).
 template <bool TC, bool VISC>
-__global__ __launch_bounds__(64 * kHRows) void k_pressure_rhs(HGeo g, HTiles t, RhsArgs A) {
-    int i, j, k0;
-    htile(t, i, j, k0);
-    if (i >= g.n[0] || j >= g.n[1]) return;
+__global__ __launch_bounds__(kTileThreads) void k_pressure_rhs(HGeo g, HTiles t, RhsArgs A) {
+    using P = Place<1>;
+    constexpr int NA = TC ? 7 : 5;  // p, rho_n, rho_np1, mom_star x and y, conc, rkc
+    __shared__ double tile[2][NA][P::PY * P::PX];
+    const P o(g, t);
     const int nz = g.n[2];
-    const int k1 = min(k0 + t.kz, nz);
     const int64_t sxy = (int64_t)g.n[0] * g.n[1];
-    constexpr bool tc = TC;
     const double ih[3] = {1.0 / g.h[0], 1.0 / g.h[1], 1.0 / g.h[2]};
-    const double* msz = A.mom_star + 2 * A.N;
-    const int64_t col = cell(g, i, j, 0);
-    // ring: z line values of planes k-1, k, k+1 (position 0, 1, 2)
-    Line Z;
-    auto load_plane = [&](int kp, int q) {
-        const int64_t a = col + (int64_t)kp * sxy;
-        Z.p[q] = A.p_n[a];
-        Z.rn[q] = A.rho_n[a];
-        Z.r1[q] = A.rho_np1[a];
-        Z.ms[q] = msz[a];
-        Z.c[q] = tc ? A.conc_n[a] : 0.0;
-        Z.k[q] = tc ? A.rkc_n[a] : 0.0;
+    struct Own {
+        double p, rn, r1, m[3], c, k;  // m: mom_star
+        double mn[3], c2, visc, temp;
     };
-    int tz = k0;
-    load_plane(neighbour(g, 2, k0, -1, &tz) ? tz : k0, 0);
-    load_plane(k0, 1);
-    for (int k = k0; k < k1; ++k) {
-        Z.lo = nz > 1 && neighbour(g, 2, k, -1, &tz);
-        tz = k;
-        Z.hi = nz > 1 && neighbour(g, 2, k, 1, &tz);
-        load_plane(tz, 2);
-        const int64_t a = col + (int64_t)k * sxy;
-        const double irn = 1.0 / Z.rn[1];
-        const double m = irn / A.c2_n[a];
-        double adv = 0.0, divu = 0.0, dc = 0.0;
-        // (an axis of one cell has no faces: its lines contribute exact zeros)
-        Line L;
-        load_line(g, A, A.mom_star, 0, i, a, 1, tc, Z, L);
-        rhs_axis(L, A.mom_n[a] * irn, ih[0], tc, adv, divu, dc);
-        load_line(g, A, A.mom_star + A.N, 1, j, a, g.n[0], tc, Z, L);
-        rhs_axis(L, A.mom_n[A.N + a] * irn, ih[1], tc, adv, divu, dc);
-        rhs_axis(Z, A.mom_n[2 * A.N + a] * irn, ih[2], tc, adv, divu, dc);
-        double b = m * (Z.p[1] - g.dt * adv) - g.dt * divu;
-        if constexpr (VISC) b -= (2.0 * g.dt / 3.0) * (m * irn) * A.visc[a];
-        if (tc) b -= (3.0 * g.dt / 4.0) * m * A.r_gas * A.temp_n[a] * dc;
-        A.b[a] = b;
-        // the ring moves up one plane
+    auto load = [&](Own& v, int k) {
+        const int64_t a = o.own + (int64_t)reach(g, 2, k) * sxy;
+        v.p = A.p_n[a];
+        v.rn = A.rho_n[a];
+        v.r1 = A.rho_np1[a];
 #pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            Z.p[q] = Z.p[q + 1];
-            Z.rn[q] = Z.rn[q + 1];
-            Z.r1[q] = Z.r1[q + 1];
-            Z.ms[q] = Z.ms[q + 1];
-            Z.c[q] = Z.c[q + 1];
-            Z.k[q] = Z.k[q + 1];
+        for (int d = 0; d < 3; ++d) {
+            v.m[d] = A.mom_star[(int64_t)d * A.N + a];
+            v.mn[d] = A.mom_n[(int64_t)d * A.N + a];
         }
+        v.c2 = A.c2_n[a];
+        if (TC) {
+            v.c = A.conc_n[a];
+            v.k = A.rkc_n[a];
+            v.temp = A.temp_n[a];
+        }
+        if (VISC) v.visc = A.visc[a];
+    };
+    RhsCell h;
+    auto load_halo = [&](int k) {
+        const int64_t a = o.hcell + (int64_t)k * sxy;
+        h.p = A.p_n[a];
+        h.rn = A.rho_n[a];
+        h.r1 = A.rho_np1[a];
+        h.ms = A.mom_star[(o.beside ? 0 : A.N) + a];
+        if (TC) {
+            h.c = A.conc_n[a];
+            h.k = A.rkc_n[a];
+        }
+    };
+    auto along = [&](const Own& v, int d) { return RhsCell{v.p, v.rn, v.r1, v.m[d], TC ? v.c : 0.0, TC ? v.k : 0.0}; };
+    Own q0, q1, q2;
+    load(q2, o.k0 - 1);
+    load(q0, o.k0);
+    load(q1, o.k0 + 1);
+    if (o.halo) load_halo(o.k0);
+    RhsFace zlo = rhs_face<TC>(nz > 1 && (g.per[2] || o.k0 > 0), along(q2, 2), along(q0, 2), q0.p, ih[2]);
+    // one plane from v, its own values, and w, the next one's; x then takes plane k + 2
+    auto plane = [&](int k, const Own& v, const Own& w, Own& x) {
+        double(*s)[P::PY * P::PX] = tile[k & 1];
+        const RhsCell mine = along(v, 0);
+        s[0][o.at] = v.p;
+        s[1][o.at] = v.rn;
+        s[2][o.at] = v.r1;
+        s[3][o.at] = v.m[0];
+        s[4][o.at] = v.m[1];
+        if (TC) {
+            s[NA - 2][o.at] = v.c;
+            s[NA - 1][o.at] = v.k;
+        }
+        if (o.halo) {
+            s[0][o.hat] = h.p;
+            s[1][o.hat] = h.rn;
+            s[2][o.hat] = h.r1;
+            s[o.beside ? 3 : 4][o.hat] = h.ms;
+            if (TC) {
+                s[NA - 2][o.hat] = h.c;
+                s[NA - 1][o.hat] = h.k;
+            }
+        }
+        __syncthreads();  // (the other slot's readers passed the previous plane's barrier)
+        load(x, k + 2);
+        if (o.halo) load_halo(min(k + 1, o.k1 - 1));
+        auto cell_at = [&](int d, int off) {
+            const int q = o.at + off;
+            return RhsCell{s[0][q], s[1][q], s[2][q], s[3 + d][q], TC ? s[NA - 2][q] : 0.0, TC ? s[NA - 1][q] : 0.0};
+        };
+        const double irn = 1.0 / v.rn;
+        const double m = irn / v.c2;
+        double adv = 0.0, divu = 0.0, dc = 0.0;
+        auto axis = [&](const RhsFace& lo, const RhsFace& hi, int d) {
+            adv += (v.mn[d] * irn) * ((hi.p - lo.p) * ih[d]);
+            divu += (hi.u - lo.u) * ih[d];
+            if (TC) dc += (hi.f - lo.f) * ih[d];
+        };
+        // (an axis of one cell has no faces: its lines contribute exact zeros)
+        axis(rhs_face<TC>(o.xl, cell_at(0, -1), mine, v.p, ih[0]), rhs_face<TC>(o.xh, mine, cell_at(0, 1), v.p, ih[0]), 0);
+        const RhsCell my = along(v, 1);
+        axis(rhs_face<TC>(o.yl, cell_at(1, -P::PX), my, v.p, ih[1]), rhs_face<TC>(o.yh, my, cell_at(1, P::PX), v.p, ih[1]), 1);
+        const RhsFace zhi = rhs_face<TC>(nz > 1 && (g.per[2] || k < nz - 1), along(v, 2), along(w, 2), v.p, ih[2]);
+        axis(zlo, zhi, 2);
+        zlo = zhi;
+        double b = m * (v.p - g.dt * adv) - g.dt * divu;
+        if constexpr (VISC) b -= (2.0 * g.dt / 3.0) * (m * irn) * v.visc;
+        if (TC) b -= (3.0 * g.dt / 4.0) * m * A.r_gas * v.temp * dc;
+        if (o.inside) A.b[o.own + (int64_t)k * sxy] = b;
+    };
+    for (int k = o.k0; k < o.k1;) {
+        plane(k, q0, q1, q2);
+        if (++k == o.k1) break;
+        plane(k, q1, q2, q0);
+        if (++k == o.k1) break;
+        plane(k, q2, q0, q1);
+        ++k;
     }
 }
 
@@ -222,91 +283,108 @@ struct UpdArgs {
     int64_t N;
 };
 
-// The updates of one axis (steps (vii)-(viii)): grad P with rho^{n+1}, the high interface
-// velocity u^{n+1} (returned through uf) and the axis' part of its divergence
-__device__ __forceinline__ double upd_axis(bool lo, bool hi, const double* p, const double* r, const double* ms,
-                                           double dt, double ih, double& uf, double& divn) {
-    const double phi = hi ? pbnd(p[1], r[1], p[2], r[2]) : p[1];
-    const double plo = lo ? pbnd(p[0], r[0], p[1], r[1]) : p[1];
-    uf = hi ? (ms[1] + ms[2]) / (r[1] + r[2]) - dt * (p[2] - p[1]) * ih * 2.0 / (r[2] + r[1]) : 0.0;
-    const double ul = lo ? (ms[0] + ms[1]) / (r[0] + r[1]) - dt * (p[1] - p[0]) * ih * 2.0 / (r[1] + r[0]) : 0.0;
-    divn += (uf - ul) * ih;
-    return (phi - plo) * ih;
+// What a cell of the update reads at its neighbours; of the momentum the component of the axis at hand.
+struct UpdCell {
+    double p, r, ms;
+};
+
+// A face between cells a and b (steps (vii)-(viii)): the pressure there with rho^{n+1}, and the interface
+// velocity u^{n+1}. Where there is none: the cell's own pressure, zero.
+struct UpdFace {
+    double p, u;
+};
+__device__ __forceinline__ UpdFace upd_face(bool face, const UpdCell& a, const UpdCell& b, double own, double dt, double ih) {
+    return {face ? pbnd(a.p, a.r, b.p, b.r) : own,
+            face ? (a.ms + b.ms) / (a.r + b.r) - dt * (b.p - a.p) * ih * 2.0 / (b.r + a.r) : 0.0};
 }
 
-__global__ __launch_bounds__(64 * kHRows) void k_pressure_update(HGeo g, HTiles t, UpdArgs A) {
-    int i, j, k0;
-    htile(t, i, j, k0);
-    if (i >= g.n[0] || j >= g.n[1]) return;
+// The updates after the solve by tiles, as in k_pressure_rhs. Bound by memory: 396 us at 256^3 for 48 B read and 56
+// written per cell; 472 us with every neighbour from memory.
+__global__ __launch_bounds__(kTileThreads) void k_pressure_update(HGeo g, HTiles t, UpdArgs A) {
+    using P = Place<1>;
+    __shared__ double tile[2][4][P::PY * P::PX];  // p, rho, mom_star x and y
+    const P o(g, t);
     const int nz = g.n[2];
-    const int k1 = min(k0 + t.kz, nz);
     const int64_t sxy = (int64_t)g.n[0] * g.n[1];
     const double ih[3] = {1.0 / g.h[0], 1.0 / g.h[1], 1.0 / g.h[2]};
-    const double* msz = A.mom_star + 2 * A.N;
-    const int64_t col = cell(g, i, j, 0);
-    double zp[3] = {0.0, 0.0, 0.0}, zr[3] = {1.0, 1.0, 1.0}, zm[3] = {0.0, 0.0, 0.0};
-    auto load_plane = [&](int kp, int q) {
-        const int64_t a = col + (int64_t)kp * sxy;
-        zp[q] = A.p[a];
-        zr[q] = A.rho_np1[a];
-        zm[q] = msz[a];
+    struct Own {
+        double p, r, m[3], e;
     };
-    // (unconditional loads, as in k_pressure_rhs: an axis of one cell has no faces and its
-    // terms are exact zeros)
-    int tz = k0;
-    load_plane(neighbour(g, 2, k0, -1, &tz) ? tz : k0, 0);
-    load_plane(k0, 1);
-    for (int k = k0; k < k1; ++k) {
-        const bool zlo = nz > 1 && neighbour(g, 2, k, -1, &tz);
-        tz = k;
-        const bool zhi = nz > 1 && neighbour(g, 2, k, 1, &tz);
-        load_plane(tz, 2);
-        const int64_t a = col + (int64_t)k * sxy;
-        const int c[2] = {i, j};
-        const int64_t st[2] = {1, g.n[0]};
-        double gp[3] = {0.0, 0.0, 0.0}, uf[3] = {0.0, 0.0, 0.0}, divn = 0.0;
+    auto load = [&](Own& v, int k) {
+        const int64_t a = o.own + (int64_t)reach(g, 2, k) * sxy;
+        v.p = A.p[a];
+        v.r = A.rho_np1[a];
 #pragma unroll
-        for (int d = 0; d < 2; ++d) {
-            int tl, th;
-            const bool lo = neighbour(g, d, c[d], -1, &tl), hi = neighbour(g, d, c[d], 1, &th);
-            const int64_t bl = lo ? a + (int64_t)(tl - c[d]) * st[d] : a;
-            const int64_t bh = hi ? a + (int64_t)(th - c[d]) * st[d] : a;
-            const double* ms = A.mom_star + (int64_t)d * A.N;
-            const double pv[3] = {A.p[bl], zp[1], A.p[bh]};
-            const double rv[3] = {A.rho_np1[bl], zr[1], A.rho_np1[bh]};
-            const double mv[3] = {ms[bl], ms[a], ms[bh]};
-            gp[d] = upd_axis(lo, hi, pv, rv, mv, g.dt, ih[d], uf[d], divn);
+        for (int d = 0; d < 3; ++d) v.m[d] = A.mom_star[(int64_t)d * A.N + a];
+        v.e = A.e_star[a];
+    };
+    UpdCell h;
+    auto load_halo = [&](int k) {
+        const int64_t a = o.hcell + (int64_t)k * sxy;
+        h = UpdCell{A.p[a], A.rho_np1[a], A.mom_star[(o.beside ? 0 : A.N) + a]};
+    };
+    auto along = [&](const Own& v, int d) { return UpdCell{v.p, v.r, v.m[d]}; };
+    Own q0, q1, q2;
+    load(q2, o.k0 - 1);
+    load(q0, o.k0);
+    load(q1, o.k0 + 1);
+    if (o.halo) load_halo(o.k0);
+    UpdFace zlo = upd_face(nz > 1 && (g.per[2] || o.k0 > 0), along(q2, 2), along(q0, 2), q0.p, g.dt, ih[2]);
+    auto plane = [&](int k, const Own& v, const Own& w, Own& x) {
+        double(*s)[P::PY * P::PX] = tile[k & 1];
+        s[0][o.at] = v.p;
+        s[1][o.at] = v.r;
+        s[2][o.at] = v.m[0];
+        s[3][o.at] = v.m[1];
+        if (o.halo) {
+            s[0][o.hat] = h.p;
+            s[1][o.hat] = h.r;
+            s[o.beside ? 2 : 3][o.hat] = h.ms;
         }
-        gp[2] = upd_axis(zlo, zhi, zp, zr, zm, g.dt, ih[2], uf[2], divn);
+        __syncthreads();  // (the other slot's readers passed the previous plane's barrier)
+        load(x, k + 2);
+        if (o.halo) load_halo(min(k + 1, o.k1 - 1));
+        auto cell_at = [&](int d, int off) { return UpdCell{s[0][o.at + off], s[1][o.at + off], s[2 + d][o.at + off]}; };
+        double gp[3], uf[3], divn = 0.0;
+        auto axis = [&](const UpdFace& lo, const UpdFace& hi, int d) {
+            uf[d] = hi.u;
+            divn += (hi.u - lo.u) * ih[d];
+            gp[d] = (hi.p - lo.p) * ih[d];
+        };
+        // (an axis of one cell has no faces and its terms are exact zeros)
+        const UpdCell mx = along(v, 0), my = along(v, 1);
+        axis(upd_face(o.xl, cell_at(0, -1), mx, v.p, g.dt, ih[0]), upd_face(o.xh, mx, cell_at(0, 1), v.p, g.dt, ih[0]), 0);
+        axis(upd_face(o.yl, cell_at(1, -P::PX), my, v.p, g.dt, ih[1]),
+             upd_face(o.yh, my, cell_at(1, P::PX), v.p, g.dt, ih[1]), 1);
+        const UpdFace zhi = upd_face(nz > 1 && (g.per[2] || k < nz - 1), along(v, 2), along(w, 2), v.p, g.dt, ih[2]);
+        axis(zlo, zhi, 2);
+        zlo = zhi;
         // step (vii): momentum; step (ix): e^{n+1} = e* - dt (P div u^{n+1} + u^{n+1} . grad P)
-        const double ir = 1.0 / zr[1];
+        const int64_t a = o.own + (int64_t)k * sxy;
+        const double ir = 1.0 / v.r;
         double ug = 0.0;
+#pragma unroll
         for (int d = 0; d < 3; ++d) {
-            const double md = A.mom_star[(int64_t)d * A.N + a] - g.dt * gp[d];
-            A.mom_out[(int64_t)d * A.N + a] = md;
-            A.uface_out[(int64_t)d * A.N + a] = uf[d];
+            const double md = v.m[d] - g.dt * gp[d];
+            if (o.inside) {
+                A.mom_out[(int64_t)d * A.N + a] = md;
+                A.uface_out[(int64_t)d * A.N + a] = uf[d];
+            }
             ug += (md * ir) * gp[d];
         }
-        A.e_out[a] = A.e_star[a] - g.dt * (zp[1] * divn + ug);
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            zp[q] = zp[q + 1];
-            zr[q] = zr[q + 1];
-            zm[q] = zm[q + 1];
-        }
+        if (o.inside) A.e_out[a] = v.e - g.dt * (v.p * divn + ug);
+    };
+    for (int k = o.k0; k < o.k1;) {
+        plane(k, q0, q1, q2);
+        if (++k == o.k1) break;
+        plane(k, q1, q2, q0);
+        if (++k == o.k1) break;
+        plane(k, q2, q0, q1);
+        ++k;
     }
 }
 
 // ---- the explicit advective part (steps (i)-(iii)) and the equation of state ----
-
-// the cell that stands at coordinate q along axis d, up to a few past either end: wrapped on a
-// periodic axis, the edge cell repeated beyond a closed boundary (a zero-gradient mirror for the
-// reconstruction)
-__device__ __forceinline__ int reach(const HGeo& g, int d, int q) {
-    const int n = g.n[d];
-    if (g.per[d]) return ((q % n) + n) % n;
-    return q < 0 ? 0 : (q >= n ? n - 1 : q);
-}
 
 // second-order ENO: the smaller in magnitude of the two one-sided differences (ties: the second)
 __device__ __forceinline__ double eno_slope(double dm, double dp) { return fabs(dm) < fabs(dp) ? dm : dp; }
@@ -339,15 +417,10 @@ struct AdvArgs {
     double* out[5];
 };
 
-// Column tiles of the advection: 32 x 8 columns (whole 256-byte lines in x, and the fewest halo cells
-// that leaves), chunks of kz planes.
-constexpr int kAdvX = 32, kAdvY = 8, kAdvThreads = kAdvX * kAdvY;
-static_assert(4 * kAdvX + 4 * kAdvY <= kAdvThreads, "one halo cell per thread");
-
 // q* = q - dt div(flux) for the five conserved fields (rho, three momenta, e), the fluxes through
 // the interfaces of every cell from eq. step1 and the upwind reconstruction.
 //
-// A workgroup walks a tile of columns through kz planes. Each plane of the tile goes through LDS
+// A workgroup walks its tile of columns through kz planes. Each plane of the tile goes through LDS
 // with two cells of halo on every side (own cells from registers, one halo cell per thread from
 // memory), so the eight x and y neighbours of a field cost one load; the z neighbours stay in a
 // ring of four planes, and the flux through a cell's low z interface is the one its lower
@@ -355,42 +428,14 @@ static_assert(4 * kAdvX + 4 * kAdvY <= kAdvThreads, "one halo cell per thread");
 // memory: 380 us at 256^3 for 1.4 GB read (the halo rows come from beyond the L2 as often as not)
 // and 0.67 GB written; one thread per cell, with every neighbour from memory and every flux
 // twice, took 1041 us. Tiles of 512 threads left one workgroup per CU (510 us) or spilled.
-__global__ __launch_bounds__(kAdvThreads, 3) void k_advect(HGeo g, HTiles t, AdvArgs A) {
-    constexpr int TX = kAdvX, TY = kAdvY, PX = TX + 4, PY = TY + 4;
+__global__ __launch_bounds__(kTileThreads, 3) void k_advect(HGeo g, HTiles t, AdvArgs A) {
+    constexpr int PX = Place<2>::PX, PY = Place<2>::PY;
     __shared__ double tile[2][5][PY * PX];
-    // each XCD takes one contiguous range of tiles (see htile)
-    const unsigned total = (unsigned)t.tx * t.ty * t.tz;
-    unsigned L = blockIdx.x;
-    if ((total & 7u) == 0) L = (L & 7u) * (total >> 3) + (L >> 3);
-    const int x0 = (int)(L % (unsigned)t.tx) * TX, y0 = (int)((L / (unsigned)t.tx) % (unsigned)t.ty) * TY;
-    const int k0 = (int)(L / ((unsigned)t.tx * t.ty)) * t.kz, k1 = min(k0 + t.kz, g.n[2]);
-    const int tid = threadIdx.x, lx = tid % TX, ly = tid / TX;
-    const int nx = g.n[0], ny = g.n[1], nz = g.n[2];
-    const int i = x0 + lx, j = y0 + ly;
-    // Positions past the end of an axis hold what its last cells see there (their halo); nothing
-    // past the second is read by a cell of the grid.
-    auto colx = [&](int q) { return reach(g, 0, min(q, nx + 1)); };
-    auto coly = [&](int q) { return reach(g, 1, min(q, ny + 1)); };
-    const int64_t sxy = (int64_t)nx * ny;
-    const int own = colx(i) + nx * coly(j);
-    // the thread's halo cell: two rows below and above the tile, two columns left and right
-    int hx = 0, hy = 0;
-    const bool halo = tid < 4 * TX + 4 * TY;
-    if (tid < 4 * TX) {
-        const int r = tid / TX;
-        hx = lx;
-        hy = r < 2 ? r - 2 : TY + r - 2;
-    } else if (halo) {
-        const int c = (tid - 4 * TX) & 3;
-        hx = c < 2 ? c - 2 : TX + c - 2;
-        hy = (tid - 4 * TX) >> 2;
-    }
-    const int hcell = colx(x0 + hx) + nx * coly(y0 + hy);
-    const int hat = (hy + 2) * PX + hx + 2, at = (ly + 2) * PX + lx + 2;
+    const Place<2> o(g, t);
+    const int k0 = o.k0, k1 = o.k1, own = o.own, at = o.at, hat = o.hat, hcell = o.hcell, nz = g.n[2];
+    const bool halo = o.halo, xl = o.xl, xh = o.xh, yl = o.yl, yh = o.yh, inside = o.inside;
+    const int64_t sxy = (int64_t)g.n[0] * g.n[1];
     const double ih[3] = {1.0 / g.h[0], 1.0 / g.h[1], 1.0 / g.h[2]};
-    const bool xl = g.per[0] || i > 0, xh = g.per[0] || i < nx - 1;
-    const bool yl = g.per[1] || j > 0, yh = g.per[1] || j < ny - 1;
-    const bool inside = i < nx && j < ny;
 
     double q0[5], q1[5], q2[5], q3[5], fz[5], hv[5];
     auto load = [&](double* v, int cell_, int k) {
@@ -486,10 +531,8 @@ int hydro_launch_advect(const int n[3], const int bc[3], const double h[3], doub
     g.dt = dt;
     const int64_t N = (int64_t)n[0] * n[1] * n[2];
     AdvArgs A{{rho, mom, mom + N, mom + 2 * N, e}, {rho_out, mom_out, mom_out + N, mom_out + 2 * N, e_out}};
-    HTiles t{(n[0] + kAdvX - 1) / kAdvX, (n[1] + kAdvY - 1) / kAdvY, 1, 1};
-    t.kz = hydro_chunk(n[2], (int64_t)t.tx * t.ty, kAdvThreads);
-    t.tz = (n[2] + t.kz - 1) / t.kz;
-    hipLaunchKernelGGL(k_advect, dim3((unsigned)((int64_t)t.tx * t.ty * t.tz)), dim3(kAdvThreads), 0, s, g, t, A);
+    const HTiles t = htiles(n);
+    hipLaunchKernelGGL(k_advect, dim3((unsigned)((int64_t)t.tx * t.ty * t.tz)), dim3(kTileThreads), 0, s, g, t, A);
     return hipGetLastError() == hipSuccess ? HP_OK : HP_EHIP;
 }
 
@@ -513,13 +556,13 @@ int hydro_launch_rhs(const int n[3], const int bc[3], const double h[3], double 
     const HTiles t = htiles(n);
     const dim3 grid((unsigned)t.tx * t.ty * t.tz);
     if (f->temp_n && f->visc)
-        hipLaunchKernelGGL((k_pressure_rhs<true, true>), grid, dim3(64 * kHRows), 0, s, g, t, A);
+        hipLaunchKernelGGL((k_pressure_rhs<true, true>), grid, dim3(kTileThreads), 0, s, g, t, A);
     else if (f->temp_n)
-        hipLaunchKernelGGL((k_pressure_rhs<true, false>), grid, dim3(64 * kHRows), 0, s, g, t, A);
+        hipLaunchKernelGGL((k_pressure_rhs<true, false>), grid, dim3(kTileThreads), 0, s, g, t, A);
     else if (f->visc)
-        hipLaunchKernelGGL((k_pressure_rhs<false, true>), grid, dim3(64 * kHRows), 0, s, g, t, A);
+        hipLaunchKernelGGL((k_pressure_rhs<false, true>), grid, dim3(kTileThreads), 0, s, g, t, A);
     else
-        hipLaunchKernelGGL((k_pressure_rhs<false, false>), grid, dim3(64 * kHRows), 0, s, g, t, A);
+        hipLaunchKernelGGL((k_pressure_rhs<false, false>), grid, dim3(kTileThreads), 0, s, g, t, A);
     return hipGetLastError() == hipSuccess ? HP_OK : HP_EHIP;
 }
 
@@ -535,7 +578,7 @@ int hydro_launch_update(const int n[3], const int bc[3], const double h[3], doub
     UpdArgs A{f->p, f->rho_np1, f->mom_star, f->e_star, f->mom_out, f->uface_out, f->e_out,
               (int64_t)n[0] * n[1] * n[2]};
     const HTiles t = htiles(n);
-    hipLaunchKernelGGL(k_pressure_update, dim3((unsigned)t.tx * t.ty * t.tz), dim3(64 * kHRows), 0, s, g, t, A);
+    hipLaunchKernelGGL(k_pressure_update, dim3((unsigned)t.tx * t.ty * t.tz), dim3(kTileThreads), 0, s, g, t, A);
     return hipGetLastError() == hipSuccess ? HP_OK : HP_EHIP;
 }
 
