@@ -734,102 +734,126 @@ __device__ __forceinline__ void stp(T* __restrict__ p, T v0, T v1) {
     *reinterpret_cast<V*>(p) = v;
 }
 
-// Operator apply over cell pairs: the same z march and face order as k_apply_zm, with half the
-// memory instructions (pair loads for the cell, its y and z neighbours, m and b; two scalar
-// loads for the outer x neighbours) and the pair's shared x face weighted once.
+// plane below / above k (the plane itself where a Neumann end has no face)
+__device__ __forceinline__ int kbelow(int k, int nz, int pz) { return k > 0 ? k - 1 : (pz ? nz - 1 : k); }
+__device__ __forceinline__ int kabove(int k, int nz, int pz) { return k < nz - 1 ? k + 1 : (pz ? 0 : k); }
+
+// Operator apply over cell pairs: the same face order as k_apply_zm, with half the memory instructions and the pair's
+// shared x face weighted once. A workgroup marches 128 x 4 columns up a z chunk: a plane's pairs of x and rho, the
+// rows beside the workgroup and its outer x neighbours go through LDS, the column's next planes form a
+// register ring that rotates by renaming (a move would wait for the load in flight). Bound by
+// memory: the residual takes 140 us at 256^3 (40 B per cell); 160 with every neighbour from memory.
 template <typename T, int MODE, int FR = 0>
-__global__ __launch_bounds__(kBlock) void k_apply_zp(Geo<T> g, ZTiles zt,
+__global__ __launch_bounds__(kBlock, 4) void k_apply_zp(Geo<T> g, ZTiles zt,
                                                      const T* __restrict__ rho,
                                                      const T* __restrict__ m,
                                                      const T* __restrict__ x,
                                                      const T* __restrict__ b, T* __restrict__ y,
                                                      double* __restrict__ partials) {
+    constexpr int kR = kBlock / 64;
+    __shared__ Pair<T> sx[2][2][kR + 2][64];  // [plane slot][x, rho][row][column]
+    __shared__ T se[2][2][kR][2];             // outer x neighbours: [slot][x, rho][row][side]
     int bx, by, bz;
     ztile(zt, bx, by, bz);
-    const int i0 = (bx * 64 + (threadIdx.x & 63)) * 2;
-    const int j = by * 4 + (threadIdx.x >> 6);
-    const int k0 = bz * zt.kz;
-    const int k1 = min(k0 + zt.kz, g.nz);
-    const int sz = g.nx * g.ny;
+    const int nx = g.nx, ny = g.ny, sz = nx * ny;
+    const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int iu = (bx * 64 + lane) * 2, j0 = by * kR;
+    const bool act = iu < nx && j0 + w < ny;
+    // a pair or row past the end holds what its last neighbour within sees there
+    const int i0 = iu < nx ? iu : (g.px && iu == nx ? 0 : nx - 2);
+    auto row = [&](int j) { return j < 0 ? (g.py ? ny - 1 : 0) : j < ny ? j : (g.py && j == ny ? 0 : ny - 1); };
+    const int j = row(j0 + w);
+    const int k0 = bz * zt.kz, k1 = min(k0 + zt.kz, g.nz);
+    const FaceTab<T> f0(g, i0, j), f1(g, i0 + 1, j);
+    const T cxl = f0.c[0], cxr = f1.c[1], cym = f0.c[2], cyp = f0.c[3];
+    const int col = i0 + nx * j;
+    // this thread's halo pair (a row beside the workgroup) and outer x neighbour (16 of them)
+    const int hside = tid >> 7, harr = (tid >> 6) & 1;
+    const T* const halo = (harr ? rho : x) + i0 + nx * row(hside ? j0 + kR : j0 - 1);
+    const int eside = tid & 1, earr = (tid >> 1) & 1, erow = (tid >> 2) & (kR - 1);
+    const int el = bx * 128 - 1, er = bx * 128 + 128;
+    const int ex = eside ? (er < nx ? er : g.px ? 0 : nx - 1) : (el >= 0 ? el : g.px ? nx - 1 : 0);
+    const T* const edge = (earr ? rho : x) + ex + nx * row(j0 + erow);
     double part = 0.0;
-    if (i0 < g.nx && j < g.ny) {
-        const FaceTab<T> f0(g, i0, j), f1(g, i0 + 1, j);
-        const int oxl = f0.o[0], oxr = 1 + f1.o[1];   // outer x neighbours, from the pair base
-        const T cxl = f0.c[0], cxr = f1.c[1];
-        const int oym = f0.o[2], oyp = f0.o[3];
-        const T cym = f0.c[2], cyp = f0.c[3];
-        const int col = i0 + g.nx * j;
-        int a = col + k0 * sz;
-        bool hm, hp;
-        const int om = zoff(k0, -1, g.nz, g.pz, sz, hm);
-        const int op = zoff(k0, 1, g.nz, g.pz, sz, hp);
-        Pair<T> xc = ldp(x + a), rc = ldp(rho + a);
-        const Pair<T> xm0 = ldp(x + a + om), rm0 = ldp(rho + a + om);
-        Pair<T> xm = xm0;
-        T wzm0 = hm ? g.cz * face_kappa<FR>(rc.v0, rm0.v0) : T(0);
-        T wzm1 = hm ? g.cz * face_kappa<FR>(rc.v1, rm0.v1) : T(0);
-        Pair<T> xn = ldp(x + a + op), rn = ldp(rho + a + op);
-        T czp = hp ? g.cz : T(0);
-        T xl = x[a + oxl], xr = x[a + oxr], rl = rho[a + oxl], rr = rho[a + oxr];
-        Pair<T> xym = ldp(x + a + oym), xyp = ldp(x + a + oyp);
-        Pair<T> rym = ldp(rho + a + oym), ryp = ldp(rho + a + oyp);
-        Pair<T> mv = ldp(m + a);
-        Pair<T> bv = {T(0), T(0)};
-        if (MODE >= 2) bv = ldp(b + a);
-        for (int k = k0; k < k1; ++k) {
-            // prefetch plane k+1 (clamped to the chunk) and the pair two planes up
-            const int kn = min(k + 1, k1 - 1);
-            const int an = col + kn * sz;
-            bool hpn;
-            const int opn = zoff(kn, 1, g.nz, g.pz, sz, hpn);
-            const T xln = x[an + oxl], xrn = x[an + oxr], rln = rho[an + oxl], rrn = rho[an + oxr];
-            const Pair<T> xymn = ldp(x + an + oym), xypn = ldp(x + an + oyp);
-            const Pair<T> rymn = ldp(rho + an + oym), rypn = ldp(rho + an + oyp);
-            const Pair<T> mvn = ldp(m + an);
-            Pair<T> bvn = {T(0), T(0)};
-            if (MODE >= 2) bvn = ldp(b + an);
-            const Pair<T> xnn = ldp(x + an + opn), rnn = ldp(rho + an + opn);
-            // plane k
-            const T wx = g.cx * face_kappa<FR>(rc.v0, rc.v1);
-            const T wzp0 = czp * face_kappa<FR>(rc.v0, rn.v0);
-            const T wzp1 = czp * face_kappa<FR>(rc.v1, rn.v1);
-            T acc0 = mv.v0 * xc.v0;
-            acc0 += cxl * face_kappa<FR>(rc.v0, rl) * (xc.v0 - xl);
-            acc0 += wx * (xc.v0 - xc.v1);
-            acc0 += cym * face_kappa<FR>(rc.v0, rym.v0) * (xc.v0 - xym.v0);
-            acc0 += cyp * face_kappa<FR>(rc.v0, ryp.v0) * (xc.v0 - xyp.v0);
-            acc0 += wzm0 * (xc.v0 - xm.v0);
-            acc0 += wzp0 * (xc.v0 - xn.v0);
-            T acc1 = mv.v1 * xc.v1;
-            acc1 += wx * (xc.v1 - xc.v0);
-            acc1 += cxr * face_kappa<FR>(rc.v1, rr) * (xc.v1 - xr);
-            acc1 += cym * face_kappa<FR>(rc.v1, rym.v1) * (xc.v1 - xym.v1);
-            acc1 += cyp * face_kappa<FR>(rc.v1, ryp.v1) * (xc.v1 - xyp.v1);
-            acc1 += wzm1 * (xc.v1 - xm.v1);
-            acc1 += wzp1 * (xc.v1 - xn.v1);
-            if (MODE >= 2) {
-                acc0 = bv.v0 - acc0;
-                acc1 = bv.v1 - acc1;
-            }
-            stp(y + a, acc0, acc1);
+    struct Own {
+        Pair<T> m, b, h;
+        T e;
+    };
+    auto load_own = [&](int k, Own& o) {
+        o.m = ldp(m + col + k * sz);
+        o.b = MODE >= 2 ? ldp(b + col + k * sz) : Pair<T>{T(0), T(0)};
+        o.h = ldp(halo + k * sz);
+        o.e = edge[k * sz];
+    };
+    auto step = [&](int k, const Pair<T>& xm, const Pair<T>& xc, const Pair<T>& xn, Pair<T>& xnn, const Pair<T>& rc,
+                    const Pair<T>& rn, Pair<T>& rnn, T& wzm0, T& wzm1, const Own& c, Own& nxt) {
+        // prefetch plane k+1 (clamped to the chunk) and the pair two planes up
+        const int kn = min(k + 1, k1 - 1);
+        load_own(kn, nxt);
+        const int up = col + kabove(kn, g.nz, g.pz) * sz;
+        xnn = ldp(x + up);
+        rnn = ldp(rho + up);
+        const int sl = k & 1;
+        sx[sl][0][w + 1][lane] = xc;
+        sx[sl][1][w + 1][lane] = rc;
+        sx[sl][harr][hside ? kR + 1 : 0][lane] = c.h;
+        if (tid < 4 * kR) se[sl][earr][erow][eside] = c.e;
+        __syncthreads();
+        const T xl = lane > 0 ? sx[sl][0][w + 1][lane - 1].v1 : se[sl][0][w][0];
+        const T rl = lane > 0 ? sx[sl][1][w + 1][lane - 1].v1 : se[sl][1][w][0];
+        T xr = lane < 63 ? sx[sl][0][w + 1][lane + 1].v0 : se[sl][0][w][1];
+        const T rr = lane < 63 ? sx[sl][1][w + 1][lane + 1].v0 : se[sl][1][w][1];
+        if (cxr == T(0)) xr = xc.v1;  // no face there: nothing but the cell itself counts
+        const Pair<T> xym = sx[sl][0][w][lane], xyp = sx[sl][0][w + 2][lane];
+        const Pair<T> rym = sx[sl][1][w][lane], ryp = sx[sl][1][w + 2][lane];
+        const T czp = (k < g.nz - 1 || g.pz) ? g.cz : T(0);
+        const T wx = g.cx * face_kappa<FR>(rc.v0, rc.v1);
+        const T wzp0 = czp * face_kappa<FR>(rc.v0, rn.v0);
+        const T wzp1 = czp * face_kappa<FR>(rc.v1, rn.v1);
+        T acc0 = c.m.v0 * xc.v0;
+        acc0 += cxl * face_kappa<FR>(rc.v0, rl) * (xc.v0 - xl);
+        acc0 += wx * (xc.v0 - xc.v1);
+        acc0 += cym * face_kappa<FR>(rc.v0, rym.v0) * (xc.v0 - xym.v0);
+        acc0 += cyp * face_kappa<FR>(rc.v0, ryp.v0) * (xc.v0 - xyp.v0);
+        acc0 += wzm0 * (xc.v0 - xm.v0);
+        acc0 += wzp0 * (xc.v0 - xn.v0);
+        T acc1 = c.m.v1 * xc.v1;
+        acc1 += wx * (xc.v1 - xc.v0);
+        acc1 += cxr * face_kappa<FR>(rc.v1, rr) * (xc.v1 - xr);
+        acc1 += cym * face_kappa<FR>(rc.v1, rym.v1) * (xc.v1 - xym.v1);
+        acc1 += cyp * face_kappa<FR>(rc.v1, ryp.v1) * (xc.v1 - xyp.v1);
+        acc1 += wzm1 * (xc.v1 - xm.v1);
+        acc1 += wzp1 * (xc.v1 - xn.v1);
+        if (MODE >= 2) {
+            acc0 = c.b.v0 - acc0;
+            acc1 = c.b.v1 - acc1;
+        }
+        if (act) {
+            stp(y + col + k * sz, acc0, acc1);
             if (MODE == 1) part += (double)xc.v0 * (double)acc0 + (double)xc.v1 * (double)acc1;
             if (MODE == 3) part += (double)acc0 * (double)acc0 + (double)acc1 * (double)acc1;
-            // advance: the z+ faces of plane k are the z- faces of plane k+1
-            wzm0 = wzp0;
-            wzm1 = wzp1;
-            xm = xc;
-            xc = xn;
-            rc = rn;
-            xn = xnn;
-            rn = rnn;
-            czp = hpn ? g.cz : T(0);
-            xl = xln; xr = xrn; rl = rln; rr = rrn;
-            xym = xymn; xyp = xypn; rym = rymn; ryp = rypn;
-            mv = mvn;
-            bv = bvn;
-            a = an;
         }
+        // the z+ faces of plane k are the z- faces of plane k+1
+        wzm0 = wzp0;
+        wzm1 = wzp1;
+    };
+    const int dn = col + kbelow(k0, g.nz, g.pz) * sz, at = col + k0 * sz, up = col + kabove(k0, g.nz, g.pz) * sz;
+    Pair<T> X0 = ldp(x + dn), X1 = ldp(x + at), X2 = ldp(x + up), X3 = {T(0), T(0)};
+    Pair<T> R0 = ldp(rho + dn), R1 = ldp(rho + at), R2 = ldp(rho + up), R3 = {T(0), T(0)};
+    Own A, B;
+    load_own(k0, A);
+    const T czm = (k0 > 0 || g.pz) ? g.cz : T(0);
+    T wzm0 = czm * face_kappa<FR>(R1.v0, R0.v0), wzm1 = czm * face_kappa<FR>(R1.v1, R0.v1);
+    int k = k0;
+    for (; k + 4 <= k1; k += 4) {
+        step(k, X0, X1, X2, X3, R1, R2, R3, wzm0, wzm1, A, B);
+        step(k + 1, X1, X2, X3, X0, R2, R3, R0, wzm0, wzm1, B, A);
+        step(k + 2, X2, X3, X0, X1, R3, R0, R1, wzm0, wzm1, A, B);
+        step(k + 3, X3, X0, X1, X2, R0, R1, R2, wzm0, wzm1, B, A);
     }
+    if (k < k1) step(k, X0, X1, X2, X3, R1, R2, R3, wzm0, wzm1, A, B);
+    if (k + 1 < k1) step(k + 1, X1, X2, X3, X0, R2, R3, R0, wzm0, wzm1, B, A);
+    if (k + 2 < k1) step(k + 2, X2, X3, X0, X1, R3, R0, R1, wzm0, wzm1, A, B);
     if (MODE == 1 || MODE == 3) block_partial(part, partials);
 }
 
@@ -874,9 +898,6 @@ __global__ __launch_bounds__(kBlock) void k_relayout(const T* __restrict__ src, 
     }
 }
 
-// plane below / above k (the plane itself where a Neumann end has no face)
-__device__ __forceinline__ int kbelow(int k, int nz, int pz) { return k > 0 ? k - 1 : (pz ? nz - 1 : k); }
-__device__ __forceinline__ int kabove(int k, int nz, int pz) { return k < nz - 1 ? k + 1 : (pz ? 0 : k); }
 
 // Per-thread neighbour rows and face factors of column pair t, row j (absent faces: factor 0 and
 // an in-bounds stand-in index).

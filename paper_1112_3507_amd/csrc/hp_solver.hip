@@ -1636,7 +1636,7 @@ int hp_residual(hp_handle* H, const double* b, const double* x, double* r, doubl
     if (!b || !x || !r) return fail(HP_EINVAL, "null vector");
     LevelData& F = H->lv[0];
     // The caller's vectors are in natural order, and so are rho_natural and m_natural: a split finest level
-    // is not worth two relayouts in and one out (256^3: 155 us instead of 255). Its r may still lie
+    // is not worth two relayouts in and one out (256^3: 140 us instead of 255). Its r may still lie
     // on x or b, which the relayouts kept apart.
     Geo<double> g = geo<double>(H, F);
     g.split = 0;
