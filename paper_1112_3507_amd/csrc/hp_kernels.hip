@@ -635,84 +635,6 @@ __global__ __launch_bounds__(kBlock) void k_apply_zm(Geo<T> g, ZTiles zt,
     if (MODE == 1 || MODE == 3) block_partial(part, partials);
 }
 
-// Inverse diagonals of the large levels by a z march: the same values as k_jacobi_diag (faces
-// summed in the same order from the same operands), with each rho plane of a column loaded once
-// per chunk and the loads of plane k+1 in flight while plane k is computed (one thread per cell
-// reads the two z-neighbour planes again, from other workgroups' tiles). Natural-order inputs;
-// SPLIT writes the outputs in split order (a wave's 64 cells of a row go to two runs of 32).
-template <int FR, bool SPLIT>
-__global__ __launch_bounds__(kBlock) void k_jacobi_diag_zm(Geo<double> g, Geo<float> g32, ZTiles zt,
-                                                           const double* __restrict__ rho,
-                                                           const double* __restrict__ m,
-                                                           double* __restrict__ dinv,
-                                                           float* __restrict__ dinv32) {
-    int bx, by, bz;
-    ztile(zt, bx, by, bz);
-    const int i = bx * 64 + (threadIdx.x & 63);
-    const int j = by * 4 + (threadIdx.x >> 6);
-    const int k0 = bz * zt.kz;
-    const int k1 = min(k0 + zt.kz, g.nz);
-    const int sz = g.nx * g.ny;
-    if (i >= g.nx || j >= g.ny) return;
-    const FaceTab<double> ft(g, i, j);
-    const FaceTab<float> ft32(g32, i, j);
-    const int col = i + g.nx * j;
-    int a = col + k0 * sz;
-    bool hm, hp;
-    const int om = zoff(k0, -1, g.nz, g.pz, sz, hm);
-    const int op = zoff(k0, 1, g.nz, g.pz, sz, hp);
-    // rho of the cell and of its z neighbours (the cell itself where a face is absent, with
-    // factor 0, as in for_faces)
-    double rc = rho[a], rm = rho[a + om], rn = rho[a + op], mv = m[a];
-    double czm = hm ? g.cz : 0.0, czp = hp ? g.cz : 0.0;
-    float czm32 = hm ? g32.cz : 0.0f, czp32 = hp ? g32.cz : 0.0f;
-    double rv[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) rv[q] = rho[a + ft.o[q]];
-    for (int k = k0; k < k1; ++k) {
-        // plane k+1 (clamped to the chunk) and the column above it
-        const int kn = min(k + 1, k1 - 1);
-        const int an = col + kn * sz;
-        bool hpn;
-        const int opn = zoff(kn, 1, g.nz, g.pz, sz, hpn);
-        double rvn[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) rvn[q] = rho[an + ft.o[q]];
-        const double mvn = m[an];
-        const double rnn = rho[an + opn];
-        // plane k: faces x-, x+, y-, y+, z-, z+
-        double d = mv;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) d += ft.c[q] * face_kappa<FR>(rc, rv[q]);
-        d += czm * face_kappa<FR>(rc, rm);
-        d += czp * face_kappa<FR>(rc, rn);
-        const int ao = SPLIT ? split_index(i, j, k, g.nx, g.ny) : a;
-        dinv[ao] = 1.0 / d;
-        if (dinv32) {
-            // the FP32 copies are the FP64 values rounded to nearest
-            const float rc32 = (float)rc;
-            float d32 = (float)mv;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) d32 += ft32.c[q] * face_kappa<FR>(rc32, (float)rv[q]);
-            d32 += czm32 * face_kappa<FR>(rc32, (float)rm);
-            d32 += czp32 * face_kappa<FR>(rc32, (float)rn);
-            dinv32[ao] = 1.0f / d32;
-        }
-        // advance: the z+ face of plane k is the z- face of plane k+1
-        rm = rc;
-        rc = rn;
-        rn = rnn;
-        mv = mvn;
-        czm = czp;
-        czm32 = czp32;
-        czp = hpn ? g.cz : 0.0;
-        czp32 = hpn ? g32.cz : 0.0f;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) rv[q] = rvn[q];
-        a = an;
-    }
-}
-
 // Cell pairs (i0, i0 + 1), i0 even, loaded and stored as one 2-vector; needs nx even and
 // 2-vector-aligned arrays.
 template <typename T>
@@ -738,6 +660,22 @@ __device__ __forceinline__ void stp(T* __restrict__ p, T v0, T v1) {
 __device__ __forceinline__ int kbelow(int k, int nz, int pz) { return k > 0 ? k - 1 : (pz ? nz - 1 : k); }
 __device__ __forceinline__ int kabove(int k, int nz, int pz) { return k < nz - 1 ? k + 1 : (pz ? 0 : k); }
 
+// A tile of 64 cell pairs in x by a few rows. A pair or a row past the grid's end holds what its last neighbour within
+// the grid sees there.
+struct PairTile {
+    int px, py, nx, ny, bx, i0;
+    __device__ __forceinline__ PairTile(int px_, int py_, int nx_, int ny_, int bx_, int iu)
+        : px(px_), py(py_), nx(nx_), ny(ny_), bx(bx_), i0(iu < nx_ ? iu : px_ && iu == nx_ ? 0 : nx_ - 2) {}
+    __device__ __forceinline__ int row(int j) const {
+        return j < 0 ? (py ? ny - 1 : 0) : j < ny ? j : py && j == ny ? 0 : ny - 1;
+    }
+    // the cell beside the tile's first (side 0) or last (1) pair
+    __device__ __forceinline__ int outer(int side) const {
+        const int el = bx * 128 - 1, er = bx * 128 + 128;
+        return side ? (er < nx ? er : px ? 0 : nx - 1) : (el >= 0 ? el : px ? nx - 1 : 0);
+    }
+};
+
 // Operator apply over cell pairs: the same face order as k_apply_zm, with half the memory instructions and the pair's
 // shared x face weighted once. A workgroup marches 128 x 4 columns up a z chunk: a plane's pairs of x and rho, the
 // rows beside the workgroup and its outer x neighbours go through LDS, the column's next planes form a
@@ -759,21 +697,17 @@ __global__ __launch_bounds__(kBlock, 4) void k_apply_zp(Geo<T> g, ZTiles zt,
     const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int iu = (bx * 64 + lane) * 2, j0 = by * kR;
     const bool act = iu < nx && j0 + w < ny;
-    // a pair or row past the end holds what its last neighbour within sees there
-    const int i0 = iu < nx ? iu : (g.px && iu == nx ? 0 : nx - 2);
-    auto row = [&](int j) { return j < 0 ? (g.py ? ny - 1 : 0) : j < ny ? j : (g.py && j == ny ? 0 : ny - 1); };
-    const int j = row(j0 + w);
+    const PairTile pt(g.px, g.py, nx, ny, bx, iu);
+    const int i0 = pt.i0, j = pt.row(j0 + w);
     const int k0 = bz * zt.kz, k1 = min(k0 + zt.kz, g.nz);
     const FaceTab<T> f0(g, i0, j), f1(g, i0 + 1, j);
     const T cxl = f0.c[0], cxr = f1.c[1], cym = f0.c[2], cyp = f0.c[3];
     const int col = i0 + nx * j;
     // this thread's halo pair (a row beside the workgroup) and outer x neighbour (16 of them)
     const int hside = tid >> 7, harr = (tid >> 6) & 1;
-    const T* const halo = (harr ? rho : x) + i0 + nx * row(hside ? j0 + kR : j0 - 1);
+    const T* const halo = (harr ? rho : x) + i0 + nx * pt.row(hside ? j0 + kR : j0 - 1);
     const int eside = tid & 1, earr = (tid >> 1) & 1, erow = (tid >> 2) & (kR - 1);
-    const int el = bx * 128 - 1, er = bx * 128 + 128;
-    const int ex = eside ? (er < nx ? er : g.px ? 0 : nx - 1) : (el >= 0 ? el : g.px ? nx - 1 : 0);
-    const T* const edge = (earr ? rho : x) + ex + nx * row(j0 + erow);
+    const T* const edge = (earr ? rho : x) + pt.outer(eside) + nx * pt.row(j0 + erow);
     double part = 0.0;
     struct Own {
         Pair<T> m, b, h;
@@ -855,6 +789,188 @@ __global__ __launch_bounds__(kBlock, 4) void k_apply_zp(Geo<T> g, ZTiles zt,
     if (k + 1 < k1) step(k + 1, X1, X2, X3, X0, R2, R3, R0, wzm0, wzm1, B, A);
     if (k + 2 < k1) step(k + 2, X2, X3, X0, X1, R3, R0, R1, wzm0, wzm1, A, B);
     if (MODE == 1 || MODE == 3) block_partial(part, partials);
+}
+
+// Inverse diagonals of the large levels by a z march: the same values as k_jacobi_diag (faces
+// summed in the same order from the same operands), with each rho plane of a column loaded once
+// per chunk and the loads of plane k+1 in flight while plane k is computed (one thread per cell
+// reads the two z-neighbour planes again, from other workgroups' tiles). For odd rows, which have no
+// split order.
+template <int FR>
+__global__ __launch_bounds__(kBlock) void k_jacobi_diag_zm(Geo<double> g, Geo<float> g32, ZTiles zt,
+                                                           const double* __restrict__ rho,
+                                                           const double* __restrict__ m,
+                                                           double* __restrict__ dinv,
+                                                           float* __restrict__ dinv32) {
+    int bx, by, bz;
+    ztile(zt, bx, by, bz);
+    const int i = bx * 64 + (threadIdx.x & 63);
+    const int j = by * 4 + (threadIdx.x >> 6);
+    const int k0 = bz * zt.kz;
+    const int k1 = min(k0 + zt.kz, g.nz);
+    const int sz = g.nx * g.ny;
+    if (i >= g.nx || j >= g.ny) return;
+    const FaceTab<double> ft(g, i, j);
+    const FaceTab<float> ft32(g32, i, j);
+    const int col = i + g.nx * j;
+    int a = col + k0 * sz;
+    bool hm, hp;
+    const int om = zoff(k0, -1, g.nz, g.pz, sz, hm);
+    const int op = zoff(k0, 1, g.nz, g.pz, sz, hp);
+    // rho of the cell and of its z neighbours (the cell itself where a face is absent, with
+    // factor 0, as in for_faces)
+    double rc = rho[a], rm = rho[a + om], rn = rho[a + op], mv = m[a];
+    double czm = hm ? g.cz : 0.0, czp = hp ? g.cz : 0.0;
+    float czm32 = hm ? g32.cz : 0.0f, czp32 = hp ? g32.cz : 0.0f;
+    double rv[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) rv[q] = rho[a + ft.o[q]];
+    for (int k = k0; k < k1; ++k) {
+        // plane k+1 (clamped to the chunk) and the column above it
+        const int kn = min(k + 1, k1 - 1);
+        const int an = col + kn * sz;
+        bool hpn;
+        const int opn = zoff(kn, 1, g.nz, g.pz, sz, hpn);
+        double rvn[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) rvn[q] = rho[an + ft.o[q]];
+        const double mvn = m[an];
+        const double rnn = rho[an + opn];
+        // plane k: faces x-, x+, y-, y+, z-, z+
+        double d = mv;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) d += ft.c[q] * face_kappa<FR>(rc, rv[q]);
+        d += czm * face_kappa<FR>(rc, rm);
+        d += czp * face_kappa<FR>(rc, rn);
+        dinv[a] = 1.0 / d;
+        if (dinv32) {
+            // the FP32 copies are the FP64 values rounded to nearest
+            const float rc32 = (float)rc;
+            float d32 = (float)mv;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) d32 += ft32.c[q] * face_kappa<FR>(rc32, (float)rv[q]);
+            d32 += czm32 * face_kappa<FR>(rc32, (float)rm);
+            d32 += czp32 * face_kappa<FR>(rc32, (float)rn);
+            dinv32[a] = 1.0f / d32;
+        }
+        // advance: the z+ face of plane k is the z- face of plane k+1
+        rm = rc;
+        rc = rn;
+        rn = rnn;
+        mv = mvn;
+        czm = czp;
+        czm32 = czp32;
+        czp = hpn ? g.cz : 0.0;
+        czp32 = hpn ? g32.cz : 0.0f;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) rv[q] = rvn[q];
+        a = an;
+    }
+}
+
+// Inverse diagonals of the large levels, even rows: the march of k_apply_zp over rho alone (the faces summed in
+// the order of k_jacobi_diag from the same operands). Natural-order inputs; SPLIT writes the outputs in
+// split order, a pair's cells to the two halves of its row. 110 us at 256^3 beside the coarsest inverse (28 B per
+// cell, 75 us of them; FP64 and FP32 face factors and divisions take about as long); one cell per thread with
+// its neighbours from memory 140.
+template <int FR, bool SPLIT>
+__global__ __launch_bounds__(kBlock) void k_jacobi_diag_zp(Geo<double> g, Geo<float> g32, ZTiles zt,
+                                                           const double* __restrict__ rho,
+                                                           const double* __restrict__ m,
+                                                           double* __restrict__ dinv,
+                                                           float* __restrict__ dinv32) {
+    constexpr int kR = kBlock / 64;
+    __shared__ Pair<double> sx[2][kR + 2][64];  // [plane slot][row][column]
+    __shared__ double se[2][kR][2];             // outer x neighbours: [slot][row][side]
+    int bx, by, bz;
+    ztile(zt, bx, by, bz);
+    const int nx = g.nx, ny = g.ny, sz = nx * ny;
+    const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int iu = (bx * 64 + lane) * 2, j0 = by * kR;
+    const bool act = iu < nx && j0 + w < ny;
+    const PairTile pt(g.px, g.py, nx, ny, bx, iu);
+    const int i0 = pt.i0, j = pt.row(j0 + w);
+    const int k0 = bz * zt.kz, k1 = min(k0 + zt.kz, g.nz);
+    const FaceTab<double> f0(g, i0, j), f1(g, i0 + 1, j);
+    const FaceTab<float> s0(g32, i0, j), s1(g32, i0 + 1, j);
+    const int col = i0 + nx * j;
+    // the first two waves bring the rows beside the workgroup, the third the outer x neighbours
+    const double* const halo = rho + i0 + nx * pt.row(tid >> 6 & 1 ? j0 + kR : j0 - 1);
+    const int eside = tid & 1, erow = (tid >> 1) & (kR - 1);
+    const double* const edge = rho + pt.outer(eside) + nx * pt.row(j0 + erow);
+    struct Own {
+        Pair<double> m, h;
+        double e;
+    };
+    auto load_own = [&](int k, Own& o) {
+        o.m = ldp(m + col + k * sz);
+        o.h = ldp(halo + k * sz);
+        o.e = edge[k * sz];
+    };
+    auto step = [&](int k, const Pair<double>& rm, const Pair<double>& rc, const Pair<double>& rn, Pair<double>& rnn,
+                    const Own& c, Own& nxt) {
+        const int kn = min(k + 1, k1 - 1);
+        load_own(kn, nxt);
+        rnn = ldp(rho + col + kabove(kn, g.nz, g.pz) * sz);
+        const int sl = k & 1;
+        sx[sl][w + 1][lane] = rc;
+        if (tid < 128) sx[sl][tid >> 6 ? kR + 1 : 0][lane] = c.h;
+        if (tid < 2 * kR) se[sl][erow][eside] = c.e;
+        __syncthreads();
+        const double rl = lane > 0 ? sx[sl][w + 1][lane - 1].v1 : se[sl][w][0];
+        const double rr = lane < 63 ? sx[sl][w + 1][lane + 1].v0 : se[sl][w][1];
+        const Pair<double> ry0 = sx[sl][w][lane], ry1 = sx[sl][w + 2][lane];
+        const bool hm = k > 0 || g.pz, hp = k < g.nz - 1 || g.pz;
+        auto diag = [&](auto zero, const auto& gg, const auto& a0, const auto& a1, auto store) {
+            using T = decltype(zero);
+            const T c0 = (T)rc.v0, c1 = (T)rc.v1;
+            const T kx = face_kappa<FR>(c0, c1);
+            const T czm = hm ? gg.cz : T(0), czp = hp ? gg.cz : T(0);
+            T d0 = (T)c.m.v0, d1 = (T)c.m.v1;
+            d0 += a0.c[0] * face_kappa<FR>(c0, (T)rl);
+            d0 += a0.c[1] * kx;
+            d0 += a0.c[2] * face_kappa<FR>(c0, (T)ry0.v0);
+            d0 += a0.c[3] * face_kappa<FR>(c0, (T)ry1.v0);
+            d0 += czm * face_kappa<FR>(c0, (T)rm.v0);
+            d0 += czp * face_kappa<FR>(c0, (T)rn.v0);
+            d1 += a1.c[0] * kx;
+            d1 += a1.c[1] * face_kappa<FR>(c1, (T)rr);
+            d1 += a1.c[2] * face_kappa<FR>(c1, (T)ry0.v1);
+            d1 += a1.c[3] * face_kappa<FR>(c1, (T)ry1.v1);
+            d1 += czm * face_kappa<FR>(c1, (T)rm.v1);
+            d1 += czp * face_kappa<FR>(c1, (T)rn.v1);
+            store(T(1) / d0, T(1) / d1);
+        };
+        const int rb = nx * j + k * sz, par = (j + k) & 1;
+        auto put = [&](auto* out) {
+            return [=](auto v0, auto v1) {
+                if (!act) return;
+                if (SPLIT) {
+                    out[rb + (i0 >> 1)] = par ? v1 : v0;
+                    out[rb + (nx >> 1) + (i0 >> 1)] = par ? v0 : v1;
+                } else {
+                    stp(out + rb + i0, v0, v1);
+                }
+            };
+        };
+        diag(0.0, g, f0, f1, put(dinv));
+        // the FP32 copies are the FP64 values rounded to nearest
+        if (dinv32) diag(0.0f, g32, s0, s1, put(dinv32));
+    };
+    Pair<double> R0 = ldp(rho + col + kbelow(k0, g.nz, g.pz) * sz), R1 = ldp(rho + col + k0 * sz);
+    Pair<double> R2 = ldp(rho + col + kabove(k0, g.nz, g.pz) * sz), R3 = {0.0, 0.0};
+    Own A, B;
+    load_own(k0, A);
+    int k = k0;
+    for (; k + 4 <= k1; k += 4) {
+        step(k, R0, R1, R2, R3, A, B);
+        step(k + 1, R1, R2, R3, R0, B, A);
+        step(k + 2, R2, R3, R0, R1, A, B);
+        step(k + 3, R3, R0, R1, R2, B, A);
+    }
+    if (k < k1) step(k, R0, R1, R2, R3, A, B);
+    if (k + 1 < k1) step(k + 1, R1, R2, R3, R0, B, A);
+    if (k + 2 < k1) step(k + 2, R2, R3, R0, R1, A, B);
 }
 
 // ---- red-black split layout (finest level) ----
@@ -1621,18 +1737,34 @@ int launch_presmooth_update(const Geo<T>& g, const T* rho, const T* dinv, const 
 
 static bool use_zm(int nx, int ny, int nz) { return nx >= 64 && ny >= 4 && nz >= 8; }
 
+// pair kernels: z-march shape, nx even and every array aligned for 2-vector access
+template <typename T>
+static bool use_zp(const Geo<T>& g, std::initializer_list<const T*> arrays) {
+    if (sizeof(T) != 8 || !use_zm(g.nx, g.ny, g.nz) || (g.nx & 1)) return false;
+    for (const T* p : arrays)
+        if (p && (reinterpret_cast<uintptr_t>(p) % (2 * sizeof(T))) != 0) return false;
+    return true;
+}
+
 void launch_jacobi_diag(const Geo<double>& g, const Geo<float>& g32, const double* rho,
                         const double* m, const float* rho32, const float* m32, double* dinv,
                         float* dinv32, bool split_out, hipStream_t s) {
-    if (use_zm(g.nx, g.ny, g.nz)) {
-        const ZTiles zt = ztiles(g.nx, g.ny, g.nz, 64);
+    if (use_zp(g, {rho, m, dinv}) && reinterpret_cast<uintptr_t>(dinv32) % (2 * sizeof(float)) == 0) {
+        const ZTiles zt = ztiles(g.nx, g.ny, g.nz, 128);
         const dim3 grid(zt.tx * zt.ty * zt.tz), block(kBlock);
         if (split_out)
-            WITH_FACE_RULE(g.frule, hipLaunchKernelGGL((k_jacobi_diag_zm<FRV, true>), grid, block, 0, s, g,
+            WITH_FACE_RULE(g.frule, hipLaunchKernelGGL((k_jacobi_diag_zp<FRV, true>), grid, block, 0, s, g,
                                                        g32, zt, rho, m, dinv, dinv32));
         else
-            WITH_FACE_RULE(g.frule, hipLaunchKernelGGL((k_jacobi_diag_zm<FRV, false>), grid, block, 0, s, g,
+            WITH_FACE_RULE(g.frule, hipLaunchKernelGGL((k_jacobi_diag_zp<FRV, false>), grid, block, 0, s, g,
                                                        g32, zt, rho, m, dinv, dinv32));
+        return;
+    }
+    if (!split_out && use_zm(g.nx, g.ny, g.nz)) {
+        const ZTiles zt = ztiles(g.nx, g.ny, g.nz, 64);
+        const dim3 grid(zt.tx * zt.ty * zt.tz), block(kBlock);
+        WITH_FACE_RULE(g.frule, hipLaunchKernelGGL((k_jacobi_diag_zm<FRV>), grid, block, 0, s, g, g32, zt, rho, m,
+                                                   dinv, dinv32));
         return;
     }
     Shape3 sh = cells_shape(g.nx, g.ny, g.nz);
@@ -1649,15 +1781,6 @@ static int64_t zm_blocks(int nx, int ny, int nz) {
         nb = std::max<int64_t>(nb, (int64_t)t.tx * t.ty * t.tz);
     }
     return nb;
-}
-
-// pair kernels: z-march shape, nx even and every array aligned for 2-vector access
-template <typename T>
-static bool use_zp(const Geo<T>& g, std::initializer_list<const T*> arrays) {
-    if (sizeof(T) != 8 || !use_zm(g.nx, g.ny, g.nz) || (g.nx & 1)) return false;
-    for (const T* p : arrays)
-        if (p && (reinterpret_cast<uintptr_t>(p) % (2 * sizeof(T))) != 0) return false;
-    return true;
 }
 
 template <typename T>

@@ -1,12 +1,14 @@
-"""hp_residual where the 128 x 4 column tiles of the operator end within or beside the grid, closed and periodic.
+"""hp_residual, and the diagonals by one half sweep, where the 128 x 4 column tiles end within or beside the grid,
+closed and periodic.
 
 Tolerance: each entry is one seven-point sum of values of order 1, 1e-13 relative as in
-test_gpu_parity; the returned relative norm 1e-12.
+test_gpu_parity; the returned relative norm and the half sweep 1e-12.
 """
 import numpy as np
 import pytest
 
 import oracle
+from oracle import mg
 
 torch = pytest.importorskip("torch")
 pytestmark = [pytest.mark.gpu,
@@ -32,3 +34,25 @@ def test_residual_tiles(n, bc):
         torch.cuda.synchronize()
     assert np.linalg.norm(r.cpu().numpy() - ref) <= 1e-13 * np.linalg.norm(ref)
     assert abs(rel - np.linalg.norm(ref) / np.linalg.norm(b)) <= 1e-12 * rel
+
+
+@pytest.mark.parametrize("n", [(64, 4, 8), (126, 6, 12), (128, 8, 16), (130, 6, 10), (65, 6, 9)])
+@pytest.mark.parametrize("bc", [(hp.NEUMANN, hp.PERIODIC, hp.NEUMANN), (hp.PERIODIC, hp.NEUMANN, hp.NEUMANN),
+                                (hp.NEUMANN, hp.NEUMANN, hp.NEUMANN)])
+def test_diagonal_tiles(n, bc):
+    if n[0] % 2 and bc[0] == hp.PERIODIC:
+        pytest.skip("periodic axes have an even number of cells")
+    rng = np.random.default_rng(8)
+    shape = n[::-1]
+    rho, c2 = 1.0 + rng.random(shape), 1.0 + rng.random(shape)
+    h, dt = (0.1, 0.2, 0.3), 0.5
+    L = mg.build_hierarchy(n, h, bc, rho, c2, dt)[0]
+    dev = lambda a: torch.from_numpy(a).cuda()  # noqa: E731
+    with hp.setup(n, h, bc, dev(rho), dev(c2), dt) as s:
+        for colour in (0, 1):
+            x, r = rng.standard_normal(shape), rng.standard_normal(shape)
+            z = dev(x.copy())
+            s.smooth(0, dev(r), z, colour)
+            torch.cuda.synchronize()
+            ref = mg.half_sweep(L, r, x, colour)
+            assert np.linalg.norm(z.cpu().numpy() - ref) <= 1e-12 * np.linalg.norm(ref), colour
