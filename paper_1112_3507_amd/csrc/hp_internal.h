@@ -181,6 +181,10 @@ InversePlan plan_inverse(const int n[3], const int per[3]);
 void launch_coarse_inverse(const InversePlan& plan, double* work, int* tables, const double* rho, const double* m,
                            const int n[3], const int per[3], const double cd[3], int face_rule, double* out, int* flag,
                            hipStream_t s);
+// y = b - A x with <y, y> under rc and <b, b> under bb (partials of their own) in one pass over even rows in natural
+// order; returns false (and does nothing) for other shapes
+bool launch_residual_norms(const Geo<double>& g, const double* rho, const double* m, const double* x, const double* b,
+                           double* y, const RedCtl& rc, const RedCtl& bb, hipStream_t s);
 
 // Deterministic dot <x, y> accumulated in FP64.
 template <typename T>

@@ -681,13 +681,15 @@ struct PairTile {
 // rows beside the workgroup and its outer x neighbours go through LDS, the column's next planes form a
 // register ring that rotates by renaming (a move would wait for the load in flight). Bound by
 // memory: the residual takes 140 us at 256^3 (40 B per cell); 160 with every neighbour from memory.
+// MODE 4: the residual with <y, y> and <b, b> (partials2).
 template <typename T, int MODE, int FR = 0>
 __global__ __launch_bounds__(kBlock, 4) void k_apply_zp(Geo<T> g, ZTiles zt,
                                                      const T* __restrict__ rho,
                                                      const T* __restrict__ m,
                                                      const T* __restrict__ x,
                                                      const T* __restrict__ b, T* __restrict__ y,
-                                                     double* __restrict__ partials) {
+                                                     double* __restrict__ partials,
+                                                     double* __restrict__ partials2) {
     constexpr int kR = kBlock / 64;
     __shared__ Pair<T> sx[2][2][kR + 2][64];  // [plane slot][x, rho][row][column]
     __shared__ T se[2][2][kR][2];             // outer x neighbours: [slot][x, rho][row][side]
@@ -708,7 +710,7 @@ __global__ __launch_bounds__(kBlock, 4) void k_apply_zp(Geo<T> g, ZTiles zt,
     const T* const halo = (harr ? rho : x) + i0 + nx * pt.row(hside ? j0 + kR : j0 - 1);
     const int eside = tid & 1, earr = (tid >> 1) & 1, erow = (tid >> 2) & (kR - 1);
     const T* const edge = (earr ? rho : x) + pt.outer(eside) + nx * pt.row(j0 + erow);
-    double part = 0.0;
+    double part = 0.0, part2 = 0.0;
     struct Own {
         Pair<T> m, b, h;
         T e;
@@ -765,7 +767,8 @@ __global__ __launch_bounds__(kBlock, 4) void k_apply_zp(Geo<T> g, ZTiles zt,
         if (act) {
             stp(y + col + k * sz, acc0, acc1);
             if (MODE == 1) part += (double)xc.v0 * (double)acc0 + (double)xc.v1 * (double)acc1;
-            if (MODE == 3) part += (double)acc0 * (double)acc0 + (double)acc1 * (double)acc1;
+            if (MODE >= 3) part += (double)acc0 * (double)acc0 + (double)acc1 * (double)acc1;
+            if (MODE == 4) part2 += (double)c.b.v0 * (double)c.b.v0 + (double)c.b.v1 * (double)c.b.v1;
         }
         // the z+ faces of plane k are the z- faces of plane k+1
         wzm0 = wzp0;
@@ -788,7 +791,8 @@ __global__ __launch_bounds__(kBlock, 4) void k_apply_zp(Geo<T> g, ZTiles zt,
     if (k < k1) step(k, X0, X1, X2, X3, R1, R2, R3, wzm0, wzm1, A, B);
     if (k + 1 < k1) step(k + 1, X1, X2, X3, X0, R2, R3, R0, wzm0, wzm1, B, A);
     if (k + 2 < k1) step(k + 2, X2, X3, X0, X1, R3, R0, R1, wzm0, wzm1, A, B);
-    if (MODE == 1 || MODE == 3) block_partial(part, partials);
+    if (MODE == 1 || MODE >= 3) block_partial(part, partials);
+    if (MODE == 4) block_partial(part2, partials2);
 }
 
 // Inverse diagonals of the large levels by a z march: the same values as k_jacobi_diag (faces
@@ -1803,10 +1807,10 @@ void launch_apply(const Geo<T>& g, const T* rho, const T* m, const T* x, const T
         nb = zt.tx * zt.ty * zt.tz;
         dim3 grid(nb), block(kBlock);
         WITH_FACE_RULE(g.frule, switch (mode) {
-            case 0: hipLaunchKernelGGL((k_apply_zp<T, 0, FRV>), grid, block, 0, s, g, zt, rho, m, x, b, y, rc.partials); break;
-            case 1: hipLaunchKernelGGL((k_apply_zp<T, 1, FRV>), grid, block, 0, s, g, zt, rho, m, x, b, y, rc.partials); break;
-            case 2: hipLaunchKernelGGL((k_apply_zp<T, 2, FRV>), grid, block, 0, s, g, zt, rho, m, x, b, y, rc.partials); break;
-            default: hipLaunchKernelGGL((k_apply_zp<T, 3, FRV>), grid, block, 0, s, g, zt, rho, m, x, b, y, rc.partials); break;
+            case 0: hipLaunchKernelGGL((k_apply_zp<T, 0, FRV>), grid, block, 0, s, g, zt, rho, m, x, b, y, rc.partials, nullptr); break;
+            case 1: hipLaunchKernelGGL((k_apply_zp<T, 1, FRV>), grid, block, 0, s, g, zt, rho, m, x, b, y, rc.partials, nullptr); break;
+            case 2: hipLaunchKernelGGL((k_apply_zp<T, 2, FRV>), grid, block, 0, s, g, zt, rho, m, x, b, y, rc.partials, nullptr); break;
+            default: hipLaunchKernelGGL((k_apply_zp<T, 3, FRV>), grid, block, 0, s, g, zt, rho, m, x, b, y, rc.partials, nullptr); break;
         });
     } else if (use_zm(g.nx, g.ny, g.nz)) {
         ZTiles zt = ztiles(g.nx, g.ny, g.nz, 64);
@@ -1830,6 +1834,20 @@ void launch_apply(const Geo<T>& g, const T* rho, const T* m, const T* x, const T
         });
     }
     if (mode == 1 || mode == 3) finalize(rc, nb, s);
+}
+
+bool launch_residual_norms(const Geo<double>& g, const double* rho, const double* m, const double* x, const double* b,
+                           double* y, const RedCtl& rc, const RedCtl& bb, hipStream_t s) {
+    // b read once: 140 us at 256^3, where a dot of b of its own came to 140 + 27; other shapes keep the two passes
+    if (g.split || !use_zp(g, {rho, m, x, b, y})) return false;
+    ZTiles zt = ztiles(g.nx, g.ny, g.nz, 128);
+    zt.rev = g.rev;
+    const int nb = zt.tx * zt.ty * zt.tz;
+    WITH_FACE_RULE(g.frule, hipLaunchKernelGGL((k_apply_zp<double, 4, FRV>), dim3(nb), dim3(kBlock), 0, s, g, zt, rho, m,
+                                               x, b, y, rc.partials, bb.partials));
+    finalize(rc, nb, s);
+    finalize(bb, nb, s);
+    return true;
 }
 
 // ------------------------------------------------------------------------------------------

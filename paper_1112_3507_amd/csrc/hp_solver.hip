@@ -94,7 +94,7 @@ struct hp_handle {
     double *bs = nullptr, *xs = nullptr, *rho_nat = nullptr, *m_nat = nullptr;
     double* scal = nullptr;
     double* partials = nullptr;
-    double* partials2 = nullptr;  // the first half of a reduction split over two launches
+    double* partials2 = nullptr;  // of a second sum beside partials: a reduction's other half, or another norm
     int* flag = nullptr;
     int64_t partial_cap = 0;
     double* host_scal = nullptr;  // pinned mirror of scal
@@ -1636,14 +1636,19 @@ int hp_residual(hp_handle* H, const double* b, const double* x, double* r, doubl
     if (!b || !x || !r) return fail(HP_EINVAL, "null vector");
     LevelData& F = H->lv[0];
     // The caller's vectors are in natural order, and so are rho_natural and m_natural: a split finest level
-    // is not worth two relayouts in and one out (256^3: 140 us instead of 255). Its r may still lie
+    // is not worth two relayouts in and one out (256^3: 140 us with the norm of b instead of 282). Its r may still lie
     // on x or b, which the relayouts kept apart.
     Geo<double> g = geo<double>(H, F);
     g.split = 0;
     auto meets = [&](const double* v) { return r < v + F.N && v < r + F.N; };
     double* const out = F.split && (meets(b) || meets(x)) ? H->z : r;
-    launch_apply<double>(g, rho_natural(H), m_natural(H), x, b, out, 3, red(H, OP_STORE, S_RR), H->stream);
-    launch_dot<double>(b, b, F.N, red(H, OP_STORE, S_BB), H->stream);
+    const RedCtl rr = red(H, OP_STORE, S_RR);
+    RedCtl bb = red(H, OP_STORE, S_BB);
+    bb.partials = H->partials2;
+    if (!launch_residual_norms(g, rho_natural(H), m_natural(H), x, b, out, rr, bb, H->stream)) {
+        launch_apply<double>(g, rho_natural(H), m_natural(H), x, b, out, 3, rr, H->stream);
+        launch_dot<double>(b, b, F.N, bb, H->stream);
+    }
     if (out != r) launch_copy<double>(out, r, F.N, H->stream);
     CHK(check_launch());
     if (rel) {
