@@ -1500,7 +1500,11 @@ int hp_solve(hp_handle* H, const double* b, double* x, double tol) {
     H->tev_used = 0;
     HIPCHK(hipEventRecord(H->ev0, s));
     if (H->mode == HP_MODE_FP64_MGPCG && small_solve(H)) {
-        const int rc = solve_small(H, b, x, tol);
+        // The launch updates the caller's x in place and reads b again at the end. On a split finest level, where
+        // the launch-by-launch solve works on copies, p may therefore share memory with rhs here, too.
+        const bool shared = F.split && b < x + N && x < b + N;
+        if (shared) launch_copy<double>(b, H->bs, N, s);
+        const int rc = solve_small(H, shared ? H->bs : b, x, tol);
         HIPCHK(hipEventRecord(H->ev1, s));
         HIPCHK(hipEventSynchronize(H->ev1));
         float ms = 0.0f;
