@@ -317,7 +317,8 @@ int hp_prolong_add_f32(hp_handle* h, int level, const float* ec, float* z);
 int hp_coarse_solve(hp_handle* h, const double* b, double* x);
 int hp_coarse_solve_f32(hp_handle* h, const float* b, float* x);
 
-/* One multigrid V-cycle z = M r on the fine level (the preconditioner of FP64_MGPCG). */
+/* One multigrid V-cycle z = M r on the fine level (the preconditioner of FP64_MGPCG). Enqueued only: if
+ * a launch of it does not finish (which hp_solve returns as HP_EHIP), z is NaN. */
 int hp_precond(hp_handle* h, const double* r, double* z);
 int hp_precond_f32(hp_handle* h, const float* r, float* z);
 

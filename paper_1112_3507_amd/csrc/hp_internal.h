@@ -20,7 +20,7 @@ enum Slot {
     S_BETA = 3,
     S_RR = 4,      // ||r||^2
     S_BB = 5,      // ||b||^2
-    S_FLAG = 6,    // breakdown flag (1.0 when p^T A p <= 0 or not finite)
+    S_FLAG = 6,    // FLAG_BREAKDOWN when p^T A p <= 0 or not finite, FLAG_LOST when a V-cycle did not finish
     S_TMP = 7,     // scratch result of a plain dot
     S_RZ_NEW = 8,
     S_GAMMA = 9,   // learned FCG: step of the network's estimate in the preconditioner
@@ -28,6 +28,8 @@ enum Slot {
     S_T2 = 11,
     S_COUNT = 16
 };
+
+constexpr double FLAG_BREAKDOWN = 1.0, FLAG_LOST = 2.0;  // (a lost V-cycle breaks the CG down, too, and is kept)
 
 // scalar steps of the learned FCG (hp_fcg.hip)
 enum FcgScalar { FCG_GAMMA = 0, FCG_ALPHA = 1, FCG_BETA = 2 };

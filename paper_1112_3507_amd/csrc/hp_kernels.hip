@@ -103,7 +103,7 @@ __global__ __launch_bounds__(kBlock) void k_finalize(const double* __restrict__ 
         case OP_ALPHA:
             sc[S_PQ] = tot;
             if (!(tot > 0.0) || !isfinite(tot)) {
-                sc[S_FLAG] = 1.0;
+                sc[S_FLAG] = fmax(sc[S_FLAG], FLAG_BREAKDOWN);
                 sc[S_ALPHA] = 0.0;
             } else {
                 sc[S_ALPHA] = rz / tot;

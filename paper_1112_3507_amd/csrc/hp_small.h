@@ -9,6 +9,7 @@ constexpr int kSmallThreads = 512;              // a workgroup (1024 leave 64 re
 constexpr int kSmallLevels = 16;                // most levels one launch takes
 constexpr int kSmallItems = 4 * kSmallThreads;  // most x pairs of its first level: four of each colour per thread
 constexpr int kSmallLds = 159 * 1024;           // LDS bytes for its vectors
+constexpr int kBarrierPolls = 1 << 22;          // seconds: only a lost member could make a barrier last that long
 
 // Counters of a launch, all zero before it (and again after it); one launch at a time.
 struct SmallState {
@@ -65,7 +66,8 @@ struct SmallArgs {
     double* z;         // where a V-cycle's result goes
     double* exchange;  // 2 nc values between the owner and its helpers
     SmallState* state;
-    double* scal;      // S_FLAG is set if a V-cycle's barrier ran out of polls
+    double* scal;      // if a V-cycle's barrier ran out of polls, S_FLAG is FLAG_LOST, and z NaN
+    int polls;
     SmallCG cg;
 };
 

@@ -34,7 +34,6 @@ namespace {
 constexpr int kTT = kSmallThreads;
 constexpr int kTW = kTT / 64;            // waves per workgroup
 constexpr int kJoinPolls = 64;           // how long the owner waits for helpers
-constexpr int kBarrierPolls = 1 << 22;   // seconds: only a lost member could make a barrier last that long
 
 template <typename T>
 __device__ __forceinline__ T ld(const T* p) {
@@ -71,7 +70,8 @@ struct Member {
     SmallState* t;
     int rank, size;      // of this workgroup among those of the launch, and how many there are
     unsigned target;     // what the counter reaches at the next barrier
-    int lost;            // a barrier ran out of polls
+    int polls;           // at most so many a barrier
+    int lost;            // a barrier ran out of them
 
     // every member's stores before the barrier are visible to every member's loads after it
     __device__ __forceinline__ void barrier() {
@@ -83,8 +83,8 @@ struct Member {
                 target += size;
                 __hip_atomic_fetch_add(&t->arrived, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 int n = 0;
-                while ((int)(ld(&t->arrived) - target) < 0 && ++n < kBarrierPolls) {}
-                ok = n < kBarrierPolls;
+                while ((int)(ld(&t->arrived) - target) < 0 && ++n < polls) {}
+                ok = n < polls;
             }
             __syncthreads();
             lost |= !ok;
@@ -517,7 +517,7 @@ __device__ __forceinline__ void own(Member& me, const SmallArgs& args, double* l
         }
         if constexpr (!CG) {
 #pragma unroll
-            for (int c = 0; c < 2; ++c) mine(c, [&](Own& o) { args.z[o.a] = z0[o.a]; });
+            for (int c = 0; c < 2; ++c) mine(c, [&](Own& o) { args.z[o.a] = me.lost ? __builtin_nan("") : z0[o.a]; });
             break;
         } else {
             double v = 0.0;
@@ -601,7 +601,7 @@ __device__ __forceinline__ void own(Member& me, const SmallArgs& args, double* l
         }
         if (me.size > 1) me.barrier();
     } else {
-        if (me.lost && threadIdx.x == 0) args.scal[S_FLAG] = 1.0;
+        if (me.lost && threadIdx.x == 0) args.scal[S_FLAG] = FLAG_LOST;
     }
 }
 
@@ -648,7 +648,7 @@ __global__ __launch_bounds__(kTT) void k_small(SmallArgs args) {
         s_size = size;
     }
     __syncthreads();
-    Member me{t, s_rank, s_size, 0u, 0};
+    Member me{t, s_rank, s_size, 0u, args.polls, 0};
     if (me.rank == 0)
         own<U, CG>(me, args, dynamic_lds, sums);
     else if (me.rank > 0)

@@ -114,6 +114,7 @@ struct hp_handle {
     // (the number of levels if none), the launch's shape, its level tables, counters, exchange and
     // the result of a solve (mapped host memory)
     int small_from = 0;
+    int small_polls = kBarrierPolls;
     SmallShape small{};
     SmallTable* small_tab = nullptr;
     SmallState* small_state = nullptr;
@@ -535,6 +536,7 @@ SmallArgs small_args(hp_handle* H, const double* r, double* z) {
     A.exchange = H->small_exchange;
     A.state = H->small_state;
     A.scal = H->scal;
+    A.polls = H->small_polls;
     return A;
 }
 
@@ -641,7 +643,12 @@ int post_scalars(hp_handle* H, int nparts) {
     return HP_OK;
 }
 
-bool host_breakdown(const hp_handle* H) { return H->host_part[H->partial_cap] != 0.0; }
+// The error that S_FLAG stands for, if any.
+int flag_error(double flag, const char* breakdown) {
+    if (flag == FLAG_LOST) return fail(HP_EHIP, "a V-cycle launch did not finish");
+    return flag != 0.0 ? fail(HP_EBREAKDOWN, "%s", breakdown) : HP_OK;
+}
+double host_flag_value(const hp_handle* H) { return H->host_part[H->partial_cap]; }
 
 // ||r||^2 from the partials of the last r -= alpha q, in workgroup order
 double host_rr(const hp_handle* H) {
@@ -768,7 +775,7 @@ int pcg64(hp_handle* H, const double* b, double* x, double tol, double bnorm) {
         CHK(check_launch());
         CHK(wait_scalars(H));
         st.iterations++;
-        if (host_breakdown(H)) return fail(HP_EBREAKDOWN, "CG breakdown: p^T A p <= 0");
+        CHK(flag_error(host_flag_value(H), "CG breakdown: p^T A p <= 0"));
         double rr = host_rr(H);
         if (!std::isfinite(rr)) return fail(HP_ENAN, "non-finite residual in iteration %d", st.iterations);
         ratio = rr_prev > 0.0 ? rr / rr_prev : 1.0;
@@ -910,7 +917,7 @@ int inner_pcg32(hp_handle* H, double eta, int budget, int* its, bool* pending) {
         CHK(check_launch());
         CHK(wait_scalars(H));
         (*its)++;
-        if (host_breakdown(H)) return fail(HP_EBREAKDOWN, "inner CG breakdown");
+        CHK(flag_error(host_flag_value(H), "inner CG breakdown"));
         double rr = host_rr(H);
         if (!std::isfinite(rr)) return fail(HP_ENAN, "non-finite inner residual");
         ratio = rr_prev > 0.0 ? rr / rr_prev : 1.0;
@@ -1042,6 +1049,7 @@ int fcg_learned(hp_handle* H, const double* b, double* x, double tol, double bno
         CHK(check_launch());
         CHK(read_scalars(H));
         st.iterations++;
+        CHK(flag_error(H->host_scal[S_FLAG], "FCG breakdown: p^T A p <= 0"));
         const double pq = H->host_scal[S_PQ];
         if (!(pq > 0.0) || !std::isfinite(pq)) return fail(HP_EBREAKDOWN, "FCG breakdown: p^T A p <= 0");
         double rr = H->host_scal[S_RR];
@@ -1366,6 +1374,10 @@ void hp_free(hp_handle* H) {
     for (hipEvent_t e : H->tev) (void)hipEventDestroy(e);
     delete H;
 }
+
+// Not part of the interface, for the tests of a lost barrier: the polls that a barrier of this handle's one-launch
+// V-cycles and solves has from now on. With 0 every barrier counts as lost, and every workgroup still ends.
+void hp_test_barrier_polls(hp_handle* H, int polls) { H->small_polls = polls; }
 
 int hp_set_stream(hp_handle* H, void* stream) {
     if (!H) return fail(HP_EINVAL, "null handle");
