@@ -205,10 +205,8 @@ __device__ __forceinline__ f64x4 operator_entries(const InverseArgs& p, const in
 // Minus the inverse of a 32 x 32 matrix held by a wave as four 16 x 16 results of the matrix instruction (lane l, value
 // i: row l / 16 + 4 i, column l % 16), by symmetric sweeps of four pivots. Rows 4 q .. 4 q + 3 of a tile are then value q
 // of every lane, in the layout of the instruction's right operand, and by symmetry columns 4 q .. in that of its
-// left operand: nothing moves between lanes but the 4 x 4 pivot block. That block is inverted with its rows and columns
-// divided by powers of two near the square roots of its diagonal (exact, so no bit depends on it): its 2 x 2
-// determinants stay within range for operators of any scale. Returns whether every pivot is
-// positive and finite.
+// left operand: nothing moves between lanes but the 4 x 4 pivot block. Returns whether every pivot is positive
+// and finite.
 __device__ __forceinline__ bool sweep_32(f64x4 (&v)[2][2]) {
     const int lane = threadIdx.x & 63, k = lane >> 4, j = lane & 3;
     const f64x4 zero = {0.0, 0.0, 0.0, 0.0};
@@ -216,16 +214,7 @@ __device__ __forceinline__ bool sweep_32(f64x4 (&v)[2][2]) {
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
         const int tq = q >> 2, rq = q & 3;
-        const double row[2] = {v[tq][0][rq], v[tq][1][rq]};
-        // a lane's exponent: of its row k and its column j of the pivot block together
-        auto pick = [](int e, auto a, auto b, auto c, auto d) { return e & 2 ? (e & 1 ? d : c) : (e & 1 ? b : a); };
-        auto half_exponent = [&](int c) {
-            const unsigned hi = __builtin_amdgcn_readlane((unsigned)(__builtin_bit_cast(uint64_t, row[tq]) >> 32), 4 * rq + 17 * c);
-            return ((int)(hi >> 20 & 0x7ffu) - 1023) >> 1;
-        };
-        const int h0 = half_exponent(0), h1 = half_exponent(1), h2 = half_exponent(2), h3 = half_exponent(3);
-        const int down = -(pick(k, h0, h1, h2, h3) + pick(j, h0, h1, h2, h3));
-        const double src = __builtin_ldexp(row[tq], down);
+        const double row[2] = {v[tq][0][rq], v[tq][1][rq]}, src = row[tq];
         auto at = [&](int r, int c) { return lane_value(src, 4 * rq + c + 16 * r); };
         const double a00 = at(0, 0), a01 = at(0, 1), a02 = at(0, 2), a03 = at(0, 3), a11 = at(1, 1), a12 = at(1, 2),
                      a13 = at(1, 3), a22 = at(2, 2), a23 = at(2, 3), a33 = at(3, 3);
@@ -245,8 +234,9 @@ __device__ __forceinline__ bool sweep_32(f64x4 (&v)[2][2]) {
         good = good && a00 > 0.0 && a00 < INFINITY && det > 0.0 && det < INFINITY && s00 > 0.0 && s00 < INFINITY &&
                dets > 0.0 && dets < INFINITY;
         // entry (lane % 4, lane / 16) of the inverse
-        const double inv = __builtin_ldexp(pick(j, pick(k, d00, d01, d02, d03), pick(k, d01, d11, d12, d13),
-                                                pick(k, d02, d12, d22, d23), pick(k, d03, d13, d23, d33)), down);
+        auto pick = [](int e, double a, double b, double c, double d) { return e & 2 ? (e & 1 ? d : c) : (e & 1 ? b : a); };
+        const double inv = pick(j, pick(k, d00, d01, d02, d03), pick(k, d01, d11, d12, d13), pick(k, d02, d12, d22, d23),
+                                pick(k, d03, d13, d23, d33));
         const double prow[2] = {mfma(inv, row[0], zero)[0], mfma(inv, row[1], zero)[0]};
         // the lanes that hold the pivots' own columns (of tile column tq): these become A_iK D
         const bool own = ((lane & 15) >> 2) == rq;
@@ -394,7 +384,27 @@ __global__ __launch_bounds__(256) void k_inverse_step(InverseArgs p) {
     for (int w = 0; w < 4; ++w)
 #pragma unroll
         for (int e = 0; e < 4; ++e) v[w >> 1][w & 1][e] = own[(w * 4 + e) * 64 + lane];
+    // Where the diagonal holds values beyond 2^+-256, rows and columns are divided by powers of two near its square
+    // roots, before the sweep and after it: the sweep's 2 x 2 determinants would leave the range otherwise. (As the
+    // factors are powers of two, no other bit would change; always doing it cost 0.4 us a step.)
+    auto half_exponent = [&](int r) {
+        const int q = r & 15, at = ((r >> 4) * 12 + (q >> 2)) * 64 + 16 * (q & 3) + q;  // of entry (r, r)
+        return ((int)(((const unsigned*)own)[2 * at + 1] >> 20 & 0x7ffu) - 1023) >> 1;
+    };
+    auto scale = [&] {
+        asm volatile("" ::: "memory");  // (the exponents are read again after the sweep: kept, they cost a wave of occupancy)
+        const int col[2] = {half_exponent(c), half_exponent(16 + c)};
+#pragma unroll
+        for (int w = 0; w < 4; ++w)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                v[w >> 1][w & 1][e] = __builtin_ldexp(v[w >> 1][w & 1][e],
+                                                      -(half_exponent(16 * (w >> 1) + k + 4 * e) + col[w & 1]));
+    };
+    const bool far = __any(abs(half_exponent(lane & 31)) > 128);
+    if (far) scale();
     if (!sweep_32(v) && lane == 0) *p.flag = 1;
+    if (far) scale();
     double* const to = p.diag + (then * kSet + slot_i) * kTile;
 #pragma unroll
     for (int w = 0; w < 4; ++w)
