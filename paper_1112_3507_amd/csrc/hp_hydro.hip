@@ -25,6 +25,8 @@
 #include "hp.h"
 #include "hp_internal.h"
 
+#include <type_traits>
+
 namespace {
 
 struct HGeo {
@@ -64,12 +66,13 @@ struct RhsArgs {
 };
 
 // z planes per chunk of a pass with `tiles` column tiles per plane and `threads` threads per
-// workgroup: up to 32, fewer (not under 2) where the launch would leave the 256 CUs short of 2048
-// threads each. A chunk loads its first planes' z neighbours again, so longer ones read less; at
+// workgroup: up to 32, fewer (not under 2) where the launch would leave the 256 CUs short of `fill`
+// threads each: 2048, and 1024 for tiles that have all rows (1 x 4 x 4096 cells, every term of the right-hand side: 22 us
+// so, 25 with 2048). A chunk loads its first planes' z neighbours again, so longer ones read less; at
 // 96 x 80 x 72 chunks of 16, 2 (this rule) and 1 planes took 28, 20 and 24 us for the right-hand side with every
 // term, 26, 17 and 18 for the update, and 34, 22 and 26 for the advection.
-static int hydro_chunk(int nz, int64_t tiles, int threads) {
-    const int64_t want = (int64_t)256 * 2048 / threads;   // workgroups that fill the GPU once
+static int hydro_chunk(int nz, int64_t tiles, int threads, int fill) {
+    const int64_t want = (int64_t)256 * fill / threads;   // workgroups that fill the GPU once
     const int64_t kz = nz * tiles / want;
     return (int)(kz < 2 ? 2 : kz > 32 ? 32 : kz);
 }
@@ -83,66 +86,107 @@ __device__ __forceinline__ int reach(const HGeo& g, int d, int q) {
     return q < 0 ? 0 : (q >= n ? n - 1 : q);
 }
 
-// Column tiles: 32 x 8 columns (whole 256-byte lines in x, and the fewest halo cells that leaves), chunks of kz
-// planes, one thread per column. The hardware hands workgroup L to XCD L % 8; the tiles are numbered so that
-// each XCD takes one contiguous range of them (whole x-y planes of chunks), which keeps the halo rows
-// of a tile in the L2 of the XCD that reads them.
+// How a pass takes a box, by column tiles and chunks of kz planes, one thread per column. FORM_BOX: tiles of 32 x 8 columns
+// (whole 256-byte lines in x, and the fewest halo cells that leaves). 1 .. kFlatRows: boxes of so many rows, 64 columns by
+// all of them, whose y neighbours are in the tile itself (most rows of a 32 x 8 tile would repeat what
+// others do: 1024 x 1 x 1024 cells take 23, 21 and 28 us so in right-hand side, update and advection, 77, 78 and 102
+// there; 1024 x 4 x 1024 96, 97 and 105 instead of 119, 128 and 159; from five rows on 32 x 8 is no slower than the 64 x 4
+// columns, every neighbour from memory, were before). FORM_PLANE: 32 x 8 on a single plane, without the loads of z
+// neighbours (4096 x 4096 x 1: right-hand side and update 308 and 349 us, 493 and 509 with them; the advection, for which it
+// makes no difference, takes such a plane as a box).
+constexpr int FORM_BOX = 0, kFlatRows = 4, FORM_PLANE = 5;
+constexpr int kTileX = 32, kTileY = 8, kFlatX = 64;
+
+static int form_of(const int n[3]) { return n[1] <= kFlatRows ? n[1] : n[2] == 1 ? FORM_PLANE : FORM_BOX; }
+constexpr int rows_of(int form) { return form >= 1 && form <= kFlatRows ? form : 0; }  // 0: 32 x 8
+constexpr int threads_of(int form) { return rows_of(form) ? kFlatX * rows_of(form) : kTileX * kTileY; }
+
+// go(the form of the box n as a constant)
+template <typename F>
+static void with_form(const int n[3], F&& go) {
+    switch (form_of(n)) {
+        case 1: go(std::integral_constant<int, 1>{}); break;
+        case 2: go(std::integral_constant<int, 2>{}); break;
+        case 3: go(std::integral_constant<int, 3>{}); break;
+        case 4: go(std::integral_constant<int, 4>{}); break;
+        case FORM_PLANE: go(std::integral_constant<int, FORM_PLANE>{}); break;
+        default: go(std::integral_constant<int, FORM_BOX>{}); break;
+    }
+}
+
+// The hardware hands workgroup L to XCD L % 8; the tiles are numbered so that each XCD takes one contiguous range of them
+// (whole x-y planes of chunks), which keeps the halo rows of a tile in the L2 of the XCD that reads them.
 struct HTiles {
     int tx, ty, tz, kz;
 };
-constexpr int kTileX = 32, kTileY = 8, kTileThreads = kTileX * kTileY;
 
 static HTiles htiles(const int n[3]) {
-    const int tx = (n[0] + kTileX - 1) / kTileX, ty = (n[1] + kTileY - 1) / kTileY;
-    const int kz = hydro_chunk(n[2], (int64_t)tx * ty, kTileThreads);
+    const int form = form_of(n), w = rows_of(form) ? kFlatX : kTileX, r = rows_of(form) ? rows_of(form) : kTileY;
+    const int tx = (n[0] + w - 1) / w, ty = (n[1] + r - 1) / r;
+    const int kz = hydro_chunk(n[2], (int64_t)tx * ty, threads_of(form), rows_of(form) ? 1024 : 2048);
     return HTiles{tx, ty, (n[2] + kz - 1) / kz, kz};
 }
 
 // A thread's place in its tile with a halo of H cells, and the halo cell that it brings. Positions past the end of
 // an axis hold what its last cells see there (their halo); nothing past those is read by a cell of the grid.
-template <int H>
+template <int H, int FORM>
 struct Place {
-    static constexpr int PX = kTileX + 2 * H, PY = kTileY + 2 * H;
-    static_assert(2 * H * (kTileX + kTileY) <= kTileThreads, "one halo cell per thread");
+    static constexpr int NY = rows_of(FORM), TX = NY ? kFlatX : kTileX, PX = TX + 2 * H;
+    static constexpr int cells = PX * (NY ? NY : kTileY + 2 * H);  // of a plane of the tile
+    static_assert(NY || 2 * H * (kTileX + kTileY) <= threads_of(FORM), "one halo cell per thread");
     int i, j, k0, k1;
     int own, hcell;     // columns of the plane: the thread's, its halo cell's
     int at, hat;        // their places in the tile
     bool halo, beside;  // it brings a halo cell; one left or right of the tile (else below or above)
     bool inside, xl, xh, yl, yh;  // the column is one of the grid's; its faces exist
+    int yo[2 * H];      // all rows in the tile: from `at` to the y neighbours -H .. -1, 1 .. H
     __device__ __forceinline__ Place(const HGeo& g, const HTiles& t) {
         const unsigned total = (unsigned)t.tx * t.ty * t.tz;
         unsigned L = blockIdx.x;
         if ((total & 7u) == 0) L = (L & 7u) * (total >> 3) + (L >> 3);
-        const int x0 = (int)(L % (unsigned)t.tx) * kTileX, y0 = (int)((L / (unsigned)t.tx) % (unsigned)t.ty) * kTileY;
+        const int x0 = (int)(L % (unsigned)t.tx) * TX, y0 = NY ? 0 : (int)((L / (unsigned)t.tx) % (unsigned)t.ty) * kTileY;
         k0 = (int)(L / ((unsigned)t.tx * t.ty)) * t.kz;
         k1 = min(k0 + t.kz, g.n[2]);
-        const int tid = threadIdx.x, lx = tid % kTileX, ly = tid / kTileX, nx = g.n[0], ny = g.n[1];
+        const int tid = threadIdx.x, lx = tid % TX, ly = tid / TX, nx = g.n[0], ny = g.n[1];
         i = x0 + lx;
         j = y0 + ly;
         auto colx = [&](int q) { return reach(g, 0, min(q, nx + H - 1)); };
-        auto coly = [&](int q) { return reach(g, 1, min(q, ny + H - 1)); };
+        auto coly = [&](int q) { return NY ? q : reach(g, 1, min(q, ny + H - 1)); };
         own = colx(i) + nx * coly(j);
         int hx = 0, hy = 0;
-        beside = tid >= 2 * H * kTileX;
-        halo = tid < 2 * H * (kTileX + kTileY);
-        if (!beside) {
-            const int r = tid / kTileX;
-            hx = lx;
-            hy = r < H ? r - H : kTileY + r - H;
-        } else if (halo) {
-            const int q = tid - 2 * H * kTileX, c = q % (2 * H);
-            hx = c < H ? c - H : kTileX + c - H;
-            hy = q / (2 * H);
+        if constexpr (NY) {
+            beside = true;
+            halo = lx < 2 * H;
+            hx = lx < H ? lx - H : TX + lx - H;
+            hy = ly;
+            at = ly * PX + lx + H;
+            hat = ly * PX + hx + H;
+#pragma unroll
+            for (int q = 0; q < 2 * H; ++q) yo[q] = NY > 1 ? (reach(g, 1, j + (q < H ? q - H : q - H + 1)) - j) * PX : 0;
+        } else {
+            beside = tid >= 2 * H * kTileX;
+            halo = tid < 2 * H * (kTileX + kTileY);
+            if (!beside) {
+                const int r = tid / kTileX;
+                hx = lx;
+                hy = r < H ? r - H : kTileY + r - H;
+            } else if (halo) {
+                const int q = tid - 2 * H * kTileX, c = q % (2 * H);
+                hx = c < H ? c - H : kTileX + c - H;
+                hy = q / (2 * H);
+            }
+            hat = (hy + H) * PX + hx + H;
+            at = (ly + H) * PX + lx + H;
         }
         hcell = colx(x0 + hx) + nx * coly(y0 + hy);
-        hat = (hy + H) * PX + hx + H;
-        at = (ly + H) * PX + lx + H;
         inside = i < nx && j < ny;
         xl = g.per[0] || i > 0;
         xh = g.per[0] || i < nx - 1;
         yl = g.per[1] || j > 0;
         yh = g.per[1] || j < ny - 1;
     }
+    // from `at` to the y neighbour d rows on
+    __device__ __forceinline__ int y(int d) const { return NY ? yo[d < 0 ? d + H : d + H - 1] : d * PX; }
 };
 
 // What a cell of the rhs reads at its neighbours, one value of it per array; of the momentum mom_star the
@@ -167,11 +211,12 @@ __device__ __forceinline__ RhsFace rhs_face(bool face, const RhsCell& a, const R
 // the high one of the plane before. Bound by memory: 375 us at 256^3 for 80 B read and 8 written per cell;
 // 414 us with every neighbour from memory, the planes of 8 workgroups per CU thrashing the L2.
 // TC: the two-component terms (temp_n, conc_n, rkc_n given); VISC: the viscous term (visc given).
-template <bool TC, bool VISC>
-__global__ __launch_bounds__(kTileThreads) void k_pressure_rhs(HGeo g, HTiles t, RhsArgs A) {
-    using P = Place<1>;
+template <bool TC, bool VISC, int FORM>
+__global__ __launch_bounds__(threads_of(FORM), TC ? (VISC && rows_of(FORM) ? 2 : 3) : 4) void k_pressure_rhs(HGeo g, HTiles t, RhsArgs A) {
+    using P = Place<1, FORM>;
+    constexpr bool Z = FORM != FORM_PLANE;
     constexpr int NA = TC ? 7 : 5;  // p, rho_n, rho_np1, mom_star x and y, conc, rkc
-    __shared__ double tile[2][NA][P::PY * P::PX];
+    __shared__ double tile[2][NA][P::cells];
     const P o(g, t);
     const int nz = g.n[2];
     const int64_t sxy = (int64_t)g.n[0] * g.n[1];
@@ -212,14 +257,14 @@ __global__ __launch_bounds__(kTileThreads) void k_pressure_rhs(HGeo g, HTiles t,
     };
     auto along = [&](const Own& v, int d) { return RhsCell{v.p, v.rn, v.r1, v.m[d], TC ? v.c : 0.0, TC ? v.k : 0.0}; };
     Own q0, q1, q2;
-    load(q2, o.k0 - 1);
+    if (Z) load(q2, o.k0 - 1);
     load(q0, o.k0);
-    load(q1, o.k0 + 1);
+    if (Z) load(q1, o.k0 + 1);
     if (o.halo) load_halo(o.k0);
-    RhsFace zlo = rhs_face<TC>(nz > 1 && (g.per[2] || o.k0 > 0), along(q2, 2), along(q0, 2), q0.p, ih[2]);
+    RhsFace zlo = rhs_face<TC>(Z && nz > 1 && (g.per[2] || o.k0 > 0), along(q2, 2), along(q0, 2), q0.p, ih[2]);
     // one plane from v, its own values, and w, the next one's; x then takes plane k + 2
     auto plane = [&](int k, const Own& v, const Own& w, Own& x) {
-        double(*s)[P::PY * P::PX] = tile[k & 1];
+        double(*s)[P::cells] = tile[k & 1];
         const RhsCell mine = along(v, 0);
         s[0][o.at] = v.p;
         s[1][o.at] = v.rn;
@@ -241,8 +286,8 @@ __global__ __launch_bounds__(kTileThreads) void k_pressure_rhs(HGeo g, HTiles t,
             }
         }
         __syncthreads();  // (the other slot's readers passed the previous plane's barrier)
-        load(x, k + 2);
-        if (o.halo) load_halo(min(k + 1, o.k1 - 1));
+        if (Z) load(x, min(k + 2, o.k1));
+        if (Z && o.halo) load_halo(min(k + 1, o.k1 - 1));
         auto cell_at = [&](int d, int off) {
             const int q = o.at + off;
             return RhsCell{s[0][q], s[1][q], s[2][q], s[3 + d][q], TC ? s[NA - 2][q] : 0.0, TC ? s[NA - 1][q] : 0.0};
@@ -258,8 +303,8 @@ __global__ __launch_bounds__(kTileThreads) void k_pressure_rhs(HGeo g, HTiles t,
         // (an axis of one cell has no faces: its lines contribute exact zeros)
         axis(rhs_face<TC>(o.xl, cell_at(0, -1), mine, v.p, ih[0]), rhs_face<TC>(o.xh, mine, cell_at(0, 1), v.p, ih[0]), 0);
         const RhsCell my = along(v, 1);
-        axis(rhs_face<TC>(o.yl, cell_at(1, -P::PX), my, v.p, ih[1]), rhs_face<TC>(o.yh, my, cell_at(1, P::PX), v.p, ih[1]), 1);
-        const RhsFace zhi = rhs_face<TC>(nz > 1 && (g.per[2] || k < nz - 1), along(v, 2), along(w, 2), v.p, ih[2]);
+        axis(rhs_face<TC>(o.yl, cell_at(1, o.y(-1)), my, v.p, ih[1]), rhs_face<TC>(o.yh, my, cell_at(1, o.y(1)), v.p, ih[1]), 1);
+        const RhsFace zhi = rhs_face<TC>(Z && nz > 1 && (g.per[2] || k < nz - 1), along(v, 2), along(w, 2), v.p, ih[2]);
         axis(zlo, zhi, 2);
         zlo = zhi;
         double b = m * (v.p - g.dt * adv) - g.dt * divu;
@@ -300,9 +345,11 @@ __device__ __forceinline__ UpdFace upd_face(bool face, const UpdCell& a, const U
 
 // The updates after the solve by tiles, as in k_pressure_rhs. Bound by memory: 396 us at 256^3 for 48 B read and 56
 // written per cell; 472 us with every neighbour from memory.
-__global__ __launch_bounds__(kTileThreads) void k_pressure_update(HGeo g, HTiles t, UpdArgs A) {
-    using P = Place<1>;
-    __shared__ double tile[2][4][P::PY * P::PX];  // p, rho, mom_star x and y
+template <int FORM>
+__global__ __launch_bounds__(threads_of(FORM)) void k_pressure_update(HGeo g, HTiles t, UpdArgs A) {
+    using P = Place<1, FORM>;
+    constexpr bool Z = FORM != FORM_PLANE;
+    __shared__ double tile[2][4][P::cells];  // p, rho, mom_star x and y
     const P o(g, t);
     const int nz = g.n[2];
     const int64_t sxy = (int64_t)g.n[0] * g.n[1];
@@ -325,13 +372,13 @@ __global__ __launch_bounds__(kTileThreads) void k_pressure_update(HGeo g, HTiles
     };
     auto along = [&](const Own& v, int d) { return UpdCell{v.p, v.r, v.m[d]}; };
     Own q0, q1, q2;
-    load(q2, o.k0 - 1);
+    if (Z) load(q2, o.k0 - 1);
     load(q0, o.k0);
-    load(q1, o.k0 + 1);
+    if (Z) load(q1, o.k0 + 1);
     if (o.halo) load_halo(o.k0);
-    UpdFace zlo = upd_face(nz > 1 && (g.per[2] || o.k0 > 0), along(q2, 2), along(q0, 2), q0.p, g.dt, ih[2]);
+    UpdFace zlo = upd_face(Z && nz > 1 && (g.per[2] || o.k0 > 0), along(q2, 2), along(q0, 2), q0.p, g.dt, ih[2]);
     auto plane = [&](int k, const Own& v, const Own& w, Own& x) {
-        double(*s)[P::PY * P::PX] = tile[k & 1];
+        double(*s)[P::cells] = tile[k & 1];
         s[0][o.at] = v.p;
         s[1][o.at] = v.r;
         s[2][o.at] = v.m[0];
@@ -342,8 +389,8 @@ __global__ __launch_bounds__(kTileThreads) void k_pressure_update(HGeo g, HTiles
             s[o.beside ? 2 : 3][o.hat] = h.ms;
         }
         __syncthreads();  // (the other slot's readers passed the previous plane's barrier)
-        load(x, k + 2);
-        if (o.halo) load_halo(min(k + 1, o.k1 - 1));
+        if (Z) load(x, min(k + 2, o.k1));
+        if (Z && o.halo) load_halo(min(k + 1, o.k1 - 1));
         auto cell_at = [&](int d, int off) { return UpdCell{s[0][o.at + off], s[1][o.at + off], s[2 + d][o.at + off]}; };
         double gp[3], uf[3], divn = 0.0;
         auto axis = [&](const UpdFace& lo, const UpdFace& hi, int d) {
@@ -354,9 +401,9 @@ __global__ __launch_bounds__(kTileThreads) void k_pressure_update(HGeo g, HTiles
         // (an axis of one cell has no faces and its terms are exact zeros)
         const UpdCell mx = along(v, 0), my = along(v, 1);
         axis(upd_face(o.xl, cell_at(0, -1), mx, v.p, g.dt, ih[0]), upd_face(o.xh, mx, cell_at(0, 1), v.p, g.dt, ih[0]), 0);
-        axis(upd_face(o.yl, cell_at(1, -P::PX), my, v.p, g.dt, ih[1]),
-             upd_face(o.yh, my, cell_at(1, P::PX), v.p, g.dt, ih[1]), 1);
-        const UpdFace zhi = upd_face(nz > 1 && (g.per[2] || k < nz - 1), along(v, 2), along(w, 2), v.p, g.dt, ih[2]);
+        axis(upd_face(o.yl, cell_at(1, o.y(-1)), my, v.p, g.dt, ih[1]),
+             upd_face(o.yh, my, cell_at(1, o.y(1)), v.p, g.dt, ih[1]), 1);
+        const UpdFace zhi = upd_face(Z && nz > 1 && (g.per[2] || k < nz - 1), along(v, 2), along(w, 2), v.p, g.dt, ih[2]);
         axis(zlo, zhi, 2);
         zlo = zhi;
         // step (vii): momentum; step (ix): e^{n+1} = e* - dt (P div u^{n+1} + u^{n+1} . grad P)
@@ -428,10 +475,11 @@ struct AdvArgs {
 // memory: 380 us at 256^3 for 1.4 GB read (the halo rows come from beyond the L2 as often as not)
 // and 0.67 GB written; one thread per cell, with every neighbour from memory and every flux
 // twice, took 1041 us. Tiles of 512 threads left one workgroup per CU (510 us) or spilled.
-__global__ __launch_bounds__(kTileThreads, 3) void k_advect(HGeo g, HTiles t, AdvArgs A) {
-    constexpr int PX = Place<2>::PX, PY = Place<2>::PY;
-    __shared__ double tile[2][5][PY * PX];
-    const Place<2> o(g, t);
+template <int FORM>
+__global__ __launch_bounds__(threads_of(FORM), 3) void k_advect(HGeo g, HTiles t, AdvArgs A) {
+    using P = Place<2, FORM>;
+    __shared__ double tile[2][5][P::cells];
+    const P o(g, t);
     const int k0 = o.k0, k1 = o.k1, own = o.own, at = o.at, hat = o.hat, hcell = o.hcell, nz = g.n[2];
     const bool halo = o.halo, xl = o.xl, xh = o.xh, yl = o.yl, yh = o.yh, inside = o.inside;
     const int64_t sxy = (int64_t)g.n[0] * g.n[1];
@@ -463,7 +511,7 @@ __global__ __launch_bounds__(kTileThreads, 3) void k_advect(HGeo g, HTiles t, Ad
     // one plane from v0 .. v3, planes k-1 .. k+2 of the own column; v0 then takes plane k+3, so that
     // the ring turns by the names below and nothing is copied
     auto plane = [&](int k, double* v0, double* v1, double* v2, double* v3) {
-        double(*p)[PY * PX] = tile[k & 1];
+        double(*p)[P::cells] = tile[k & 1];
 #pragma unroll
         for (int f = 0; f < 5; ++f) {
             p[f][at] = v1[f];
@@ -472,17 +520,19 @@ __global__ __launch_bounds__(kTileThreads, 3) void k_advect(HGeo g, HTiles t, Ad
         __syncthreads();  // (the other slot's readers passed the previous plane's barrier)
         load(hv, hcell, min(k + 1, k1 - 1));
         // interface velocities; zero on an axis of one cell, whose fluxes then cancel to zero
-        const double uxl = step1(xl, p[1][at - 1], v1[1], p[0][at - 1], v1[0]);
-        const double uxh = step1(xh, v1[1], p[1][at + 1], v1[0], p[0][at + 1]);
-        const double uyl = step1(yl, p[2][at - PX], v1[2], p[0][at - PX], v1[0]);
-        const double uyh = step1(yh, v1[2], p[2][at + PX], v1[0], p[0][at + PX]);
+        const double *r = p[0] + at, *mx = p[1] + at, *my = p[2] + at;
+        const int yl1 = o.y(-1), yh1 = o.y(1), yl2 = o.y(-2), yh2 = o.y(2);
+        const double uxl = step1(xl, mx[-1], v1[1], r[-1], v1[0]);
+        const double uxh = step1(xh, v1[1], mx[1], v1[0], r[1]);
+        const double uyl = step1(yl, my[yl1], v1[2], r[yl1], v1[0]);
+        const double uyh = step1(yh, v1[2], my[yh1], v1[0], r[yh1]);
         const double uzh = step1(g.per[2] || k < nz - 1, v1[3], v2[3], v1[0], v2[0]);
-        const int64_t a = own + (int64_t)k * sxy, an = own + (int64_t)reach(g, 2, k + 3) * sxy;
+        const int64_t a = own + (int64_t)k * sxy, an = own + (int64_t)reach(g, 2, min(k + 3, k1 + 1)) * sxy;
 #pragma unroll
         for (int f = 0; f < 5; ++f) {
             const double* c = p[f] + at;
             double div = axis_div(uxl, uxh, c[-2], c[-1], v1[f], c[1], c[2]) * ih[0];
-            div += axis_div(uyl, uyh, c[-2 * PX], c[-PX], v1[f], c[PX], c[2 * PX]) * ih[1];
+            div += axis_div(uyl, uyh, c[yl2], c[yl1], v1[f], c[yh1], c[yh2]) * ih[1];
             const double d1 = v2[f] - v1[f];
             const double fh = eno_flux(uzh, v1[f], eno_slope(v1[f] - v0[f], d1), v2[f], eno_slope(d1, v3[f] - v2[f]));
             v0[f] = A.q[f][an];
@@ -532,7 +582,10 @@ int hydro_launch_advect(const int n[3], const int bc[3], const double h[3], doub
     const int64_t N = (int64_t)n[0] * n[1] * n[2];
     AdvArgs A{{rho, mom, mom + N, mom + 2 * N, e}, {rho_out, mom_out, mom_out + N, mom_out + 2 * N, e_out}};
     const HTiles t = htiles(n);
-    hipLaunchKernelGGL(k_advect, dim3((unsigned)((int64_t)t.tx * t.ty * t.tz)), dim3(kTileThreads), 0, s, g, t, A);
+    with_form(n, [&](auto form) {
+        constexpr int F = decltype(form)::value == FORM_PLANE ? FORM_BOX : decltype(form)::value;
+        hipLaunchKernelGGL(k_advect<F>, dim3((unsigned)((int64_t)t.tx * t.ty * t.tz)), dim3(threads_of(F)), 0, s, g, t, A);
+    });
     return hipGetLastError() == hipSuccess ? HP_OK : HP_EHIP;
 }
 
@@ -554,15 +607,20 @@ int hydro_launch_rhs(const int n[3], const int bc[3], const double h[3], double 
     RhsArgs A{f->rho_n, f->c2_n, f->p_n, f->mom_n, f->rho_np1, f->mom_star, f->visc, f->temp_n, f->conc_n,
               f->rkc_n, f->r_gas, (int64_t)n[0] * n[1] * n[2], rhs};
     const HTiles t = htiles(n);
-    const dim3 grid((unsigned)t.tx * t.ty * t.tz);
-    if (f->temp_n && f->visc)
-        hipLaunchKernelGGL((k_pressure_rhs<true, true>), grid, dim3(kTileThreads), 0, s, g, t, A);
-    else if (f->temp_n)
-        hipLaunchKernelGGL((k_pressure_rhs<true, false>), grid, dim3(kTileThreads), 0, s, g, t, A);
-    else if (f->visc)
-        hipLaunchKernelGGL((k_pressure_rhs<false, true>), grid, dim3(kTileThreads), 0, s, g, t, A);
-    else
-        hipLaunchKernelGGL((k_pressure_rhs<false, false>), grid, dim3(kTileThreads), 0, s, g, t, A);
+    auto go = [&](auto tc, auto visc) {
+        constexpr bool TC = decltype(tc)::value, VISC = decltype(visc)::value;
+        with_form(n, [&](auto form) {
+            constexpr int F = decltype(form)::value;
+            hipLaunchKernelGGL((k_pressure_rhs<TC, VISC, F>), dim3((unsigned)t.tx * t.ty * t.tz), dim3(threads_of(F)), 0, s,
+                               g, t, A);
+        });
+    };
+    using Yes = std::true_type;
+    using No = std::false_type;
+    if (f->temp_n && f->visc) go(Yes{}, Yes{});
+    else if (f->temp_n) go(Yes{}, No{});
+    else if (f->visc) go(No{}, Yes{});
+    else go(No{}, No{});
     return hipGetLastError() == hipSuccess ? HP_OK : HP_EHIP;
 }
 
@@ -578,7 +636,10 @@ int hydro_launch_update(const int n[3], const int bc[3], const double h[3], doub
     UpdArgs A{f->p, f->rho_np1, f->mom_star, f->e_star, f->mom_out, f->uface_out, f->e_out,
               (int64_t)n[0] * n[1] * n[2]};
     const HTiles t = htiles(n);
-    hipLaunchKernelGGL(k_pressure_update, dim3((unsigned)t.tx * t.ty * t.tz), dim3(kTileThreads), 0, s, g, t, A);
+    with_form(n, [&](auto form) {
+        constexpr int F = decltype(form)::value;
+        hipLaunchKernelGGL(k_pressure_update<F>, dim3((unsigned)t.tx * t.ty * t.tz), dim3(threads_of(F)), 0, s, g, t, A);
+    });
     return hipGetLastError() == hipSuccess ? HP_OK : HP_EHIP;
 }
 
