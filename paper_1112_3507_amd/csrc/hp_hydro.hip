@@ -65,16 +65,16 @@ struct RhsArgs {
     double* b;
 };
 
-// z planes per chunk of a pass with `tiles` column tiles per plane and `threads` threads per
-// workgroup: up to 32, fewer (not under 2) where the launch would leave the 256 CUs short of `fill`
-// threads each: 2048, and 1024 for tiles that have all rows (1 x 4 x 4096 cells, every term of the right-hand side: 22 us
-// so, 25 with 2048). A chunk loads its first planes' z neighbours again, so longer ones read less; at
-// 96 x 80 x 72 chunks of 16, 2 (this rule) and 1 planes took 28, 20 and 24 us for the right-hand side with every
-// term, 26, 17 and 18 for the update, and 34, 22 and 26 for the advection.
-static int hydro_chunk(int nz, int64_t tiles, int threads, int fill) {
-    const int64_t want = (int64_t)256 * fill / threads;   // workgroups that fill the GPU once
-    const int64_t kz = nz * tiles / want;
-    return (int)(kz < 2 ? 2 : kz > 32 ? 32 : kz);
+// z planes per chunk of a pass with `tiles` column tiles of `threads` threads per plane. A chunk loads its first planes' z
+// neighbours again, so longer ones read less, and there have to be enough of them for 256 CUs. Counted in
+// workgroups of 256 threads, two per CU are enough from 4096 tiles' planes on (kz = 8; right-hand side at 256 x 256 x 32: 16
+// planes 40 us, 8 43, 4 47); below that kz is at most 3, and at least 2 (96 x 80 x 72: 1, 2, 4 and 16 planes take 24, 17, 19 and 24
+// us there). More than 16 planes pay only where eight workgroups per CU remain (256^3, advection: 32 planes 406 us, 16
+// 424; 192^3: 199 and 195).
+static int hydro_chunk(int nz, int64_t tiles, int threads) {
+    const int64_t planes = nz * tiles * threads / 256;
+    const int64_t kz = planes >= 4096 ? (planes < 512 * 16 ? planes / 512 : 16) : planes / 1024;
+    return (int)(kz < 2 ? 2 : planes / 2048 < kz ? kz : planes / 2048 > 32 ? 32 : planes / 2048);
 }
 
 // the cell that stands at coordinate q along axis d, up to a few past either end: wrapped on a
@@ -89,8 +89,8 @@ __device__ __forceinline__ int reach(const HGeo& g, int d, int q) {
 // How a pass takes a box, by column tiles and chunks of kz planes, one thread per column. FORM_BOX: tiles of 32 x 8 columns
 // (whole 256-byte lines in x, and the fewest halo cells that leaves). 1 .. kFlatRows: boxes of so many rows, 64 columns by
 // all of them, whose y neighbours are in the tile itself (most rows of a 32 x 8 tile would repeat what
-// others do: 1024 x 1 x 1024 cells take 23, 21 and 28 us so in right-hand side, update and advection, 77, 78 and 102
-// there; 1024 x 4 x 1024 96, 97 and 105 instead of 119, 128 and 159; from five rows on 32 x 8 is no slower than the 64 x 4
+// others do: 1024 x 1 x 1024 cells take 21, 20 and 27 us so in right-hand side, update and advection, 77, 78 and 102
+// there; 1024 x 4 x 1024 96, 98 and 112 instead of 119, 128 and 159; from five rows on 32 x 8 is no slower than the 64 x 4
 // columns, every neighbour from memory, were before). FORM_PLANE: 32 x 8 on a single plane, without the loads of z
 // neighbours (4096 x 4096 x 1: right-hand side and update 308 and 349 us, 493 and 509 with them; the advection, for which it
 // makes no difference, takes such a plane as a box).
@@ -123,7 +123,7 @@ struct HTiles {
 static HTiles htiles(const int n[3]) {
     const int form = form_of(n), w = rows_of(form) ? kFlatX : kTileX, r = rows_of(form) ? rows_of(form) : kTileY;
     const int tx = (n[0] + w - 1) / w, ty = (n[1] + r - 1) / r;
-    const int kz = hydro_chunk(n[2], (int64_t)tx * ty, threads_of(form), rows_of(form) ? 1024 : 2048);
+    const int kz = hydro_chunk(n[2], (int64_t)tx * ty, threads_of(form));
     return HTiles{tx, ty, (n[2] + kz - 1) / kz, kz};
 }
 

@@ -3,7 +3,7 @@
 Every number of such rows, closed and periodic (two rows: a cell's both neighbours are the same one, and the advection
 reaches round to the cell itself), x of one cell, one tile of 64 columns, one cell short of it and over it, and of three
 tiles; z of one plane, a chunk of two, and chunks with a remainder. Planes (more rows, nz = 1) with tiles of 32 x 8 cut
-by the box. Reference and bound as in test_gpu_hydro_tiles: 64 units in the last place of the largest term.
+by the box. Then boxes at the edges of the rule for the length of chunks. Reference and bound as in test_gpu_hydro_tiles: 64 units in the last place of the largest term.
 """
 import numpy as np
 import pytest
@@ -23,6 +23,8 @@ BOXES = [((64, 1, 7), (P, P, N)), ((65, 1, 1), (N, P, N)), ((1, 1, 9), (P, P, N)
          ((64, 3, 1), (P, N, N)), ((1, 3, 4), (P, N, N)), ((66, 4, 6), (P, P, P)), ((65, 4, 3), (N, N, N)),
          ((3, 4, 5), (N, P, N)), ((34, 10, 1), (P, P, P)), ((33, 5, 1), (N, N, N)), ((64, 17, 1), (P, N, P)),
          ((64, 4, 300), (P, P, N))]
+# where chunks get longer: 4096 planes of tiles (8 to a chunk), some more with a remainder, 16 to a chunk with one
+CHUNKS = [((64, 64, 256), (P, P, N)), ((96, 80, 148), (P, P, N)), ((128, 64, 260), (P, N, N)), ((1024, 4, 522), (P, P, N))]
 
 
 def _close(got, ref, scale):
@@ -31,7 +33,7 @@ def _close(got, ref, scale):
     assert np.max(np.abs(got - ref)) <= 64 * EPS * scale
 
 
-@pytest.mark.parametrize("n,bc", BOXES)
+@pytest.mark.parametrize("n,bc", BOXES + CHUNKS)
 def test_passes_match_formulas(n, bc):
     rng = np.random.default_rng(sum(n))
     shape = n[::-1]
