@@ -110,10 +110,10 @@ struct hp_handle {
     hipStream_t side = nullptr;
     hipEvent_t ev_fork = nullptr, ev_join = nullptr;
     unsigned dir = 0;              // traversal direction of the last finest-level pass
-    // One-launch V-cycles and solves (hp_small.hip): the level from which a V-cycle runs in one launch
-    // (the number of levels if none), the launch's shape, its level tables, counters, exchange and
-    // the result of a solve (mapped host memory)
-    int small_from = 0;
+    // One-launch V-cycles and solves (hp_small.hip): the level from which they may run (the number of levels if
+    // none), and from which a V-cycle does (a whole solve is one launch where small.lds_cg says so), the launch's shape, its
+    // level tables, counters, exchange and the result of a solve (mapped host memory)
+    int small_from = 0, cycle_from = 0;
     int small_polls = kBarrierPolls;
     SmallShape small{};
     SmallTable* small_tab = nullptr;
@@ -560,7 +560,7 @@ bool vcycle(hp_handle* H, int l, const T* r, T* z, const RedCtl* dot = nullptr, 
         return false;
     }
     if constexpr (sizeof(T) == 8) {
-        if (l == H->small_from && !pre_done) {
+        if (l == H->cycle_from && !pre_done) {
             launch_small(small_args(H, r, z), false, H->small, s);
             return false;
         }
@@ -831,10 +831,12 @@ void next_direction32(hp_handle* H, bool pre_done = false) {
 // launches, and with them the rounding of its FP32 cycles. Above 512 coarsest cells (odd sizes stop the
 // coarsening early) the helpers' registers don't hold the inverse, and under larger levels the coarsest
 // solve's own launch is the faster (224 x 80 x 44 cells with 1540: 2290 us against 2220); a whole solve
-// still gains (63 x 1 x 62 with 1953: 384 us against 640).
+// still gains (63 x 1 x 62 with 1953: 384 us against 640), and so does a V-cycle of its own up to 1024 of them, one turn
+// of two rows for every helper wave (66 x 1 x 62 with 1023: 25 us against 28; 45 x 1 x 50 with 1125 30 against 28, 63 x 1 x 62
+// 38 against 30).
 int setup_small(hp_handle* H) {
     const int levels = (int)H->lv.size();
-    H->small_from = levels;
+    H->small_from = H->cycle_from = levels;
     int64_t below = 0;  // LDS values of the levels under the first
     for (int l = levels - 2; l >= 0 && levels - l <= kSmallLevels; --l) {
         const LevelData& L = H->lv[l];
@@ -844,6 +846,7 @@ int setup_small(hp_handle* H) {
         const bool whole = l == 0 && (4 * L.N + below) * (int64_t)sizeof(double) <= kSmallLds;
         if (H->nc > 512 && !whole) continue;
         H->small_from = l;
+        if (H->nc <= 1024) H->cycle_from = l;
         H->small.per_thread = (int)((items + kSmallThreads - 1) / kSmallThreads);
         H->small.lds_cycle = (int)(2 * L.N + below);
         H->small.lds_cg = whole ? (int)(4 * L.N + below) : 0;
