@@ -317,6 +317,7 @@ __global__ __launch_bounds__(256) void k_conv_fwd(ConvArgs p) {
     if constexpr (OUT == OUT_CONCAT) {
         // The children of a coarse voxel sit in two lanes (x), two rows (y) and two waves (z, handed
         // over through LDS); they are added one after the other, x fastest.
+        static_assert(2 * 4 * CU * 64 <= FHV * G, "in the place of the staged brick");
         __syncthreads();
         f32x4* odd = (f32x4*)lds + (wave >> 1) * (4 * CU * 64);
         if (wave & 1) {
@@ -1075,6 +1076,7 @@ struct hp_net {
     hipStream_t side[kSides] = {};
     int turn = 0;
     hipEvent_t ready = nullptr, read[kGradBufs] = {};  // a gradient is written; gbuf[q] has been read
+    hipEvent_t test_event = nullptr;                   // (hp_test_nn_beside)
     bool reading[kGradBufs] = {};                      // read[q] has been recorded in this pass
     float *gskip0 = nullptr, *gskip1 = nullptr;  // gradients of e1 and e2 through their skip connections
     float *gp1 = nullptr, *gp2 = nullptr;        // gradients of the pooled tensors
@@ -1262,23 +1264,27 @@ int rhs_scale(hp_net* N, const double* b) {
     return check();
 }
 
-// The buffer for the next masked gradient, once nothing reads it any more.
-int next_gradient(hp_net* N) {
-    const int q = (N->cur + 1) % (N->beside ? kGradBufs : 2);
-    if (N->reading[q]) (void)hipStreamWaitEvent(N->stream, N->read[q], 0);
-    return q;
+// Orders between the network's stream and those of the weight gradients. Without one, what follows would race: a pass in
+// which one fails launches nothing more (see backward_net).
+int record(hipEvent_t e, hipStream_t s) { return hipEventRecord(e, s) == hipSuccess ? HP_OK : nfail(HP_EHIP, "event record failed"); }
+int wait_for(hipStream_t s, hipEvent_t e) { return hipStreamWaitEvent(s, e, 0) == hipSuccess ? HP_OK : nfail(HP_EHIP, "event wait failed"); }
+
+// The buffer *q for the next masked gradient, once nothing reads it any more.
+int next_gradient(hp_net* N, int* q) {
+    *q = (N->cur + 1) % (N->beside ? kGradBufs : 2);
+    return N->reading[*q] ? wait_for(N->stream, N->read[*q]) : HP_OK;
 }
 
 // Weight gradient of layer l from its masked output gradient, beside what follows on the network's stream: its
 // workgroups are few (96 at 16 -> 16 channels) and each brick waits for the one before. A step at 128^3
 // takes 1941 us so, 2238 in one stream (2105 with one stream for them and three buffers).
-void weight_gradient(hp_net* N, int l) {
+int weight_gradient(hp_net* N, int l) {
     hipStream_t side = N->stream;
+    int rc;
     if (N->beside) {
         N->turn = (N->turn + 1) % kSides;
         side = N->side[N->turn];
-        (void)hipEventRecord(N->ready, N->stream);
-        (void)hipStreamWaitEvent(side, N->ready, 0);
+        if ((rc = record(N->ready, N->stream)) || (rc = wait_for(side, N->ready))) return rc;
     }
     const Level& L = N->lv[level_of_conv(l)];
     const int co = COUT[l];
@@ -1292,10 +1298,9 @@ void weight_gradient(hp_net* N, int l) {
     const int n = co * 27 * CIN[l];
     hipLaunchKernelGGL(k_reduce_dw, dim3(nblk(n, 16)), dim3(256), 0, side, N->wpart[N->turn], parts, chunks, co, CIN[l],
                        N->grad + N->woff[l]);
-    if (N->beside) {
-        (void)hipEventRecord(N->read[N->cur], side);
-        N->reading[N->cur] = true;
-    }
+    if (!N->beside) return HP_OK;
+    N->reading[N->cur] = true;
+    return record(N->read[N->cur], side);
 }
 
 // out[0..c) = column sums of cpart[rows][stride] from column c0 on
@@ -1306,13 +1311,14 @@ void column_sums(hp_net* N, int rows, int stride, int c0, int c, float* out) {
 // Backward of layer l from its masked output gradient: its weight gradient, and the
 // gradient of its input (see conv_backward_data). Where that is the masked gradient of layer
 // l - 1's output, it becomes the current one and that layer's bias gradient is formed.
-void backward_conv(hp_net* N, int l, float* f32 = nullptr) {
-    weight_gradient(N, l);
-    if (l == 0) return;
+int backward_conv(hp_net* N, int l, float* f32 = nullptr) {
+    int rc = weight_gradient(N, l);
+    if (rc || l == 0) return rc;
     const bool pooled = l == 4 || l == 2;
-    const int q = pooled ? N->cur : next_gradient(N);
+    int q = N->cur;
+    if (!pooled && (rc = next_gradient(N, &q))) return rc;
     conv_backward_data(N, l, pooled ? nullptr : N->gbuf[q], f32);
-    if (pooled) return;
+    if (pooled) return HP_OK;
     const int64_t nv = N->lv[level_of_conv(l - 1)].nv;
     const unsigned rows = nblk(nv, kSumVox);
     const int c = COUT[l - 1];
@@ -1323,17 +1329,21 @@ void backward_conv(hp_net* N, int l, float* f32 = nullptr) {
     }
     column_sums(N, (int)rows, c, 0, c, N->grad + N->boff[l - 1]);
     N->cur = q;
+    return HP_OK;
 }
 
 // Masked gradient of the skip activation of layer l (1 or 3), now the current one, and its bias gradient.
-void backward_skip(hp_net* N, int l, const float* g, const float* gpool) {
+int backward_skip(hp_net* N, int l, const float* g, const float* gpool) {
     const Level& L = N->lv[level_of_conv(l)];
     const unsigned rows = nblk(L.nv, kSumVox);
     auto kernel = l == 1 ? k_relu_bwd_pool<16> : k_relu_bwd_pool<32>;
-    N->cur = next_gradient(N);
+    int q;
+    if (int rc = next_gradient(N, &q)) return rc;
+    N->cur = q;
     hipLaunchKernelGGL(kernel, dim3(rows), dim3(256), 0, N->stream, g, gpool, N->act[l], N->gbuf[N->cur], L.nx, L.ny, L.nv,
                        N->cpart);
     column_sums(N, (int)rows, COUT[l], 0, COUT[l], N->grad + N->boff[l]);
+    return HP_OK;
 }
 
 }  // namespace
@@ -1361,6 +1371,7 @@ void hp_nn_free(hp_net* N) {
             (void)hipStreamDestroy(t);
         }
     if (N->ready) (void)hipEventDestroy(N->ready);
+    if (N->test_event) (void)hipEventDestroy(N->test_event);
     for (hipEvent_t e : N->read)
         if (e) (void)hipEventDestroy(e);
     for (void* p : N->allocs) (void)hipFree(p);
@@ -1553,22 +1564,31 @@ int backward_net(hp_net* N) {
     column_sums(N, (int)rows, kHeadCols, 0, HEAD + 1, N->grad + N->hoff);
     column_sums(N, (int)rows, kHeadCols, HEAD + 1, HEAD, N->grad + N->boff[9]);
     // decoder and encoder in reverse
-    backward_conv(N, 9);
-    backward_conv(N, 8, N->gskip0);  // [up(act7), act1]
-    backward_conv(N, 7);
-    backward_conv(N, 6, N->gskip1);  // [up(act5), act3]
-    backward_conv(N, 5);
-    backward_conv(N, 4, N->gp2);
-    backward_skip(N, 3, N->gskip1, N->gp2);
-    backward_conv(N, 3);
-    backward_conv(N, 2, N->gp1);
-    backward_skip(N, 1, N->gskip0, N->gp1);
-    backward_conv(N, 1);
-    backward_conv(N, 0);
-    // what follows stands behind the weight gradients, too
-    for (hipStream_t t : N->side)
-        if (N->beside && (hipEventRecord(N->ready, t) != hipSuccess || hipStreamWaitEvent(N->stream, N->ready, 0) != hipSuccess))
-            return nfail(HP_EHIP, "event wait failed");
+    auto layers = [&]() -> int {
+        int rc;
+        if ((rc = backward_conv(N, 9))) return rc;
+        if ((rc = backward_conv(N, 8, N->gskip0))) return rc;  // [up(act7), act1]
+        if ((rc = backward_conv(N, 7))) return rc;
+        if ((rc = backward_conv(N, 6, N->gskip1))) return rc;  // [up(act5), act3]
+        if ((rc = backward_conv(N, 5))) return rc;
+        if ((rc = backward_conv(N, 4, N->gp2))) return rc;
+        if ((rc = backward_skip(N, 3, N->gskip1, N->gp2))) return rc;
+        if ((rc = backward_conv(N, 3))) return rc;
+        if ((rc = backward_conv(N, 2, N->gp1))) return rc;
+        if ((rc = backward_skip(N, 1, N->gskip0, N->gp1))) return rc;
+        if ((rc = backward_conv(N, 1))) return rc;
+        if ((rc = backward_conv(N, 0))) return rc;
+        // what follows stands behind the weight gradients, too
+        for (hipStream_t t : N->side)
+            if (N->beside && ((rc = record(N->ready, t)) || (rc = wait_for(N->stream, N->ready)))) return rc;
+        return HP_OK;
+    };
+    if (const int rc = layers()) {
+        for (hipStream_t t : N->side)
+            if (N->beside) (void)hipStreamSynchronize(t);
+        (void)hipGetLastError();  // reported by rc
+        return rc;
+    }
     return check();
 }
 
@@ -1624,6 +1644,17 @@ int hp_nn_loss_grad_raw(hp_net* N, const unsigned short* in, const float* target
         hipMemcpyAsync(N->t, target, V * sizeof(float), hipMemcpyDeviceToDevice, N->stream) != hipSuccess)
         return nfail(HP_EHIP, "input copy failed");
     return loss_grad(N, loss);
+}
+
+// Not part of the interface, for tests. how = 0: the weight gradients of a network that has streams for them run on its own
+// stream; 1: on those streams (as it is created); 2: the same with an event that can't be recorded. Between passes
+// only; returns whether the network has such streams.
+int hp_test_nn_beside(hp_net* N, int how) {
+    if (!N->side[0]) return 0;
+    if (!N->ready) std::swap(N->ready, N->test_event);
+    if (how == 2) std::swap(N->ready, N->test_event);
+    N->beside = how != 0;
+    return 1;
 }
 
 int hp_nn_adam(hp_net* N, float lr) {
