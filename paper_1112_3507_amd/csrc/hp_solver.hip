@@ -13,6 +13,7 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <new>
 #include <string>
 #include <utility>
 #include <vector>
@@ -1309,7 +1310,11 @@ int hp_setup_two_density(const hp_grid* grid, const double* rho_n, const double*
         }
     }
     const int per[3] = {H->bc.x == HP_BC_PERIODIC, H->bc.y == HP_BC_PERIODIC, H->bc.z == HP_BC_PERIODIC};
-    H->ainv_plan = plan_inverse(H->lv.back().n, per);
+    try {
+        H->ainv_plan = plan_inverse(H->lv.back().n, per);
+    } catch (const std::bad_alloc&) {
+        return bail(fail(HP_ENOMEM, "host allocation failed"));
+    }
     const InversePlan& plan = H->ainv_plan;
     if ((rc = dalloc(H, &H->ainv, (int64_t)H->nc * H->nc)) || (rc = dalloc(H, &H->ainv_work, plan.doubles)) ||
         (rc = dalloc(H, &H->ainv_tables, plan.ints)))
