@@ -23,6 +23,7 @@
 // also that of the columns. A step takes 9 to 11 us, 6 of them the 32 pivots of the next. New coefficients
 // take 225 us on 96 x 56 x 192 cells (504 coarsest ones) and 141 on 64 x 64 (256); with two launches per 32
 // pivots, swept one at a time through LDS (15 us), and every block on its own it was 475 and 265.
+#include "hp_device.h"
 #include "hp_internal.h"
 
 #include <algorithm>
@@ -163,22 +164,6 @@ struct InverseArgs {
     int* flag;
 };
 
-// 1/x from the hardware estimate and two Newton steps (within an ulp or so). A zero, infinite or
-// NaN pivot gives a result that is not finite; the pivot flag is taken from the pivot itself.
-__device__ __forceinline__ double rcp_nr(double x) {
-    double r = __builtin_amdgcn_rcp(x);
-    double e = __builtin_fma(-x, r, 1.0);
-    r = __builtin_fma(r, e, r);
-    e = __builtin_fma(-x, r, 1.0);
-    return __builtin_fma(r, e, r);
-}
-
-__device__ __forceinline__ double lane_value(double v, int lane) {
-    const uint64_t u = __builtin_bit_cast(uint64_t, v);
-    const unsigned lo = __builtin_amdgcn_readlane((unsigned)u, lane), hi = __builtin_amdgcn_readlane((unsigned)(u >> 32), lane);
-    return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
-}
-
 __device__ __forceinline__ f64x4 mfma(double a, double b, f64x4 c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0); }
 
 // The operator's entries (a[e], b), natural indices (-1: none): a lane's part of a tile's quadrant. On a diagonal
@@ -230,17 +215,18 @@ __device__ __forceinline__ bool sweep_32(f64x4 (&v)[2][2]) {
     for (int q = 0; q < 8; ++q) {
         const int tq = q >> 2, rq = q & 3;
         const double row[2] = {v[tq][0][rq], v[tq][1][rq]}, src = row[tq];
-        auto at = [&](int r, int c) { return lane_value(src, 4 * rq + c + 16 * r); };
+        auto at = [&](int r, int c) { return of_lane(src, 4 * rq + c + 16 * r); };
         const double a00 = at(0, 0), a01 = at(0, 1), a02 = at(0, 2), a03 = at(0, 3), a11 = at(1, 1), a12 = at(1, 2),
                      a13 = at(1, 3), a22 = at(2, 2), a23 = at(2, 3), a33 = at(3, 3);
         // the inverse of [X Y; Y^T Z], 2 x 2 each, by X's inverse and that of S = Z - Y^T X^-1 Y
-        const double det = a00 * a11 - a01 * a01, rd = rcp_nr(det);
+        // (of a pivot that is zero or not finite the reciprocal is not finite; the flag is taken from the pivot itself)
+        const double det = a00 * a11 - a01 * a01, rd = fast_rcp(det);
         const double x00 = a11 * rd, x01 = -a01 * rd, x11 = a00 * rd;
         const double w00 = x00 * a02 + x01 * a12, w01 = x00 * a03 + x01 * a13;  // W = X^-1 Y
         const double w10 = x01 * a02 + x11 * a12, w11 = x01 * a03 + x11 * a13;
         const double s00 = a22 - (a02 * w00 + a12 * w10), s01 = a23 - (a02 * w01 + a12 * w11),
                      s11 = a33 - (a03 * w01 + a13 * w11);
-        const double dets = s00 * s11 - s01 * s01, rs = rcp_nr(dets);
+        const double dets = s00 * s11 - s01 * s01, rs = fast_rcp(dets);
         const double d22 = s11 * rs, d23 = -s01 * rs, d33 = s00 * rs;
         const double d02 = -(w00 * d22 + w01 * d23), d03 = -(w00 * d23 + w01 * d33);
         const double d12 = -(w10 * d22 + w11 * d23), d13 = -(w10 * d23 + w11 * d33);

@@ -15,6 +15,13 @@ __device__ __forceinline__ double fast_rcp(double x) {
 }
 __device__ __forceinline__ float fast_rcp(float x) { return __builtin_amdgcn_rcpf(x); }
 
+// the value that lane `lane` of the wave holds
+__device__ __forceinline__ double of_lane(double v, int lane) {
+    const uint64_t u = __builtin_bit_cast(uint64_t, v);
+    const unsigned lo = __builtin_amdgcn_readlane((unsigned)u, lane), hi = __builtin_amdgcn_readlane((unsigned)(u >> 32), lane);
+    return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+}
+
 // kappa = 1/rho at the face between cells of face densities ra and rb. FR = 0 (the default): the
 // factor 2 / (ra + rb) of the face-velocity update (step (viii)); FR = 1: the mean of the two
 // cells' kappa, (1/ra + 1/rb) / 2.

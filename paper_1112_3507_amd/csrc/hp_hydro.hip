@@ -36,23 +36,6 @@ struct HGeo {
     double dt;
 };
 
-// Neighbour of cell c along axis d in direction s (+1 / -1): its coordinate in *t, false when
-// there is no face (closed boundary).
-__device__ __forceinline__ bool neighbour(const HGeo& g, int d, int c, int s, int* t) {
-    int q = c + s;
-    const int n = g.n[d];
-    if (q < 0 || q >= n) {
-        if (!g.per[d]) return false;
-        q = q < 0 ? n - 1 : 0;
-    }
-    *t = q;
-    return true;
-}
-
-__device__ __forceinline__ int64_t cell(const HGeo& g, int i, int j, int k) {
-    return i + (int64_t)g.n[0] * (j + (int64_t)g.n[1] * k);
-}
-
 // eq. pbnd: the pressure at the interface between cells a and b
 __device__ __forceinline__ double pbnd(double pa, double ra, double pb, double rb) {
     return (pb * ra + pa * rb) / (ra + rb);

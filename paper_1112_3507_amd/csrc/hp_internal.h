@@ -94,8 +94,6 @@ void launch_setup_coef(const double* rho_mass, const double* rho_face, const dou
 // flux per face (natural layout; coef = dt^2 / h_d)
 void launch_neumann_rhs(int nx, int ny, int nz, int d, int side, double coef, const double* q, double* b,
                         hipStream_t s);
-// coarse rho and m as the means over each coarse cell's children (natural order; the FP32 copies
-// in the red-black split order with split32)
 // Where the coefficients of the finest level (rho_split and m_split only in split order, then the FP32 ones are, too)
 // and of the next one go.
 struct SetupOut {
@@ -109,6 +107,8 @@ struct SetupOut {
 // arrays don't allow it
 bool launch_setup_coarsen(const double* rho_mass, const double* rho_face, const double* c2, const SetupOut& o,
                           const Transfer& t, int* bad, hipStream_t s);
+// coarse rho and m as the means over each coarse cell's children (natural order; the FP32 copies
+// in the red-black split order with split32)
 void launch_coarsen_coef(const Transfer& t, const double* rho_f, const double* m_f,
                          double* rho_c, double* m_c, float* rho32_c, float* m32_c, bool split32,
                          hipStream_t s);

@@ -53,11 +53,6 @@ __device__ __forceinline__ double permuted(double v) {
     const unsigned hi = __builtin_amdgcn_update_dpp(0u, (unsigned)(u >> 32), CTRL, 0xf, 0xf, true);
     return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
 }
-__device__ __forceinline__ double of_lane(double v, int lane) {
-    const uint64_t u = __builtin_bit_cast(uint64_t, v);
-    const unsigned lo = __builtin_amdgcn_readlane((unsigned)u, lane), hi = __builtin_amdgcn_readlane((unsigned)(u >> 32), lane);
-    return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
-}
 __device__ __forceinline__ double wave_total(double v) {
     v += permuted<0xB1>(v);   // lanes 1 0 3 2 of each four
     v += permuted<0x4E>(v);   // lanes 2 3 0 1
