@@ -381,36 +381,42 @@ __global__ __launch_bounds__(256) void k_inverse_step(InverseArgs p) {
     __syncthreads();
     if (wave) return;
     f64x4 v[2][2];
-#pragma unroll
-    for (int w = 0; w < 4; ++w)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) v[w >> 1][w & 1][e] = own[(w * 4 + e) * 64 + lane];
-    // Where the diagonal holds values beyond 2^+-256, rows and columns are divided by powers of two near its square
-    // roots, before the sweep and after it: the sweep's 2 x 2 determinants would leave the range otherwise. (As the
-    // factors are powers of two, no other bit would change; always doing it cost 0.4 us a step.)
-    auto half_exponent = [&](int r) {
-        const int q = r & 15, at = ((r >> 4) * 12 + (q >> 2)) * 64 + 16 * (q & 3) + q;  // of entry (r, r)
-        return ((int)(((const unsigned*)own)[2 * at + 1] >> 20 & 0x7ffu) - 1023) >> 1;
-    };
-    auto scale = [&] {
-        asm volatile("" ::: "memory");  // (the exponents are read again after the sweep: kept, they cost a wave of occupancy)
-        const int col[2] = {half_exponent(c), half_exponent(16 + c)};
+    auto take = [&] {
 #pragma unroll
         for (int w = 0; w < 4; ++w)
 #pragma unroll
-            for (int e = 0; e < 4; ++e)
-                v[w >> 1][w & 1][e] = __builtin_ldexp(v[w >> 1][w & 1][e],
-                                                      -(half_exponent(16 * (w >> 1) + k + 4 * e) + col[w & 1]));
+            for (int e = 0; e < 4; ++e) v[w >> 1][w & 1][e] = own[(w * 4 + e) * 64 + lane];
     };
-    const bool far = __any(abs(half_exponent(lane & 31)) > 128);
-    if (far) scale();
+    take();
+    // Where the diagonal holds values beyond 2^+-256, rows and columns are divided by powers of two near its square
+    // roots, before the sweep and after it: the sweep's 2 x 2 determinants would leave the range otherwise. (As the
+    // factors are powers of two, no other bit would change; always doing it cost 0.4 us a step. The loops are rolled up:
+    // beside a pass over memory longer code took 2 us a step to fetch.)
+    __shared__ int half[kB];
+    const int r = lane & 31, q = r & 15, diagonal = ((r >> 4) * 12 + (q >> 2)) * 64 + 16 * (q & 3) + q;  // entry (r, r)
+    const int mine = ((int)(((const unsigned*)own)[2 * diagonal + 1] >> 20 & 0x7ffu) - 1023) >> 1;
+    const bool far = __any(abs(mine) > 128);
+    auto down = [&](int e) { return -(half[16 * (e >> 3) + k + 4 * (e & 3)] + half[16 * (e >> 2 & 1) + c]); };
+    if (far) {
+        half[r] = mine;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll 1
+        for (int e = 0; e < 16; ++e) own[e * 64 + lane] = __builtin_ldexp(own[e * 64 + lane], down(e));
+        take();
+    }
     if (!sweep_32(v) && lane == 0) *p.flag = 1;
-    if (far) scale();
     double* const to = p.diag + (then * kSet + slot_i) * kTile;
 #pragma unroll
     for (int w = 0; w < 4; ++w)
 #pragma unroll
         for (int e = 0; e < 4; ++e) to[(16 * (w >> 1) + k + 4 * e) * kB + 16 * (w & 1) + c] = -v[w >> 1][w & 1][e];
+    if (far) {
+#pragma unroll 1
+        for (int e = 0; e < 16; ++e) {
+            double* const x = to + (16 * (e >> 3) + k + 4 * (e & 3)) * kB + 16 * (e >> 2 & 1) + c;
+            *x = __builtin_ldexp(*x, down(e));
+        }
+    }
 }
 
 }  // namespace
