@@ -21,8 +21,8 @@
 // block of a pivot of the next step, inverts it at once (k_inverse_step). The products are matrix
 // instructions, whose operand layout is that of the rows as they lie in memory, and by symmetry
 // also that of the columns. A step takes 9 to 11 us, 6 of them the 32 pivots of the next. New coefficients
-// take 225 us on 96 x 56 x 192 cells (504 coarsest ones) and 141 on 64 x 64 (256); with two launches per 32
-// pivots, swept one at a time through LDS (15 us), and every block on its own it was 475 and 265.
+// took 225 us on 96 x 56 x 192 cells (504 coarsest ones) and 141 on 64 x 64 (256) when this came in, 475 and 265 with
+// two launches per 32 pivots, swept one at a time through LDS (15 us), and every block on its own.
 #include "hp_device.h"
 #include "hp_internal.h"
 

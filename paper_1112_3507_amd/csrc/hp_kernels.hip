@@ -310,8 +310,9 @@ void launch_coarsen_coef(const Transfer& t, const double* rho_f, const double* m
 }
 
 // k_setup_coef on the finest level and k_coarsen_coef towards the next one in one pass, NY x NZ rows of fine
-// cells and x pairs to a coarse cell: the coarsening reads nothing again. Bound by memory: 24 B in, 40 (split
-// 56) out per fine cell, 2.8 of them for the coarse one; at 256^3 157 us, 150 + 90 as two passes.
+// cells and x pairs to a coarse cell: the coarsening reads nothing again. Bound by memory: 16 B in per fine cell (24 with
+// two densities) and 27 out (43 in split order), 3 of them for the coarse one where all three axes are coarsened; at
+// 256^3 in split order 157 to 174 us over several runs, 150 to 155 + 90 to 92 as two passes.
 template <int NY, int NZ, bool SPLIT>
 __global__ __launch_bounds__(kBlock) void k_setup_coarsen(const double* __restrict__ rho_mass,
                                                           const double* __restrict__ rho_face,

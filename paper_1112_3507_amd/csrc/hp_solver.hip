@@ -827,11 +827,13 @@ void next_direction32(hp_handle* H, bool pre_done = false) {
 
 // Which levels and solves run as one launch (hp_small.hip), and their buffers. The levels that one
 // workgroup's LDS and registers hold do: an FP64 solve of 64 x 64 cells takes 320 us instead of 866 (29 us
-// an iteration, where its 25 launches took 79), of 16 x 16 x 16 cells 272 instead of 686; and one of 64^3, whose
-// V-cycles run in one launch from 16^3 cells down, 1357 instead of 1482. FP64 only: the mixed form keeps its
+// an iteration, where its 25 launches took 79), of 16 x 16 x 16 cells 275 instead of 675; for one of 64^3, whose
+// V-cycles run in one launch from 16^3 cells down, that is 1375 to 1395 instead of 1400 to 1485, within what separate
+// processes differ by (the host enqueues fewer launches: it gains where that is slow). FP64 only: the mixed form keeps its
 // launches, and with them the rounding of its FP32 cycles. Above 512 coarsest cells (odd sizes stop the
 // coarsening early) the helpers' registers don't hold the inverse, and under larger levels the coarsest
-// solve's own launch is the faster (224 x 80 x 44 cells with 1540: 2290 us against 2220); a whole solve
+// solve's own launch is the faster (224 x 80 x 44 cells with 1540: 2290 us against 2220; 160 x 96 x 72 with 540, where only
+// 28 of a row's columns are not held: 2274 against 2228); a whole solve
 // still gains (63 x 1 x 62 with 1953: 384 us against 640), and so does a V-cycle of its own up to 1024 of them, one turn
 // of two rows for every helper wave (66 x 1 x 62 with 1023: 25 us against 28; 45 x 1 x 50 with 1125 30 against 28, 63 x 1 x 62
 // 38 against 30).
