@@ -725,7 +725,7 @@ int solve_small(hp_handle* H, const double* b, double* x, double tol) {
     HIPCHK(hipStreamSynchronize(H->stream));
     st.iterations = t.iterations;
     st.restarts = t.rounds;
-    st.rel_residual = t.bb > 0.0 ? std::sqrt(t.rr / t.bb) : 0.0;
+    if (t.code == SMALL_CONVERGED || t.code == SMALL_BUDGET) st.rel_residual = t.bb > 0.0 ? std::sqrt(t.rr / t.bb) : 0.0;
     switch (t.code) {
         case SMALL_CONVERGED: st.converged = 1; return HP_OK;
         case SMALL_INPUT: return fail(HP_ENAN, "rhs or initial guess contains non-finite values");
